@@ -204,52 +204,6 @@ gemm_smfmac_kernel(const GemmArgs a, const int tiles_o, const int n_tiles)
     store_tile<FO, FT>(a, acc, o0 + wo * WO, t0 + wt * WT, li, lg);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Any pattern, any shape, any alignment, either layout: one thread per output element, walking
-// the metadata.
-// ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-gemm_generic_kernel(const GemmArgs a)
-{
-    const long long id_raw = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = (long long)a.tokens * a.O;
-    const bool live = id_raw < total;          // threads past the end recompute the last output and store nothing
-    const long long id = live ? id_raw : total - 1;
-    const int t = (int)(id / a.O), o = (int)(id % a.O);
-    const int ib = (a.N >= a.M) ? 0 : (a.M == 4) ? 2 : 4;
-    const int kc = a.K / a.M * a.N;
-    const int8_t* x = a.X + (size_t)t * a.ldx;
-    int sum = 0;
-    for (int e = 0; e < kc; ++e) {
-        int q, off;
-        if (a.bits == 8) q = (int8_t)a.vals[a.pv.at((uint32_t)o, (uint32_t)e)];
-        else { int nib = (a.vals[a.pv.at((uint32_t)o, (uint32_t)e >> 1)] >> ((e & 1) * 4)) & 15; q = (nib ^ 8) - 8; }
-        if (ib == 0) off = e % a.N;
-        else if (ib == 2) off = (a.meta[a.pm.at((uint32_t)o, (uint32_t)e >> 2)] >> ((e & 3) * 2)) & 3;
-        else off = (a.meta[a.pm.at((uint32_t)o, (uint32_t)e >> 1)] >> ((e & 1) * 4)) & 15;
-        sum += (int)x[(e / a.N) * a.M + off] * q;
-    }
-    const size_t at = (size_t)t * a.ldo + o;
-    const float s_act = act_scale_of(a);
-    if (a.out_dtype == 3) {                    // requantised output: every lane takes part in the reduction of max |y|
-        const float s_out = out_scale_of(a);
-        float g[4] = {0.f, 0.f, 0.f, 0.f}, h[4] = {0.f, 0.f, 0.f, 0.f};
-        requant_column(s_act, a.scales[o], a.bias ? a.bias[o] : 0.0f, s_out, g[0], h[0]);
-        float m = 0.0f;
-        const uint32_t q = requant4(v4i{sum, 0, 0, 0}, g, h, m);
-        if (live) reinterpret_cast<uint8_t*>(a.out)[at] = (uint8_t)q;
-        absmax_commit(m, s_out, a.absmax);
-        return;
-    }
-    if (!live) return;
-    if (a.acc) a.acc[at] = sum;
-    if (a.out_dtype != 0) {
-        float y = (float)sum * (s_act * a.scales[o]) + (a.bias ? a.bias[o] : 0.0f);
-        if (a.out_dtype == 1) reinterpret_cast<float*>(a.out)[at] = y;
-        else reinterpret_cast<uint16_t*>(a.out)[at] = (uint16_t)pack_bf16x2(y, 0.0f);
-    }
-}
-
 // Register-resident loop of the sparse MFMA (measurement hook, see nm_test_hooks.h).
 __global__ void __launch_bounds__(256)
 smfmac_probe_kernel(int iters, unsigned long long* counters)
@@ -414,8 +368,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t st)
 #undef NM_CASE
         return launch_status();
     }
-    const long long total = (long long)a.tokens * a.O;
-    hipLaunchKernelGGL(gemm_generic_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    launch_gemm_any(a, st);
     note_gemm_tile(-1);
     return launch_status();
 }

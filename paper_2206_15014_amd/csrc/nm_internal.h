@@ -144,6 +144,8 @@ int launch_quantize_act(const float* X, int tokens, int K, int ldx, float scale,
                         hipStream_t st);
 int launch_smfmac_probe(int blocks, int iters, unsigned long long* counters, hipStream_t st);
 int launch_gemm(const GemmArgs& a, hipStream_t st);
+// Every call the sparse-MFMA kernels do not take (nm_gemm_any.hip); part of launch_gemm's bracket.
+void launch_gemm_any(const GemmArgs& a, hipStream_t st);
 // `count` (1 .. GEMM_BATCH_MAX) GEMMs of one pattern, layout and output type: one launch where the
 // LDS-direct kernels cover every item, else one launch per item.
 int launch_gemm_batch(const GemmArgs* items, int count, hipStream_t st);
@@ -154,8 +156,8 @@ bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg);
 // Tile variant forced by the tests (0 = automatic), see nm_test_hooks.h.
 int forced_gemm_tile();
 // Records which kernel variant the last nm_gemm / nm_gemm_q8 / nm_gemm_batch call launched (the tile ids
-// of the LDS-direct kernels, 1 .. 3 for the register-staged shapes, -1 for the one-thread-per-output
-// kernel): read back by bench.py to group a step's launches by kernel.
+// of the LDS-direct kernels, 1 .. 3 for the register-staged shapes, -1 for the kernel of the odd
+// shapes): read back by bench.py to group a step's launches by kernel.
 void note_gemm_tile(int cfg);
 
 }  // namespace nm

@@ -27,8 +27,8 @@ int nm_bench_smfmac_probe(int blocks, int iters, unsigned long long *counters_de
 /*
  * Measurement hook of bench.py: the kernel variant that the most recent nm_gemm, nm_gemm_q8 or
  * nm_gemm_batch call of this process launched - the tile id of the LDS-direct kernels (>= 100),
- * 1 .. 3 for the register-staged kernel of the row layout, -1 for the one-thread-per-output
- * kernel, 0 before the first call.  bench.py groups the launches of a step by it, as a kernel
+ * 1 .. 3 for the register-staged kernel of the row layout, -1 for the kernel of the odd
+ * shapes, 0 before the first call.  bench.py groups the launches of a step by it, as a kernel
  * trace groups them by kernel name.  One process-wide atomic integer: meaningful only while one
  * thread issues the calls.
  */

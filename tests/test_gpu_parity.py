@@ -392,6 +392,37 @@ def test_gemm_generic_path_odd_shapes(N, M, bits, layout):
         check_outputs(acc_ref, sx, ref[2], bias, res["acc"], res["f32"], res["bf16"], what="T%d K%d O%d" % (T, K, O))
 
 
+@pytest.mark.parametrize("N,M,bits", ALL_SCHEMES + [(3, 8, 8), (5, 8, 4), (6, 8, 8), (6, 8, 4), (7, 8, 8)])
+@pytest.mark.parametrize("T,K,O,ldx,x_off,ldo,out_off", [
+    (31, 264, 33, 264, 0, 33, 0),          # one chunk and a row's end in the next, ragged tile edges
+    (33, 312, 64, 317, 3, 70, 1),          # no alignment anywhere
+    (65, 520, 36, 528, 0, 36, 0),          # aligned: stores of four outputs
+    (1300, 24, 1604, 24, 0, 1604, 0),      # enough output for the 64 x 64 tile
+    (1285, 256, 1601, 256, 0, 1601, 0),
+])
+def test_gemm_any_shape_alignment_and_pattern(N, M, bits, T, K, O, ldx, x_off, ldo, out_off):
+    """The kernel of the odd shapes at the edges of its chunks and tiles, on buffers at any byte address
+    that end with the last byte the call may touch."""
+    say("gemm any", N, M, bits, "T", T, "K", K, "O", O, "ldx", ldx, x_off, "ldo", ldo, out_off)
+    W, Xq, sx, bias, ref, acc_ref = small_case(N, M, bits, T, K, O, 31)
+    vals, meta, scales = gpu_compress(W, N, M, bits)
+    xbuf = torch.zeros(x_off + (T - 1) * ldx + K, dtype=torch.int8, device=DEV)
+    X = torch.as_strided(xbuf, (T, K), (ldx, 1), x_off)
+    X.copy_(torch.from_numpy(Xq))
+    b = torch.from_numpy(bias).to(DEV)
+    acc = torch.full((T, ldo), -7, dtype=torch.int32, device=DEV)
+    fbuf = torch.full((out_off + T * ldo,), -7.0, dtype=torch.float32, device=DEV)
+    hbuf = torch.full((out_off + T * ldo,), -7.0, dtype=torch.bfloat16, device=DEV)
+    f32, b16 = fbuf[out_off:].view(T, ldo), hbuf[out_off:].view(T, ldo)
+    nm.nm_gemm(X, float(sx), vals, meta, scales, O, N, M, bits, bias=b, acc=acc, out=f32, out_dtype=NM_OUT_F32, ldo=ldo)
+    nm.nm_gemm(X, float(sx), vals, meta, scales, O, N, M, bits, bias=b, out=b16, out_dtype=NM_OUT_BF16, ldo=ldo)
+    torch.cuda.synchronize()
+    assert torch.all(acc[:, O:] == -7) and torch.all(f32[:, O:] == -7.0) and torch.all(b16[:, O:] == -7.0)
+    assert torch.all(fbuf[:out_off] == -7.0) and torch.all(hbuf[:out_off] == -7.0)
+    check_outputs(acc_ref, sx, ref[2], bias, acc[:, :O].cpu().numpy(), f32[:, :O].cpu().numpy(),
+                  b16[:, :O].contiguous().view(torch.int16).cpu().numpy().view(np.uint16))
+
+
 def test_gemm_large_output_written_through_with_padded_rows():
     """A bf16 output large enough (>= 14 MB) to take the written-through stores of the wide tile, with
     padded output rows (the padding must stay untouched) and a ragged last column tile."""
