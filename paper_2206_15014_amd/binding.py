@@ -32,6 +32,7 @@ class GemmItem(ctypes.Structure):
 
 
 _lib = None
+_cuda = None          # (torch.cuda, torch._C), bound with the library
 
 
 class NMError(RuntimeError):
@@ -45,7 +46,7 @@ def library_path() -> str:
 
 
 def _load():
-    global _lib
+    global _lib, _cuda
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -54,7 +55,8 @@ def _load():
             % _LIB_PATH)
     # torch first: the process must hold ONE HIP runtime, and torch brings its own copy; with it
     # already loaded, libnm's dependency on libamdhip64 resolves to that same copy.
-    import torch  # noqa: F401
+    import torch
+    _cuda = torch.cuda, torch._C
     lib = ctypes.CDLL(_LIB_PATH)
     c_int, c_vp, c_f = ctypes.c_int, ctypes.c_void_p, ctypes.c_float
     szp = ctypes.POINTER(ctypes.c_size_t)
@@ -125,8 +127,12 @@ def _ptr(t) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        # The current stream's handle without the Stream object around it: 0.3 us instead of 3.1 us, a
+        # third of a whole nm_gemm call from Python (9.1 -> 6.2 us), which bounds the small layers.
+        cuda, c = _cuda
+        if cuda.is_initialized():
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        return cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
