@@ -294,6 +294,16 @@ struct Unit {
     }
 };
 
+// The arguments every workgroup needs before its first operand loads, fetched in one round trip
+// to the argument memory: left to itself the compiler fetches each where it is first used, four
+// dependent round trips of a few hundred nanoseconds each before the first load is issued.
+__device__ __forceinline__ void fetch_now(GemmArgs& a)
+{
+    asm volatile("" : "+s"(a.X), "+s"(a.vals), "+s"(a.meta), "+s"(a.scales), "+s"(a.bias), "+s"(a.tokens), "+s"(a.K),
+                      "+s"(a.ldx), "+s"(a.O), "+s"(a.k_rotate), "+s"(a.out), "+s"(a.acc), "+s"(a.out_dtype), "+s"(a.ldo),
+                      "+s"(a.store_through), "+s"(a.out_scale));
+}
+
 // ---------------------------------------------------------------------------------------------
 // LDS-direct operand staging (global_load_lds_dwordx4): geometry of one ring stage and the load /
 // wait primitives.  A direct load writes 64 lanes x 16 bytes to 1 KB of consecutive LDS in lane

@@ -326,6 +326,33 @@ def test_gemm_batch_falls_back_to_one_launch_per_item(layout, N, M, bits, shapes
     _gemm_batch(N, M, bits, layout, 0, shapes, seed=13)
 
 
+@pytest.mark.parametrize("tile", [130, 141, 142, 143, 144])
+@pytest.mark.parametrize("N,M,bits", FAST_SCHEMES + DUAL_SCHEMES + ODD8_SCHEMES)
+def test_gemm_few_tokens_kernels(N, M, bits, tile):
+    """The kernels that split K over the wavefronts of a workgroup: one slice, a remainder behind the eight,
+    whole shares of three, and a second round of four; ragged tiles; every output type; one launch for several layers."""
+    shapes = [(1, 128, 4), (17, 1152, 36), (33, 3072, 68), (15, 4224, 132)]
+    _gemm_small(N, M, bits, tile, TILED, shapes=shapes, seed=7)
+    with forced_tile(tile):
+        W, Xq, sx, bias, ref, acc_ref = small_case(N, M, bits, 33, 1152, 68, 8)
+        packed = gpu_compress(W, N, M, bits, layout=TILED)
+        so = q8_scale(acc_ref, sx, ref[2], bias)
+        q, amax = run_gemm_q8(Xq, sx, packed, 68, N, M, bits, bias, so, ldo=72, layout=TILED, device_scales=True)
+        assert np.all(q[:, 68:] == -77)
+        check_q8(acc_ref, sx, ref[2], bias, so, q[:, :68], amax)
+        outs, cases = [], [small_case(N, M, bits, T, K, O, 9) for T, K, O in shapes[:3]]
+        calls = []
+        for W, Xq, sx, bias, ref, acc_ref in cases:
+            v, m, sc = gpu_compress(W, N, M, bits, layout=TILED)
+            outs.append(torch.full((Xq.shape[0], W.shape[0]), -7.0, dtype=torch.float32, device=DEV))
+            calls.append({"X": torch.from_numpy(Xq).to(DEV), "act_scale": float(sx), "vals": v, "meta": m, "scales": sc, "O": W.shape[0],
+                          "bias": torch.from_numpy(bias).to(DEV), "out": outs[-1]})
+        nm.nm_gemm_batch(calls, N, M, bits, out_dtype=NM_OUT_F32, layout=TILED)
+        torch.cuda.synchronize()
+        for (W, Xq, sx, bias, ref, acc_ref), out in zip(cases, outs):
+            check_outputs(acc_ref, sx, ref[2], bias, None, out.cpu().numpy(), None, what="batch")
+
+
 @pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 8, 4), (4, 4, 8), (7, 8, 4)])
 def test_gemm_tiled_kernels_smallest_shapes(N, M, bits):
     """The smallest problems the matrix-core kernels of the tiled layout accept: one token, four output columns,
