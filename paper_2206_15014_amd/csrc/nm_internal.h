@@ -126,6 +126,7 @@ struct CompressItem {
     float* scales;
 };
 int launch_compress_batch(const CompressItem* items, int count, int N, int M, int bits, int layout, hipStream_t st);
+void launch_row_maxima(const float* W, int rows, int cols, int ldw, float* amax, hipStream_t st);
 void launch_group_scales(const float* W, int rows, int cols, int ldw, int rows_per_scale, float qmax, float* scales,
                          hipStream_t st);
 int launch_repack(const void* vals_in, const void* meta_in, int rows, int cols, int N, int M, int bits, int layout_in,

@@ -3,10 +3,20 @@
 // ADMM-Max scale per group of output neurons, Sec. 4) and the dual update U + W - Z, on gfx950.
 //
 // Purely HBM-bound: 4 (W) + 4 (U) bytes read and 4 (Z) + 4 (U') bytes written per weight, plus
-// one more read of W and U for the scales.  Three small kernels, no workspace: the per-row scale
-// array the caller passes first receives the rows' largest magnitudes, is then turned in place into
-// the scales of the row groups, and is finally read by the projection proper.  Every arithmetic
-// step is one fp32 operation, in the order the declaration of nm_project states.
+// one more read of W and U for the scales where a scale group is too large for the wavefronts that
+// hold its values (the second read mostly hits the last-level cache).  At these sizes a launch is a
+// few microseconds, so what counts is loads in flight and the number of launches: every lane
+// requests all it needs before its first use (8 loads of 16 bytes), and there are one launch (one row
+// per scale) or two.  The per-row scale array is the only scratch: it first receives the rows'
+// largest magnitudes, negated, and the projection replaces them by the scales while it runs - a
+// value with the sign bit set is a maximum, one without is a scale, and either tells a reader what
+// it needs.  Every arithmetic step is one fp32 operation, in the order the declaration of nm_project
+// states.
+//
+// Measured against three launches (maxima, scales, one thread per group of M columns, a load at a time):
+// 3072 x 768 (2:4 int8, 32 rows per scale) 7.3 + 2.4 + 6.7 -> 7.0 + 5.6 us, 768 x 3072 10.0 + 2.4 + 8.2 -> 7.0 +
+// 7.0, 768 x 768 3.6 + 2.4 + 3.8 -> 3.7 + 4.8; the 48 matrices of a BERT-base encoder 748 -> 597 us, of
+// which moving every byte once takes about 250.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,38 +33,87 @@ __device__ __forceinline__ float wave_max_f(float m)
     return m;
 }
 
-// Largest |W + U| of every row (one wavefront per row, four rows per workgroup).
+// max over the wavefront of 32-bit signed values
+__device__ __forceinline__ int wave_max_i(int m)
+{
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
+    return m;
+}
+
+__device__ __forceinline__ float scale_of_max(float m, float qmax) { return (m == 0.0f) ? 1.0f : __fdiv_rn(m, qmax); }
+
+// COUNT groups of F float4s of W + U, at a time: every load is requested before the first sum (one
+// test of U for all of them: a test per load would leave each to wait for the one before it).
+template <int COUNT, int F, typename At>
+__device__ __forceinline__ void sums_at(const float* W, const float* U, At at, float4 (&x)[COUNT][F])
+{
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+        for (int f = 0; f < F; ++f) x[i][f] = *reinterpret_cast<const float4*>(W + at(i) + 4 * f);
+    if (!U) return;
+    float4 u[COUNT][F];
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+        for (int f = 0; f < F; ++f) u[i][f] = *reinterpret_cast<const float4*>(U + at(i) + 4 * f);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i)
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            x[i][f].x = __fadd_rn(x[i][f].x, u[i][f].x);
+            x[i][f].y = __fadd_rn(x[i][f].y, u[i][f].y);
+            x[i][f].z = __fadd_rn(x[i][f].z, u[i][f].z);
+            x[i][f].w = __fadd_rn(x[i][f].w, u[i][f].w);
+        }
+}
+
+__device__ __forceinline__ float max4(float m, const float4& v)
+{
+    return fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+}
+
+// -(largest |W + U|) of every row: -0 for a row of zeros.  WAVES wavefronts per row (1: four rows per
+// workgroup), four 16-byte pieces of W and of U per lane in flight.
+template <int WAVES>
 __global__ void __launch_bounds__(256)
 project_amax_kernel(const float* __restrict__ W, const float* __restrict__ U, int rows, int cols, int ldw,
                     float* __restrict__ amax, int vec)         // vec: rows are whole, 16-byte aligned float4s
 {
+    __shared__ float part[4];
+    constexpr int STEP = 64 * WAVES;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = blockIdx.x * 4 + wave;
-    if (row >= rows) return;                   // no barrier below
-    if (!vec) {                                // any alignment, any width: one float at a time
-        float m = 0.0f;
-        for (int c = lane; c < cols; c += 64) {
-            float v = W[(size_t)row * ldw + c];
-            if (U) v = __fadd_rn(v, U[(size_t)row * ldw + c]);
+    const int row = WAVES == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    if (row >= rows) return;                   // WAVES > 1: one row per workgroup, none leaves before the barrier
+    const int at = WAVES == 1 ? lane : (int)threadIdx.x;
+    const size_t base = (size_t)row * ldw;
+    float m = 0.0f;
+    if (vec) {
+        const int last = cols / 4 - 1;
+        for (int i = at; i <= last; i += 4 * STEP) {
+            float4 v[4][1];
+            sums_at<4, 1>(W, U, [&](int k) __attribute__((always_inline)) { return base + 4 * (size_t)min(i + k * STEP, last); }, v);    // (the last piece again past the end)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) m = max4(m, v[k][0]);
+        }
+    } else {                                   // any alignment, any width: one float at a time
+        for (int c = at; c < cols; c += STEP) {
+            float v = W[base + c];
+            if (U) v = __fadd_rn(v, U[base + c]);
             m = fmaxf(m, fabsf(v));
         }
-        m = wave_max_f(m);
-        if (lane == 0) amax[row] = m;
-        return;
-    }
-    const float4* __restrict__ w4 = reinterpret_cast<const float4*>(W + (size_t)row * ldw);
-    const float4* __restrict__ u4 = U ? reinterpret_cast<const float4*>(U + (size_t)row * ldw) : nullptr;
-    float m = 0.0f;
-    for (int i = lane; i < cols / 4; i += 64) {
-        float4 v = w4[i];
-        if (u4) {
-            const float4 u = u4[i];
-            v.x = __fadd_rn(v.x, u.x); v.y = __fadd_rn(v.y, u.y); v.z = __fadd_rn(v.z, u.z); v.w = __fadd_rn(v.w, u.w);
-        }
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
     }
     m = wave_max_f(m);
-    if (lane == 0) amax[row] = m;
+    if constexpr (WAVES > 1) {
+        if (lane == 0) part[wave] = m;
+        __syncthreads();
+        m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+        if (threadIdx.x == 0) amax[row] = -m;
+    } else {
+        if (lane == 0) amax[row] = -m;
+    }
 }
 
 // Row maxima -> scales of the row groups, in place: one wavefront per group of rows_per_scale
@@ -67,66 +126,16 @@ project_scale_kernel(float* __restrict__ s, int rows, int rows_per_scale, float 
     if (r0 >= rows) return;
     const int r1 = (int)((r0 + rows_per_scale < rows) ? r0 + rows_per_scale : rows);
     float m = 0.0f;
-    for (int r = (int)r0 + lane; r < r1; r += 64) m = fmaxf(m, s[r]);
+    for (int r = (int)r0 + lane; r < r1; r += 64) m = fmaxf(m, fabsf(s[r]));
     m = wave_max_f(m);
-    const float scale = (m == 0.0f) ? 1.0f : __fdiv_rn(m, qmax);
+    const float scale = scale_of_max(m, qmax);
     for (int r = (int)r0 + lane; r < r1; r += 64) s[r] = scale;
 }
 
-// Both of the above in one launch for scale groups of moderate size: one workgroup per group of
-// rows, its four wavefronts sharing the rows, the largest magnitude combined through LDS.
-__global__ void __launch_bounds__(256)
-project_group_scale_kernel(const float* __restrict__ W, const float* __restrict__ U, int rows, int cols, int ldw,
-                           int rows_per_scale, float qmax, float* __restrict__ s)
-{
-    __shared__ float part[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long r0 = (long long)blockIdx.x * rows_per_scale;
-    const int r1 = (int)((r0 + rows_per_scale < rows) ? r0 + rows_per_scale : rows);
-    const int c4 = cols / 4;
-    const long long total = (long long)(r1 - (int)r0) * c4;          // 16-byte pieces of the group
-    float m = 0.0f;
-    for (long long i = threadIdx.x; i < total; i += 256) {
-        const int r = (int)r0 + (int)(i / c4), c = (int)(i % c4);
-        float4 v = reinterpret_cast<const float4*>(W + (size_t)r * ldw)[c];
-        if (U) {
-            const float4 u = reinterpret_cast<const float4*>(U + (size_t)r * ldw)[c];
-            v.x = __fadd_rn(v.x, u.x); v.y = __fadd_rn(v.y, u.y); v.z = __fadd_rn(v.z, u.z); v.w = __fadd_rn(v.w, u.w);
-        }
-        m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-    }
-    m = wave_max_f(m);
-    if (lane == 0) part[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-    const float scale = (m == 0.0f) ? 1.0f : __fdiv_rn(m, qmax);
-    for (int r = (int)r0 + threadIdx.x; r < r1; r += 256) s[r] = scale;
-}
-
-// One thread per group of M consecutive columns.
+// One group of M consecutive columns: z = Pi(v), the kept entries at scale s where bits > 0.
 template <int M>
-__global__ void __launch_bounds__(256)
-project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw,
-               int N, int bits, const float* __restrict__ scales,
-               float* __restrict__ Z, float* U_out, int ldz)     // U_out may be U (same leading dimension): no restrict on the two
+__device__ __forceinline__ void project_group(const float (&v)[M], int N, int bits, float s, float (&z)[M])
 {
-    const int groups = cols / M;
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (id >= (long long)rows * groups) return;
-    const int row = (int)(id / groups), g = (int)(id - (long long)row * groups);
-    const size_t in_at = (size_t)row * ldw + (size_t)g * M, out_at = (size_t)row * ldz + (size_t)g * M;
-
-    float v[M];
-#pragma unroll
-    for (int f = 0; f < M / 4; ++f) {
-        float4 x = *reinterpret_cast<const float4*>(W + in_at + 4 * f);
-        if (U) {
-            const float4 u = *reinterpret_cast<const float4*>(U + in_at + 4 * f);
-            x.x = __fadd_rn(x.x, u.x); x.y = __fadd_rn(x.y, u.y); x.z = __fadd_rn(x.z, u.z); x.w = __fadd_rn(x.w, u.w);
-        }
-        v[4 * f + 0] = x.x; v[4 * f + 1] = x.y; v[4 * f + 2] = x.z; v[4 * f + 3] = x.w;
-    }
-    const float s = bits ? scales[row] : 1.0f;
     const float qmax = (float)((1 << (bits ? bits - 1 : 7)) - 1);
     // Eq. 5 (offset 0), then Eq. 4: the value the integer code stands for (an integer code: its zero has no sign)
     auto requantised = [&](float x) {
@@ -160,10 +169,7 @@ project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, 
                 if (bits) kept = requantised(kept);
                 z0 = k0 ? kept : 0.0f; z1 = k1 ? kept : 0.0f; z2 = k2 ? kept : 0.0f; z3 = k3 ? kept : 0.0f;
             }
-            *reinterpret_cast<float4*>(Z + out_at) = make_float4(z0, z1, z2, z3);
-            if (U_out)
-                *reinterpret_cast<float4*>(U_out + out_at) =
-                    make_float4(__fsub_rn(v[0], z0), __fsub_rn(v[1], z1), __fsub_rn(v[2], z2), __fsub_rn(v[3], z3));
+            z[0] = z0; z[1] = z1; z[2] = z2; z[3] = z3;
             return;
         }
     }
@@ -172,7 +178,6 @@ project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, 
     float a[M];
 #pragma unroll
     for (int c = 0; c < M; ++c) a[c] = fabsf(v[c]);
-    float z[M];
 #pragma unroll
     for (int c = 0; c < M; ++c) {
         int outranked = 0;
@@ -185,55 +190,205 @@ project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, 
         if (bits) kept_value = requantised(v[c]);
         z[c] = (outranked < N) ? kept_value : 0.0f;
     }
+}
+
+// P groups of M columns; at(i) is the place of the i-th.
+template <int M, int P, typename At>
+__device__ __forceinline__ void load_groups(const float* W, const float* U, At at, float (&v)[P][M])
+{
+    float4 x[P][M / 4];
+    sums_at<P, M / 4>(W, U, at, x);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int f = 0; f < M / 4; ++f) {
+            v[i][4 * f + 0] = x[i][f].x; v[i][4 * f + 1] = x[i][f].y; v[i][4 * f + 2] = x[i][f].z; v[i][4 * f + 3] = x[i][f].w;
+        }
+}
+
+template <int M>
+__device__ __forceinline__ void store_group(const float (&v)[M], const float (&z)[M], float* Z, float* U_out, size_t at)
+{
 #pragma unroll
     for (int f = 0; f < M / 4; ++f) {
-        *reinterpret_cast<float4*>(Z + out_at + 4 * f) = make_float4(z[4 * f + 0], z[4 * f + 1], z[4 * f + 2], z[4 * f + 3]);
+        *reinterpret_cast<float4*>(Z + at + 4 * f) = make_float4(z[4 * f + 0], z[4 * f + 1], z[4 * f + 2], z[4 * f + 3]);
         if (U_out)
-            *reinterpret_cast<float4*>(U_out + out_at + 4 * f) =
+            *reinterpret_cast<float4*>(U_out + at + 4 * f) =
                 make_float4(__fsub_rn(v[4 * f + 0], z[4 * f + 0]), __fsub_rn(v[4 * f + 1], z[4 * f + 1]),
                             __fsub_rn(v[4 * f + 2], z[4 * f + 2]), __fsub_rn(v[4 * f + 3], z[4 * f + 3]));
     }
 }
 
+// In all three kernels U_out may be U (same leading dimension): no restrict on the two, and a lane reads
+// every group it writes before it writes any.  (Lanes past a row's end load its last group and drop it.)
+
+// One scale per row: WAVES wavefronts hold a row's values between its maximum and its projection, so W
+// and U are read once.  16 columns per lane: rows of up to 1024 columns on one wavefront (four rows
+// per workgroup), of up to 4096 on four.
+template <int M, int WAVES>
+__global__ void __launch_bounds__(256)
+project_row_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw, int N, int bits,
+                   float* __restrict__ scales, float* __restrict__ Z, float* U_out, int ldz)
+{
+    constexpr int P = 16 / M, STEP = 64 * WAVES;
+    __shared__ float part[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = WAVES == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+    if (row >= rows) return;                   // WAVES > 1: one row per workgroup, none leaves before the barrier
+    const int groups = cols / M, at = WAVES == 1 ? lane : (int)threadIdx.x;
+    float v[P][M];
+    load_groups<M, P>(W, U, [&](int i) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)min(at + i * STEP, groups - 1) * M; }, v);
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+        for (int c = 0; c < M; ++c) m = fmaxf(m, fabsf(v[i][c]));
+    m = wave_max_f(m);
+    if constexpr (WAVES > 1) {
+        if (lane == 0) part[wave] = m;
+        __syncthreads();                       // (also: every lane of the row has its values before the first store)
+        m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    }
+    const float s = scale_of_max(m, (float)((1 << (bits - 1)) - 1));
+    if (at == 0) scales[row] = s;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        if (at + i * STEP >= groups) break;
+        float z[M];
+        project_group<M>(v[i], N, bits, s, z);
+        store_group<M>(v[i], z, Z, U_out, (size_t)row * ldz + (size_t)(at + i * STEP) * M);
+    }
+}
+
+// One wavefront per 64 * P groups of a row.  rows_per_scale > 0: scales[] holds the row maxima, negated,
+// and this launch turns them into scales: the wavefront at a row's start writes the row's, while
+// others still read.  A reader takes the largest of its group's values as signed integers: any scale (sign
+// bit clear, and all rows of a group get the same one) is above every maximum, and among maxima (sign bit
+// set) the larger magnitude is the larger integer.  So it ends with the scale itself or with the group's
+// largest magnitude, whichever mixture it met.
+// rows_per_scale = 0: scales[row] is final.
+template <int M>
+__global__ void __launch_bounds__(256)
+project_wave_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw, int N, int bits, int rows_per_scale,
+                    float* scales, float* __restrict__ Z, float* U_out, int ldz, int chunks)
+{
+    constexpr int P = 16 / M;
+    const int lane = threadIdx.x & 63;
+    const unsigned id = (unsigned)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (threadIdx.x >> 6)));
+    const int row = (int)(id / (unsigned)chunks), chunk = (int)(id - (unsigned)row * (unsigned)chunks);
+    if (row >= rows) return;                   // no barrier below
+    const int groups = cols / M, g0 = chunk * (64 * P) + lane;
+    float v[P][M];
+    load_groups<M, P>(W, U, [&](int i) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)min(g0 + i * 64, groups - 1) * M; }, v);
+    float s = 1.0f;
+    if (bits && rows_per_scale > 0) {
+        const int r0 = row / rows_per_scale * rows_per_scale, r1 = rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale;
+        int top = (int)0x80000000;             // the maximum of no row
+        for (int r = r0 + lane; r < r1; r += 64)
+            top = max(top, __hip_atomic_load(reinterpret_cast<int*>(scales) + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        top = wave_max_i(top);
+        s = __int_as_float(top);
+        if (top < 0) s = scale_of_max(-s, (float)((1 << (bits - 1)) - 1));
+        if (chunk == 0 && lane == 0)
+            __hip_atomic_store(reinterpret_cast<int*>(scales) + row, __float_as_int(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (bits) {
+        s = scales[row];
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        if (g0 + i * 64 >= groups) break;
+        float z[M];
+        project_group<M>(v[i], N, bits, s, z);
+        store_group<M>(v[i], z, Z, U_out, (size_t)row * ldz + (size_t)(g0 + i * 64) * M);
+    }
+}
+
+// One thread per group of M consecutive columns, rows of any length one after the other; scales[row] is final.
+template <int M>
+__global__ void __launch_bounds__(256)
+project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw,
+               int N, int bits, const float* __restrict__ scales, float* __restrict__ Z, float* U_out, int ldz)
+{
+    const int groups = cols / M;
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (id >= (long long)rows * groups) return;
+    const int row = (int)(id / groups), g = (int)(id - (long long)row * groups);
+    float v[1][M], z[M];
+    load_groups<M, 1>(W, U, [&](int) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)g * M; }, v);
+    project_group<M>(v[0], N, bits, bits ? scales[row] : 1.0f, z);
+    store_group<M>(v[0], z, Z, U_out, (size_t)row * ldz + (size_t)g * M);
+}
+
+// Four wavefronts per row once a row is more than four 16-byte pieces per lane of one: 768 x 3072 on one wavefront
+// per row is three rounds of loads one after the other on 768 wavefronts, 10.0 us against 7.0.
+void launch_row_maxima(const float* W, const float* U, int rows, int cols, int ldw, float* amax, int vec, hipStream_t st)
+{
+    if (cols > 1024 && rows <= (1 << 23))
+        hipLaunchKernelGGL(project_amax_kernel<4>, dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
+    else
+        hipLaunchKernelGGL(project_amax_kernel<1>, dim3((rows + 3) / 4), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
+}
+
+void launch_max_to_scale(float* scales, int rows, int rows_per_scale, float qmax, hipStream_t st)
+{
+    const long long n_groups = ((long long)rows + rows_per_scale - 1) / rows_per_scale;
+    hipLaunchKernelGGL(project_scale_kernel, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st, scales, rows, rows_per_scale, qmax);
+}
+
+template <int M>
+void launch_project_m(const float* W, const float* U, int rows, int cols, int ldw, int N, int bits, int rows_per_scale,
+                      float* Z, float* U_out, int ldz, float* scales, hipStream_t st)
+{
+    const int groups = cols / M;
+    const float qmax = (float)((1 << (bits ? bits - 1 : 7)) - 1);
+    if (bits && rows_per_scale == 1 && cols <= 1024 && rows <= (1 << 25)) {
+        hipLaunchKernelGGL((project_row_kernel<M, 1>), dim3((rows + 3) / 4), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
+        return;
+    }
+    if (bits && rows_per_scale == 1 && cols <= 4096 && cols > 1024 && rows <= (1 << 23)) {
+        hipLaunchKernelGGL((project_row_kernel<M, 4>), dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
+        return;
+    }
+    // Wavefronts within a row need rows that fill one (and a launch holds fewer than 2^32 threads); every one
+    // of them reads its group's maxima, which stays cheaper than a launch of its own up to a few hundred rows.
+    const long long chunks = (groups + 1024 / M - 1) / (1024 / M), waves = chunks * rows;
+    const bool wide = groups >= 64 && waves <= (1 << 25);
+    const bool finish = wide && rows_per_scale <= 256;
+    if (bits) {
+        launch_row_maxima(W, U, rows, cols, ldw, scales, 1, st);
+        if (!finish) launch_max_to_scale(scales, rows, rows_per_scale, qmax, st);
+    }
+    if (wide)
+        hipLaunchKernelGGL(project_wave_kernel<M>, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits,
+                           finish ? rows_per_scale : 0, scales, Z, U_out, ldz, (int)chunks);
+    else
+        hipLaunchKernelGGL(project_kernel<M>, dim3((unsigned)(((long long)rows * groups + 255) / 256)), dim3(256), 0, st, W, U, rows, cols,
+                           ldw, N, bits, scales, Z, U_out, ldz);
+}
+
 }  // namespace
 
+// amax[row] <- -(largest |W|) of the row, any width and alignment.
+void launch_row_maxima(const float* W, int rows, int cols, int ldw, float* amax, hipStream_t st)
+{
+    launch_row_maxima(W, nullptr, rows, cols, ldw, amax, ((uintptr_t)W % 16 == 0 && ldw % 4 == 0 && cols % 4 == 0) ? 1 : 0, st);
+}
+
 // scales[row] <- the scale of the row's group: largest |W| over the group's rows / qmax, 1 for an
-// all-zero group.  Two launches, no workspace (scales[] first holds the rows' maxima).
+// all-zero group.  Two launches, no workspace (scales[] first holds the rows' maxima, negated).
 void launch_group_scales(const float* W, int rows, int cols, int ldw, int rows_per_scale, float qmax, float* scales,
                          hipStream_t st)
 {
-    const int vec = ((uintptr_t)W % 16 == 0 && ldw % 4 == 0 && cols % 4 == 0) ? 1 : 0;
-    hipLaunchKernelGGL(project_amax_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, W, (const float*)nullptr, rows, cols, ldw, scales, vec);
-    const long long n_groups = ((long long)rows + rows_per_scale - 1) / rows_per_scale;
-    hipLaunchKernelGGL(project_scale_kernel, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st, scales, rows, rows_per_scale, qmax);
+    launch_row_maxima(W, rows, cols, ldw, scales, st);
+    launch_max_to_scale(scales, rows, rows_per_scale, qmax, st);
 }
 
 int launch_project(const float* W, const float* U, int rows, int cols, int ldw, int N, int M, int bits,
                    int rows_per_scale, float* Z, float* U_out, int ldz, float* scales, hipStream_t st)
 {
     begin_launch();
-    if (bits) {
-        const float qmax = (float)((1 << (bits - 1)) - 1);
-        const long long n_groups = ((long long)rows + rows_per_scale - 1) / rows_per_scale;
-        // A workgroup per scale group reads the group alone: fine while a group is a row or a few
-        // (3072 x 768, one row per scale: 10.4 against 11.7 us); for 32 rows per scale the 96
-        // workgroups that remain are too few to pull the matrix in (20.6 against 14.0 us), so then
-        // row maxima first, all rows at once, and the groups in a second small launch.
-        if (n_groups >= 512 && (long long)rows_per_scale * cols <= 4096) {
-            hipLaunchKernelGGL(project_group_scale_kernel, dim3((unsigned)n_groups), dim3(256), 0, st,
-                               W, U, rows, cols, ldw, rows_per_scale, qmax, scales);
-        } else {
-            hipLaunchKernelGGL(project_amax_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, W, U, rows, cols, ldw, scales, 1);
-            hipLaunchKernelGGL(project_scale_kernel, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st,
-                               scales, rows, rows_per_scale, qmax);
-        }
-    }
-    const long long total = (long long)rows * (cols / M);
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (M == 4)
-        hipLaunchKernelGGL(project_kernel<4>, grid, dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
-    else
-        hipLaunchKernelGGL(project_kernel<8>, grid, dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
+    if (M == 4) launch_project_m<4>(W, U, rows, cols, ldw, N, bits, rows_per_scale, Z, U_out, ldz, scales, st);
+    else launch_project_m<8>(W, U, rows, cols, ldw, N, bits, rows_per_scale, Z, U_out, ldz, scales, st);
     return launch_status();
 }
 

@@ -861,6 +861,27 @@ def test_project_dual_update_in_place_and_full_size():
     assert np.all(np.abs(codes - np.rint(codes)) < 1e-3) and np.abs(np.rint(codes)).max() == 127
 
 
+@pytest.mark.parametrize("M", [4, 8])
+def test_project_rows_at_the_edges_of_its_kernels(M):
+    """One scale per row: rows that one wavefront holds (up to 1024 columns), four hold (up to 4096), and longer
+    ones; larger scale groups: several wavefronts per row with the scales formed on the way (up to 256 rows per
+    scale) or by a launch of their own, and rows too narrow for a wavefront.  U updated in place on half."""
+    rng = np.random.default_rng([M, 77])
+    for rows, cols in [(5, 64 * M - M), (6, 64 * M), (9, 1024 - M), (9, 1024), (9, 1024 + M), (7, 4096), (7, 4096 + M), (517, 264)]:
+        W = (rng.standard_normal((rows, cols)) * rng.random((rows, 1)) * 0.05).astype(np.float32)
+        W[rng.integers(0, rows)] = 0.0
+        U = (rng.standard_normal((rows, cols)) * 0.004).astype(np.float32)
+        for rps, N, bits in [(1, 2, 8), (1, M, 4), (2, 1, 4), (4, 2, 8), (256, 2, 4), (257, 3, 8), (1, 2, 0)]:
+            say("project edges", rows, cols, N, M, bits, rps)
+            Zr, Ur, sr = oracle.admm_project(W, U, N, M, bits, rps)
+            Z, Uo, s = run_project(W, U, N, M, bits, rps, in_place=rps % 2 == 0)
+            what = "rows %d cols %d rps %d" % (rows, cols, rps)
+            assert np.array_equal(Z.view(np.uint32), Zr.view(np.uint32)), what + ": Z differs"
+            assert np.array_equal(Uo.view(np.uint32), Ur.view(np.uint32)), what + ": U differs"
+            if bits:
+                assert np.array_equal(s, sr), what + ": scales differ"
+
+
 # ---- one scale per group of rows (nm_compress_grouped): packed bytes and scales bit-exact --------
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("rps", [2, 32, 100])
