@@ -3,13 +3,24 @@
 // their quantised values, searched over the candidate grid that the declaration in include/nm.h
 // fixes (the paper states the criterion, not an algorithm).
 //
-// Three launches: the groups' max-rule scales (into the scales array), the error of every
-// candidate per row (one wavefront per row, double precision, into the workspace), and per group
-// the sum over its rows and the choice.  The per-row partial errors are the only scratch memory:
-// [rows][candidates / 2 + 1] doubles.  Sums run in a fixed order (lane-strided partial sums, a fixed
-// butterfly over the wavefront, then the rows of a group one after the other), so a call is
-// deterministic; it is not the CPU's plain left-to-right order, so candidates whose errors agree
-// to about 1e-15 relative can be ranked differently than there.
+// Three launches: the rows' largest magnitudes (into the scales array, negated), the error of every
+// candidate per row (one workgroup per row, double precision, into the workspace), and per group
+// the sum over its rows and the choice; the last two form the group's max-rule scale themselves.
+// The per-row partial errors are the only scratch memory: [rows][candidates / 2 + 1] doubles.  Sums
+// run in a fixed order (lane-strided partial sums, a fixed butterfly over the wavefront, then the
+// rows of a group one after the other), so a call is deterministic; it is not the CPU's plain
+// left-to-right order, so candidates whose errors agree to about 1e-15 relative can be ranked
+// differently than there.
+//
+// The error launch is bound by arithmetic: about a dozen operations per kept weight and candidate, three
+// of them in double.  The four wavefronts of a row share its candidates, not its columns, so a
+// candidate's sum keeps its order and a matrix of 768 rows has 3072 wavefronts; the kept entries of a
+// group are picked out first, so no lane idles on a column that is not kept; and the quotients come
+// from the candidate's reciprocal (five operations, see nm_quantize.h) instead of a division.
+// Measured against four wavefronts' rows per workgroup, every column tried under a mask, a division per quotient and
+// the maxima turned into scales by a launch of their own (2:4 int8, 32 candidates, 32 rows per scale): the
+// error launch 3072 x 768 41.1 -> 18.6 us, 768 x 3072 54.2 -> 22; the choice, which added 32 rows one load
+// after the other, 11.6 -> 4.0; weights of a BERT-base layer to deployed ones 281 -> 146 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -17,6 +28,7 @@
 
 #include "nm.h"
 #include "nm_internal.h"
+#include "nm_quantize.h"
 
 // Scratch of the entry point that allocates nothing (nm_scale_search_static): the rows' partial
 // errors live in this array instead of a caller's workspace.  Every GPU the library runs on holds
@@ -28,83 +40,155 @@ namespace nm {
 
 namespace {
 
-constexpr int MAX_CAND = 33;                   // candidates / 2 + 1 with candidates <= 64
-
 __device__ __forceinline__ float candidate_scale(float smax, int c, int candidates)
 {
     return __fdiv_rn(__fmul_rn(smax, (float)c), (float)candidates);
 }
 
-// scales[row] holds the max-rule scale of the row's group.  err[row][k] = sum over the row's kept
-// entries of (w - s_k * q_k(w))^2 for candidate k = c - candidates / 2.
-template <int M>
-__global__ void __launch_bounds__(256)
-row_errors_kernel(const float* __restrict__ W, int rows, int cols, int ldw, int N, int bits, int candidates,
-                  const float* __restrict__ scales, double* __restrict__ err)
+// The max-rule scale of rows r0 .. r1-1: from their maxima (negated) where `maxima`, else as it stands.
+__device__ __forceinline__ float max_rule_scale(const float* scales, int r0, int r1, int maxima, float qmax, int lane)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = blockIdx.x * 4 + wave;
-    if (row >= rows) return;                   // no barrier below
-    const int nc = candidates / 2 + 1;
-    const float smax = scales[row];
-    const float qmax = (float)((1 << (bits - 1)) - 1);
-    double e[MAX_CAND];
+    if (!maxima) return scales[r0];
+    float m = 0.0f;
+    for (int r = r0 + lane; r < r1; r += 64) m = fmaxf(m, fabsf(scales[r]));
 #pragma unroll
-    for (int k = 0; k < MAX_CAND; ++k) e[k] = 0.0;
-    const float* w = W + (size_t)row * ldw;
-    for (int g = lane; g < cols / M; g += 64) {
-        float v[M], a[M];
+    for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+    return (m == 0.0f) ? 1.0f : __fdiv_rn(m, qmax);
+}
+
+// CPW sums of one wavefront over a row: e[i] = sum over the kept entries of (w - s_i * q_i(w))^2, the
+// candidates' scales in d[].  Columns in the order lane, lane + 64, ... (groups of M), kept entries of a group from
+// the lowest column up.
+template <int N, int M, int CPW, bool RECIP>
+__device__ __forceinline__ void row_sums(const float* __restrict__ w, int groups, int lane, float qmax, const Divisor<RECIP> (&d)[CPW], double (&e)[CPW])
+{
+    double neg[CPW];
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        neg[i] = -(double)d[i].s;
+        e[i] = 0.0;
+    }
+    float next[M];
+    __builtin_memcpy(next, w + (size_t)min(lane, groups - 1) * M, 4 * M);
+    for (int g = lane; g < groups; g += 64) {
+        float v[M], a[M], kept[N];
 #pragma unroll
         for (int c = 0; c < M; ++c) {
-            v[c] = w[g * M + c];
+            v[c] = next[c];
             a[c] = fabsf(v[c]);
         }
+        __builtin_memcpy(next, w + (size_t)min(g + 64, groups - 1) * M, 4 * M);
+        if constexpr (N == M) {
 #pragma unroll
-        for (int c = 0; c < M; ++c) {
-            // Eq. 3: kept when fewer than N entries outrank it (larger magnitude, or equal and a lower column)
-            int outranked = 0;
+            for (int c = 0; c < M; ++c) kept[c] = v[c];
+        } else {
+            bool nan = false;
 #pragma unroll
-            for (int d = 0; d < M; ++d) {
-                if (d == c) continue;
-                outranked += (d < c) ? (a[d] >= a[c]) : (a[d] > a[c]);
-            }
-            if (outranked >= N) continue;
+            for (int c = 0; c < M; ++c) nan = nan || !(v[c] == v[c]);
+            if constexpr (N == 2 && M == 4) {
+                // the six comparisons decide every pair (the lower column outranks on >=); an entry is kept
+                // when at most one outranks it
+                const bool c01 = a[0] >= a[1], c02 = a[0] >= a[2], c03 = a[0] >= a[3], c12 = a[1] >= a[2], c13 = a[1] >= a[3], c23 = a[2] >= a[3];
+                auto under_two = [](bool p, bool q, bool r) { return !((p && q) || (p && r) || (q && r)); };
+                const bool k0 = under_two(!c01, !c02, !c03), k1 = under_two(c01, !c12, !c13);
+                const bool k2 = under_two(c02, c12, !c23), k3 = under_two(c03, c13, c23);
+                kept[0] = k0 ? v[0] : (k1 ? v[1] : v[2]);
+                kept[1] = k3 ? v[3] : (k2 ? v[2] : v[1]);
+            } else {
+                int at = 0;
 #pragma unroll
-            for (int k = 0; k < MAX_CAND; ++k) {
-                if (k < nc) {
-                    const float s = candidate_scale(smax, candidates / 2 + k, candidates);
-                    const float q = fminf(fmaxf(rintf(__fdiv_rn(v[c], s)), -qmax), qmax);      // Eq. 5, offset 0
-                    const double d = __dsub_rn((double)v[c], __dmul_rn((double)s, (double)q));
-                    e[k] = __dadd_rn(e[k], __dmul_rn(d, d));
+                for (int j = 0; j < N; ++j) kept[j] = 0.0f;
+#pragma unroll
+                for (int c = 0; c < M; ++c) {
+                    // Eq. 3: kept when fewer than N entries outrank it (larger magnitude, or equal and a lower column)
+                    int outranked = 0;
+#pragma unroll
+                    for (int k = 0; k < M; ++k) {
+                        if (k == c) continue;
+                        outranked += (k < c) ? (a[k] >= a[c]) : (a[k] > a[c]);
+                    }
+                    const bool keep = outranked < N;
+#pragma unroll
+                    for (int j = 0; j < N; ++j) kept[j] = (keep && at == j) ? v[c] : kept[j];
+                    at += keep ? 1 : 0;
                 }
             }
+            // nothing outranks a NaN, so it is kept - maybe as one too many: it must reach the sum
+            if (nan) kept[0] = __builtin_nanf("");
         }
-    }
 #pragma unroll
-    for (int k = 0; k < MAX_CAND; ++k) {
-        if (k < nc) {
-            double t = e[k];
+        for (int j = 0; j < N; ++j) {
+            const double x = (double)kept[j];
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) t = __dadd_rn(t, __shfl_xor(t, d, 64));
-            if (lane == 0) err[(size_t)row * nc + k] = t;
+            for (int i = 0; i < CPW; ++i) {
+                const float q = __builtin_amdgcn_fmed3f(rintf(d[i].quotient(kept[j])), -qmax, qmax);      // Eq. 5, offset 0 (of a NaN, r is one)
+                const double r = __fma_rn(neg[i], (double)q, x);                               // (the product is exact: 31 bits)
+                e[i] = __dadd_rn(e[i], __dmul_rn(r, r));
+            }
         }
     }
 }
 
-// One wavefront per scale group: lane k sums candidate k over the group's rows, then the least
-// error wins, the larger scale between equal errors; every row of the group receives the scale.
+// scales[]: the rows' maxima, negated (maxima != 0), or every row's max-rule scale.  err[row][k] = the row's
+// sum for candidate k = c - candidates / 2.  Wavefront w of the workgroup takes candidates w, w + 4, ...
+template <int N, int M, int CPW>
 __global__ void __launch_bounds__(256)
-choose_scale_kernel(const double* __restrict__ err, int rows, int rows_per_scale, int candidates, float* __restrict__ scales)
+row_errors_kernel(const float* __restrict__ W, int rows, int cols, int ldw, float qmax, int rows_per_scale, int maxima, int candidates,
+                  const float* __restrict__ scales, double* __restrict__ err)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long r0 = ((long long)blockIdx.x * 4 + wave) * rows_per_scale;
-    if (r0 >= rows) return;
-    const int r1 = (int)((r0 + rows_per_scale < rows) ? r0 + rows_per_scale : rows);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nc = candidates / 2 + 1;
-    const float smax = scales[r0];             // read before any row of the group is overwritten (same wavefront)
+    for (int row = blockIdx.x; row < rows; row += gridDim.x) {           // no barrier below
+        const int r0 = maxima ? row / rows_per_scale * rows_per_scale : row;
+        const float smax = max_rule_scale(scales, r0, rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale, maxima, qmax, lane);
+        double e[CPW];
+        float s[CPW];
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) s[i] = candidate_scale(smax, candidates / 2 + min(wave + 4 * i, nc - 1), candidates);
+        // The candidates lie between half of smax and smax, and |w| is at most 127 smax: within the range of the
+        // reciprocal route, which holds up to |w| = 254 s as it does up to 127 s.
+        if (smax >= 0x1p-59f && smax <= 0x1p60f) {
+            Divisor<true> d[CPW];
+#pragma unroll
+            for (int i = 0; i < CPW; ++i) d[i] = Divisor<true>{s[i], __fdiv_rn(1.0f, s[i])};
+            row_sums<N, M, CPW, true>(W + (size_t)row * ldw, cols / M, lane, qmax, d, e);
+        } else {
+            Divisor<false> d[CPW];
+#pragma unroll
+            for (int i = 0; i < CPW; ++i) d[i] = Divisor<false>{s[i], 0.0f};
+            row_sums<N, M, CPW, false>(W + (size_t)row * ldw, cols / M, lane, qmax, d, e);
+        }
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            double t = e[i];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) t = __dadd_rn(t, __shfl_xor(t, d, 64));
+            if (lane == 0 && wave + 4 * i < nc) err[(size_t)row * nc + wave + 4 * i] = t;
+        }
+    }
+}
+
+// One wavefront per scale group: lane k sums candidate k over the group's rows (sixteen loads in flight), then
+// the least error wins, the larger scale between equal errors; every row of the group receives the scale.
+__global__ void __launch_bounds__(64)
+choose_scale_kernel(const double* __restrict__ err, int rows, int rows_per_scale, int maxima, float qmax, int candidates, float* scales)
+{
+    const int lane = threadIdx.x;
+    const long long first = (long long)blockIdx.x * rows_per_scale;
+    if (first >= rows) return;
+    const int r0 = (int)first, r1 = rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale;
+    const int nc = candidates / 2 + 1;
+    const double* mine = err + min(lane, nc - 1);
     double total = 0.0;
-    if (lane < nc)
-        for (int r = (int)r0; r < r1; ++r) total = __dadd_rn(total, err[(size_t)r * nc + lane]);
+    for (int r = r0; r < r1; r += 16) {
+        double t[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i] = mine[(size_t)min(r + i, r1 - 1) * nc];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (r + i < r1) total = __dadd_rn(total, t[i]);
+    }
+    const float smax = max_rule_scale(scales, r0, r1, maxima, qmax, lane);       // read before any row of the group is overwritten (same wavefront)
     int best = lane < nc ? lane : -1;
     double best_err = total;
 #pragma unroll
@@ -116,7 +200,20 @@ choose_scale_kernel(const double* __restrict__ err, int rows, int rows_per_scale
         best = take ? ob : best;
     }
     const float s = candidate_scale(smax, candidates / 2 + best, candidates);
-    for (int r = (int)r0 + lane; r < r1; r += 64) scales[r] = s;
+    for (int r = r0 + lane; r < r1; r += 64) scales[r] = s;
+}
+
+template <int N, int M>
+void launch_row_errors(const float* W, int rows, int cols, int ldw, float qmax, int rows_per_scale, int maxima, int candidates,
+                       const float* scales, double* err, hipStream_t st)
+{
+    const dim3 grid((unsigned)(rows < (1 << 20) ? rows : (1 << 20))), wg(256);       // a launch holds fewer than 2^32 threads
+    const int share = (candidates / 2 + 1 + 3) / 4;                                   // candidates per wavefront: 1 .. 9
+#define NM_SHARE(n) hipLaunchKernelGGL((row_errors_kernel<N, M, n>), grid, wg, 0, st, W, rows, cols, ldw, qmax, rows_per_scale, maxima, candidates, scales, err)
+    if (share <= 3) NM_SHARE(3);
+    else if (share <= 5) NM_SHARE(5);
+    else NM_SHARE(9);
+#undef NM_SHARE
 }
 
 }  // namespace
@@ -125,13 +222,19 @@ int launch_scale_search(const float* W, int rows, int cols, int ldw, int N, int 
                         int candidates, float* scales, double* row_errors, hipStream_t st)
 {
     begin_launch();
-    launch_group_scales(W, rows, cols, ldw, rows_per_scale, (float)((1 << (bits - 1)) - 1), scales, st);
-    if (M == 4)
-        hipLaunchKernelGGL(row_errors_kernel<4>, dim3((rows + 3) / 4), dim3(256), 0, st, W, rows, cols, ldw, N, bits, candidates, scales, row_errors);
-    else
-        hipLaunchKernelGGL(row_errors_kernel<8>, dim3((rows + 3) / 4), dim3(256), 0, st, W, rows, cols, ldw, N, bits, candidates, scales, row_errors);
+    const float qmax = (float)((1 << (bits - 1)) - 1);
+    // Every workgroup of the second launch reads its group's maxima: cheaper than a launch that turns them
+    // into scales up to a few hundred rows.
+    const int maxima = rows_per_scale <= 256 ? 1 : 0;
+    if (maxima) launch_row_maxima(W, rows, cols, ldw, scales, st);
+    else launch_group_scales(W, rows, cols, ldw, rows_per_scale, qmax, scales, st);
+#define NM_CASE(n, m) \
+    if (N == n && M == m) launch_row_errors<n, m>(W, rows, cols, ldw, qmax, rows_per_scale, maxima, candidates, scales, row_errors, st)
+    NM_CASE(1, 4); NM_CASE(2, 4); NM_CASE(3, 4); NM_CASE(4, 4);
+    NM_CASE(1, 8); NM_CASE(2, 8); NM_CASE(3, 8); NM_CASE(4, 8); NM_CASE(5, 8); NM_CASE(6, 8); NM_CASE(7, 8); NM_CASE(8, 8);
+#undef NM_CASE
     const long long n_groups = ((long long)rows + rows_per_scale - 1) / rows_per_scale;
-    hipLaunchKernelGGL(choose_scale_kernel, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st, row_errors, rows, rows_per_scale, candidates, scales);
+    hipLaunchKernelGGL(choose_scale_kernel, dim3((unsigned)n_groups), dim3(64), 0, st, row_errors, rows, rows_per_scale, maxima, qmax, candidates, scales);
     return launch_status();
 }
 

@@ -66,3 +66,14 @@ def test_random_dividends_in_the_code_range():
     s = divisors(rng, n)
     w = (rng.uniform(-127.2, 127.2, n) * s.astype(f64)).astype(f32)
     assert np.array_equal(quotient_by_reciprocal(w, s).view(np.uint32), (w / s).astype(f32).view(np.uint32))
+
+
+def test_dividends_up_to_twice_the_code_range():
+    """The scale search divides by scales down to half the max-rule scale: |w| up to 254 s."""
+    rng = np.random.default_rng(3)
+    n = 1_000_000
+    s = divisors(rng, n)
+    k = rng.integers(-254, 254, n).astype(f64) + 0.5
+    w = (np.where(rng.random(n) < 0.5, k, rng.uniform(-254.2, 254.2, n)) * s.astype(f64)).astype(f32)
+    w = (w.view(np.int32) + rng.integers(-3, 4, n).astype(np.int32)).view(f32)
+    assert np.array_equal(quotient_by_reciprocal(w, s).view(np.uint32), (w / s).astype(f32).view(np.uint32))

@@ -971,6 +971,35 @@ def test_scale_search_matches_oracle_and_feeds_compress(N, M, bits, rps):
     check_outputs(acc_ref, sx, s_dev.cpu().numpy(), bias, res["acc"], res["f32"], None, what="gemm on searched scales")
 
 
+@pytest.mark.parametrize("C", [2, 8, 22, 24, 38, 40, 64])
+@pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (3, 4, 4), (4, 4, 8), (7, 8, 8), (8, 8, 4)])
+def test_scale_search_candidate_counts_and_scale_ranges(N, M, bits, C):
+    """Candidate counts at the edges of the wavefronts' shares; rows of zeros, rows whose scale lies outside the
+    range of the reciprocal route, an unaligned matrix; groups above and below 256 rows.  The oracle's choice, or one
+    whose error the oracle puts within 1e-12 of the least."""
+    say("scale search shares", N, M, bits, C)
+    rng = np.random.default_rng([N, M, bits, C])
+    for rows, cols, rps in [(6, 64 * M + M, 1), (300, 40, 256), (300, 40, 300)]:
+        W = (rng.standard_normal((rows, cols)) * rng.random((rows, 1)) * 0.05).astype(np.float32)
+        W[1] = 0.0
+        if rps == 1:
+            W[2] *= np.float32(2.0 ** -70)
+            W[3] *= np.float32(2.0 ** 70)
+        s_ref, err = oracle.dist_scales(W, N, M, bits, rps, C)
+        buf = torch.zeros((rows, cols + 1), dtype=torch.float32, device=DEV)
+        buf[:, 1:] = torch.from_numpy(W).to(DEV)
+        s_gpu = nm.nm_scale_search(buf[:, 1:], N, M, bits, rps, C).cpu().numpy()
+        qmax = np.float32((1 << (bits - 1)) - 1)
+        for gi, r0 in enumerate(range(0, rows, rps)):
+            blk = slice(r0, min(r0 + rps, rows))
+            assert np.all(s_gpu[blk] == s_gpu[r0])
+            if s_gpu[r0] == s_ref[r0]:
+                continue
+            smax = np.abs(W[blk]).max() / qmax
+            cands = [np.float32(np.float32(smax * np.float32(c)) / np.float32(C)) for c in range(C // 2, C + 1)]
+            assert err[gi][cands.index(s_gpu[r0])] <= err[gi].min() * (1 + 1e-12)
+
+
 # ---- several matrices in one call (nm_compress_batch): byte for byte what nm_compress gives -----
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 4, 4), (2, 8, 4), (4, 8, 8), (3, 4, 8), (4, 4, 8), (8, 8, 4)])
