@@ -3,19 +3,20 @@
 // and N >= 3 in the row layout.  Any pattern, any shape, any alignment, either layout.
 //
 // One workgroup of four wavefronts computes a BT-token x BO-row output tile, K in chunks of 256
-// columns.  The packed weights are expanded once per tile to dense int8 rows in LDS and multiplied on
-// the dense integer MFMA (v_mfma_i32_16x16x64_i8): at the widths that come here a call is bound by
-// the latency of its few chunks (global -> registers -> LDS -> MFMA) and not by the matrix pipe, so
-// the dense instruction's lower rate costs nothing, and one decode serves every pattern.  The next
-// chunk's loads are in flight while the current one is multiplied; 35 KB of LDS (17 KB for the small
-// tile) let several workgroups share a CU and cover each other's barriers.
+// columns.  A tile's packed weights go through registers to LDS: as operands of the sparse MFMA
+// where a group keeps at most two (for 2:4 int8 the bytes as they are), expanded to dense int8 rows for
+// the dense integer MFMA otherwise.  At the widths that come here a call is bound by the latency of
+// its few chunks (global -> registers -> LDS -> MFMA) and not by the matrix pipe.  So two chunks are
+// in flight, no load waits behind a branch that differs between lanes, and 15 KB of LDS (17 KB
+// dense) for the small tile let several workgroups share a CU and cover each other's barriers.
 //
-// Loads are 16 bytes wide at any byte address (global memory takes unaligned vectors); only the chunk
-// that holds a row's end is read in guarded pieces, so no byte past a row's K columns is touched.
-// X is zero beyond K in LDS, which makes the columns of a partial chunk contribute nothing.
+// Loads are 16 bytes wide at any byte address (global memory takes unaligned vectors); only a buffer's
+// last bytes are read in guarded pieces, so no byte past its end is touched.  X is zero beyond K in
+// LDS, which makes the columns of a partial chunk contribute nothing, whatever the weights' bytes there.
 //
 // Against one thread per output walking the metadata, which this kernel replaces: the 16 layers of a
-// 312-wide encoder (F = 1200, 2:4 int8) at 1999 tokens 23.08 ms -> 0.139 ms a pass; eight layers of
+// 312-wide encoder (F = 1200, 2:4 int8) at 1999 tokens 23.08 ms -> 0.106 ms a pass (0.139 with dense
+// rows in LDS, one chunk in flight and the bytes of a row's last unit loaded one after the other); eight layers of
 // BERT-base at 3001 tokens with a 3-output layer behind them (K = 768, 31 tokens) 293.6 -> 112.0 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,6 +30,8 @@ namespace {
 
 constexpr int KC = 256;                        // columns per chunk
 constexpr int ROW = KC + 16;                   // LDS bytes per row: 16-byte reads of 8 consecutive rows cover all banks once
+constexpr int CROW = KC / 2 + 16;              // the same for rows of sparse-MFMA codes (16 bytes per 32 columns) ...
+constexpr int PROW = KC / 8 + 4;               // ... and of their positions (4 bytes per 32 columns)
 
 // The packed bytes of 32 consecutive columns of one weight row, and their expansion to 32 dense codes.
 template <int N, int M, int BITS>
@@ -37,19 +40,37 @@ struct PackedUnit {
     static constexpr int VB = U::VBYTES, MB = U::MBYTES;
     uint32_t v[U::VD], m[U::MD];
 
-    // UB bytes from `src`, of which `avail` are the row's own (the rest of the unit is zero)
+    // UB bytes from byte `at` on of an array of `bytes` bytes; past its end, anything.
     template <int UB, int WORDS>
-    static __device__ __forceinline__ void read(const uint8_t* src, int avail, uint32_t (&dst)[WORDS])
+    static __device__ __forceinline__ void read_inside(const uint8_t* base, size_t at, uint32_t (&dst)[WORDS])
+    {
+        if constexpr (UB % 4 != 0) dst[WORDS - 1] = 0u;
+        __builtin_memcpy(dst, base + at, UB);
+    }
+    template <int UB, int WORDS>
+    static __device__ __forceinline__ void read_at_end(const uint8_t* base, size_t at, size_t bytes, uint32_t (&dst)[WORDS])
     {
 #pragma unroll
         for (int w = 0; w < WORDS; ++w) dst[w] = 0u;
-        if (avail >= UB) {
-            __builtin_memcpy(dst, src, UB);
+        if (bytes < UB) {                      // uniform; an array of a few bytes
+#pragma unroll 1
+            for (int b = 0; b < UB; ++b) {
+                const uint32_t x = (uint32_t)base[at + b < bytes ? at + b : bytes - 1] << (8 * (b % 4));
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) dst[w] |= b / 4 == w ? x : 0u;
+            }
             return;
         }
+        // the array's last UB bytes at the most, moved down by as many as they begin too early
+        const size_t from = at + UB <= bytes ? at : bytes - UB;
+        const int d = (int)(at - from);
+        __builtin_memcpy(dst, base + from, UB);
 #pragma unroll
-        for (int b = 0; b < UB; ++b)
-            if (b < avail) dst[b / 4] |= (uint32_t)src[b] << (8 * (b % 4));
+        for (int step = 4; step >= 1; step /= 2)
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) dst[w] = (d / 4 & step) ? (w + step < WORDS ? dst[w + step] : 0u) : dst[w];
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) dst[w] = __builtin_amdgcn_alignbyte(w + 1 < WORDS ? dst[w + 1] : 0u, dst[w], (uint32_t)(d % 4));
     }
     template <int UB, int WORDS>
     static __device__ __forceinline__ void read_pieces(const uint8_t* block, int lane, uint32_t (&dst)[WORDS])
@@ -60,24 +81,24 @@ struct PackedUnit {
 #pragma unroll
         for (int p = 0; p < UB / PB; ++p) __builtin_memcpy(reinterpret_cast<uint8_t*>(dst) + p * PB, block + (p * 64 + lane) * PB, PB);
     }
-    __device__ __forceinline__ void load(const GemmArgs& a, int row, int unit)
+    __device__ __forceinline__ void load_tiled(const GemmArgs& a, int row, int unit)
     {
-        if (a.pv.tiled) {
-            const size_t block = (size_t)(row >> 4) * a.pv.slices + (unit >> 2);
-            const int lane = (unit & 3) * 16 + (row & 15);
-            read_pieces<VB>(a.vals + block * 64 * VB, lane, v);
-            if constexpr (MB > 0) read_pieces<MB>(a.meta + block * 64 * MB, lane, m);
-            return;
-        }
-        read<VB>(a.vals + (size_t)row * a.pv.stride + (size_t)unit * VB, (int)a.pv.stride - unit * VB, v);
-        if constexpr (MB > 0) read<MB>(a.meta + (size_t)row * a.pm.stride + (size_t)unit * MB, (int)a.pm.stride - unit * MB, m);
+        const size_t block = (size_t)(row >> 4) * a.pv.slices + (unit >> 2);
+        const int lane = (unit & 3) * 16 + (row & 15);
+        read_pieces<VB>(a.vals + block * 64 * VB, lane, v);
+        if constexpr (MB > 0) read_pieces<MB>(a.meta + block * 64 * MB, lane, m);
     }
-    __device__ __forceinline__ void clear()
+    template <bool AT_END>
+    __device__ __forceinline__ void load_rows(const GemmArgs& a, int row, int unit)
     {
-#pragma unroll
-        for (int w = 0; w < U::VD; ++w) v[w] = 0u;
-#pragma unroll
-        for (int w = 0; w < U::MD; ++w) m[w] = 0u;
+        const size_t va = (size_t)row * a.pv.stride + (size_t)(unit * VB), ma = (size_t)row * a.pm.stride + (size_t)(unit * MB);
+        if constexpr (AT_END) {
+            read_at_end<VB>(a.vals, va, (size_t)a.O * a.pv.stride, v);
+            if constexpr (MB > 0) read_at_end<MB>(a.meta, ma, (size_t)a.O * a.pm.stride, m);
+        } else {
+            read_inside<VB>(a.vals, va, v);
+            if constexpr (MB > 0) read_inside<MB>(a.meta, ma, m);
+        }
     }
     __device__ __forceinline__ void expand(uint32_t (&d)[8]) const
     {
@@ -124,24 +145,6 @@ struct PackedUnit {
     }
 };
 
-// Columns k .. k+15 of a row of X, zero from column K on (K is a multiple of 4).
-__device__ __forceinline__ v4i load_x16(const int8_t* row, int k, int K)
-{
-    v4i x = v4i{0, 0, 0, 0};
-    if (k + 16 <= K) {
-        __builtin_memcpy(&x, row + k, 16);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (k + 4 * i < K) {
-                int t;
-                __builtin_memcpy(&t, row + k + 4 * i, 4);
-                x[i] = t;
-            }
-    }
-    return x;
-}
-
 template <int N, int M, int BITS, int BT, int BO>
 __global__ void __launch_bounds__(256)
 gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const int vec)
@@ -149,9 +152,11 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
     constexpr int FT = BT / 32, FO = BO / 32;          // 16x16 fragments per wavefront along each side (2 x 2 wavefronts)
     constexpr int XCH = BT * (KC / 16) / 256;          // 16-byte pieces of X per thread and chunk
     constexpr int WUN = BO * (KC / 32) / 256;          // weight units per thread and chunk
+    using U = Unit<N, M, BITS>;
+    constexpr bool SPARSE = !U::DUAL;
     static_assert(BT % 32 == 0 && BO % 32 == 0 && XCH * 256 == BT * (KC / 16) && WUN * 256 == BO * (KC / 32), "whole shares");
     __shared__ __align__(16) uint8_t xs[BT * ROW];
-    __shared__ __align__(16) uint8_t ws[BO * ROW];
+    __shared__ __align__(16) uint8_t ws[BO * (SPARSE ? CROW + PROW : ROW)];
 
     // each XCD (workgroups are dealt to the eight in turn) takes a contiguous run of tiles
     const int per_xcd = (n_tiles + 7) >> 3;
@@ -162,21 +167,77 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
     const int wt = wave & 1, wo = wave >> 1;
     const int li = lane & 15, lg = lane >> 4;
 
-    v4i xr[XCH];
-    PackedUnit<N, M, BITS> wr[WUN];
-    auto load = [&](int k0) __attribute__((always_inline)) {
+    struct Chunk {
+        v4i x[XCH];
+        PackedUnit<N, M, BITS> w[WUN];
+    };
+    // What a chunk loads past column K is dropped (X, in stage) or meets zeros of X (weights), so addresses are
+    // clamped to what the buffers hold and no load waits behind a branch of its lanes: pieces of X past K become
+    // the row's last columns, units past K the row's last unit.  Only a piece or unit that begins before
+    // a buffer's end and would reach past it is taken apart: the last token's, the last output row's.
+    auto load = [&](int k0, Chunk& r) __attribute__((always_inline)) {
+        if (k0 >= a.K) return;                         // this and all conditions below: uniform
+        const bool whole = k0 + KC <= a.K;
+        const bool x_whole = whole || (t0 + BT < a.tokens && a.ldx >= 16);     // (a piece may run into the next row)
+        const bool w_whole = whole || (o0 + BO < a.O && a.K >= 32);
 #pragma unroll
-        for (int r = 0; r < XCH; ++r) {
-            const int c = tid + 256 * r;
-            const int t = min(t0 + c / (KC / 16), a.tokens - 1);
-            xr[r] = load_x16(a.X + (size_t)t * a.ldx, k0 + (c % (KC / 16)) * 16, a.K);
+        for (int i = 0; i < XCH; ++i) {
+            const int c = tid + 256 * i;
+            const int8_t* row = a.X + (size_t)min(t0 + c / (KC / 16), a.tokens - 1) * a.ldx;
+            const int k = k0 + (c % (KC / 16)) * 16;
+            if (x_whole) {
+                __builtin_memcpy(&r.x[i], row + min(k, a.K - 4), 16);          // (k < K: k is K - 4 at most)
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    int w;
+                    __builtin_memcpy(&w, row + min(k + 4 * j, a.K - 4), 4);
+                    r.x[i][j] = w;
+                }
+            }
         }
 #pragma unroll
-        for (int r = 0; r < WUN; ++r) {
-            const int u = tid + 256 * r;
-            const int k = k0 + (u % (KC / 32)) * 32;
-            if (k < a.K) wr[r].load(a, min(o0 + u / (KC / 32), a.O - 1), k / 32);
-            else wr[r].clear();
+        for (int i = 0; i < WUN; ++i) {
+            const int u = tid + 256 * i;
+            const int row = min(o0 + u / (KC / 32), a.O - 1), unit = min(k0 / 32 + u % (KC / 32), (a.K - 1) / 32);
+            if (a.pv.tiled) r.w[i].load_tiled(a, row, unit);
+            else if (w_whole) r.w[i].template load_rows<false>(a, row, unit);
+            else r.w[i].template load_rows<true>(a, row, unit);
+        }
+    };
+    auto stage = [&](const Chunk& r, int k0) __attribute__((always_inline)) {
+        const bool whole = k0 + KC <= a.K;             // uniform
+#pragma unroll
+        for (int i = 0; i < XCH; ++i) {
+            const int c = tid + 256 * i;
+            v4i x = r.x[i];
+            if (!whole) {
+                const int k = k0 + (c % (KC / 16)) * 16;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[j] = k + 4 * j < a.K ? x[j] : 0;
+            }
+            *reinterpret_cast<v4i*>(xs + (c / (KC / 16)) * ROW + (c % (KC / 16)) * 16) = x;
+        }
+#pragma unroll
+        for (int i = 0; i < WUN; ++i) {
+            const int u = tid + 256 * i, row = u / (KC / 32), unit = u % (KC / 32);
+            if constexpr (SPARSE) {
+                typename U::Raw raw;
+#pragma unroll
+                for (int w = 0; w < U::VD; ++w) raw.v[w] = r.w[i].v[w];
+#pragma unroll
+                for (int w = 0; w < U::MD; ++w) raw.m[w] = r.w[i].m[w];
+                v4i codes; int pos;
+                U::decode(raw, codes, pos);
+                *reinterpret_cast<v4i*>(ws + row * CROW + unit * 16) = codes;
+                *reinterpret_cast<int*>(ws + BO * CROW + row * PROW + unit * 4) = pos;
+            } else {
+                uint32_t d[8];
+                r.w[i].expand(d);
+                v4i* dst = reinterpret_cast<v4i*>(ws + row * ROW + unit * 32);
+                dst[0] = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
+                dst[1] = v4i{(int)d[4], (int)d[5], (int)d[6], (int)d[7]};
+            }
         }
     };
 
@@ -186,40 +247,62 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) acc[fo][ft] = v4i{0, 0, 0, 0};
 
-    load(0);
-    for (int k0 = 0; k0 < a.K; k0 += KC) {
-        if (k0 > 0) __syncthreads();                   // everyone has read the previous chunk
+    auto multiply = [&](int k0) __attribute__((always_inline)) {
+        if constexpr (SPARSE) {
+            const int steps = min((a.K - k0 + 127) >> 7, KC / 128);
+            for (int s = 0; s < steps; ++s) {
+                v8i xf[FT];
 #pragma unroll
-        for (int r = 0; r < XCH; ++r) {
-            const int c = tid + 256 * r;
-            *reinterpret_cast<v4i*>(xs + (c / (KC / 16)) * ROW + (c % (KC / 16)) * 16) = xr[r];
-        }
+                for (int ft = 0; ft < FT; ++ft) {
+                    const uint8_t* src = xs + (wt * (BT / 2) + ft * 16 + li) * ROW + s * 128 + lg * 16;
+                    const v4i lo = *reinterpret_cast<const v4i*>(src), hi = *reinterpret_cast<const v4i*>(src + 64);
+                    xf[ft] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                }
 #pragma unroll
-        for (int r = 0; r < WUN; ++r) {
-            const int u = tid + 256 * r;
-            uint32_t d[8];
-            wr[r].expand(d);
-            v4i* dst = reinterpret_cast<v4i*>(ws + (u / (KC / 32)) * ROW + (u % (KC / 32)) * 32);
-            dst[0] = v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
-            dst[1] = v4i{(int)d[4], (int)d[5], (int)d[6], (int)d[7]};
-        }
-        __syncthreads();
-        if (k0 + KC < a.K) load(k0 + KC);
-        const int steps = min((a.K - k0 + 63) >> 6, KC / 64);
-        for (int s = 0; s < steps; ++s) {
-            v4i xf[FT], wf[FO];
+                for (int fo = 0; fo < FO; ++fo) {
+                    const int row = wo * (BO / 2) + fo * 16 + li, unit = 4 * s + lg;
+                    const v4i codes = *reinterpret_cast<const v4i*>(ws + row * CROW + unit * 16);
+                    const int pos = *reinterpret_cast<const int*>(ws + BO * CROW + row * PROW + unit * 4);
 #pragma unroll
-            for (int ft = 0; ft < FT; ++ft)
-                xf[ft] = *reinterpret_cast<const v4i*>(xs + (wt * (BT / 2) + ft * 16 + li) * ROW + s * 64 + lg * 16);
-#pragma unroll
-            for (int fo = 0; fo < FO; ++fo)
-                wf[fo] = *reinterpret_cast<const v4i*>(ws + (wo * (BO / 2) + fo * 16 + li) * ROW + s * 64 + lg * 16);
-#pragma unroll
-            for (int fo = 0; fo < FO; ++fo)
+                    for (int ft = 0; ft < FT; ++ft)
+                        acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(codes, xf[ft], acc[fo][ft], pos, 0, 0);
+                }
+            }
+        } else {
+            const int steps = min((a.K - k0 + 63) >> 6, KC / 64);
+            for (int s = 0; s < steps; ++s) {
+                v4i xf[FT], wf[FO];
 #pragma unroll
                 for (int ft = 0; ft < FT; ++ft)
-                    acc[fo][ft] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[fo], xf[ft], acc[fo][ft], 0, 0, 0);
+                    xf[ft] = *reinterpret_cast<const v4i*>(xs + (wt * (BT / 2) + ft * 16 + li) * ROW + s * 64 + lg * 16);
+#pragma unroll
+                for (int fo = 0; fo < FO; ++fo)
+                    wf[fo] = *reinterpret_cast<const v4i*>(ws + (wo * (BO / 2) + fo * 16 + li) * ROW + s * 64 + lg * 16);
+#pragma unroll
+                for (int fo = 0; fo < FO; ++fo)
+#pragma unroll
+                    for (int ft = 0; ft < FT; ++ft)
+                        acc[fo][ft] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[fo], xf[ft], acc[fo][ft], 0, 0, 0);
+            }
         }
+    };
+
+    // two chunks in flight: a call of two chunks waits for memory once
+    Chunk even, odd;
+    load(0, even);
+    load(KC, odd);
+    for (int k0 = 0; k0 < a.K; k0 += 2 * KC) {
+        if (k0 > 0) __syncthreads();                   // everyone has read the previous chunk
+        stage(even, k0);
+        __syncthreads();
+        load(k0 + 2 * KC, even);
+        multiply(k0);
+        if (k0 + KC >= a.K) break;                     // uniform
+        __syncthreads();
+        stage(odd, k0 + KC);
+        __syncthreads();
+        load(k0 + 3 * KC, odd);
+        multiply(k0 + KC);
     }
 
     // Lane (li, lg) holds rows 4*lg .. 4*lg+3 of token li of every fragment.

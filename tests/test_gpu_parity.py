@@ -450,6 +450,18 @@ def test_gemm_any_shape_alignment_and_pattern(N, M, bits, T, K, O, ldx, x_off, l
                   b16[:, :O].contiguous().view(torch.int16).cpu().numpy().view(np.uint16))
 
 
+@pytest.mark.parametrize("N,M,bits", [(1, 4, 4), (2, 4, 8), (4, 4, 4), (1, 8, 8), (2, 8, 4), (7, 8, 8)])
+@pytest.mark.parametrize("T,K,O,ldx", [
+    (1, 8, 1, 8), (70, 8, 3, 8),           # packed arrays shorter than one unit; pieces of X longer than a row
+    (33, 40, 34, 40),                      # the last row's last unit begins just before the array's end
+    (65, 776, 65, 784),                    # four chunks, ragged last tiles
+    (32, 272, 32, 272),                    # one whole tile, which is also the last
+])
+def test_gemm_any_ends_of_its_buffers(N, M, bits, T, K, O, ldx):
+    """Loads at the ends of the packed arrays and of X, which are taken apart or moved."""
+    test_gemm_any_shape_alignment_and_pattern(N, M, bits, T, K, O, ldx, 0, O, 0)
+
+
 def test_gemm_large_output_written_through_with_padded_rows():
     """A bf16 output large enough (>= 14 MB) to take the written-through stores of the wide tile, with
     padded output rows (the padding must stay untouched) and a ragged last column tile."""
