@@ -810,8 +810,8 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         // (nm_gemm_few.h has the measurements).  One of fewer than 128 tiles of 128 x 96 beyond that leaves
         // half the chip idle while every workgroup pulls its whole share of X and W through one CU's
         // fill path: the smallest tile that still runs in one round (384 x 1024 -> 3072 6.1 -> 5.0 us).
-        if (few_tile(items, count) != 0) cfg = 130;
-        else if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 131;
+        if (const int few = few_tile(items, count)) cfg = few;
+        else if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 130;
         else if (!U::DUAL && n96 < 128 && n64x96 <= 256 && count == 1) cfg = 132;
         else if (NARROW_ONCE && count == 1 && ((DECODE_BOUND && ALWAYS_ONCE) || a.O <= 1024)) cfg = 127;
         else if (U::IDENTITY && count == 1 && n96 >= 256) cfg = modelled_tile(a);
@@ -829,7 +829,7 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
     if constexpr (!ODD8) {
         if (cfg == 112) return launch_dma_tile<N, M, BITS, 256, 96, 4, 2, 3, 1>(items, count, st);
     }
-    if (cfg == 130 || (cfg >= 141 && cfg <= 144)) return launch_few<N, M, BITS>(items, count, st, cfg);
+    if (cfg >= 141 && cfg <= 144) return launch_few<N, M, BITS>(items, count, st, cfg);
     if (cfg == 116) return launch_dma_tile<N, M, BITS, 128, 96, 4, 2, 3, 1, true>(items, count, st);
     if (cfg == 115) return launch_dma_tile<N, M, BITS, 128, 96, 2, 2, 3, 1, true>(items, count, st);
     if (cfg == 117) return launch_dma_tile<N, M, BITS, 128, 128, 4, 2, 3, 1, true>(items, count, st);
@@ -855,7 +855,7 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         if (cfg == 113) return launch_dma_tile<N, M, BITS, 128, 96, 4, 2, 3, 2>(items, count, st);
         // small tiles for problems of a few output tiles (few tokens): more workgroups, each with a
         // smaller share of X and W to pull through its CU's fill path
-        if (cfg == 131) return launch_dma_tile<N, M, BITS, 64, 48, 2, 1, 4, 1, true>(items, count, st);
+        if (cfg == 130) return launch_dma_tile<N, M, BITS, 64, 48, 2, 1, 4, 1, true>(items, count, st);
         if (cfg == 132) return launch_dma_tile<N, M, BITS, 64, 96, 2, 2, 4, 1>(items, count, st);
     }
     return false;

@@ -224,7 +224,6 @@ inline int few_tile(const GemmArgs* items, int count)
 template <int N, int M, int BITS>
 bool launch_few(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
-    if (cfg < 141) cfg = few_tile(items, count);
     if (cfg == 141) return launch_few_tile<N, M, BITS, 1, 1>(items, count, st);
     if (cfg == 143) return launch_few_tile<N, M, BITS, 1, 2>(items, count, st);
     if (cfg == 142) return launch_few_tile<N, M, BITS, 2, 2>(items, count, st);

@@ -326,7 +326,7 @@ def test_gemm_batch_falls_back_to_one_launch_per_item(layout, N, M, bits, shapes
     _gemm_batch(N, M, bits, layout, 0, shapes, seed=13)
 
 
-@pytest.mark.parametrize("tile", [130, 141, 142, 143, 144])
+@pytest.mark.parametrize("tile", [141, 142, 143, 144])
 @pytest.mark.parametrize("N,M,bits", FAST_SCHEMES + DUAL_SCHEMES + ODD8_SCHEMES)
 def test_gemm_few_tokens_kernels(N, M, bits, tile):
     """The kernels that split K over the wavefronts of a workgroup: one slice, a remainder behind the eight,
@@ -692,7 +692,14 @@ def q8_scale(acc_ref, sx, scales_ref, bias):
     return np.float32(np.abs(f32).max() / 127.0)
 
 
-@pytest.mark.parametrize("tile,layout", [(0, ROWS), (2, ROWS), (0, TILED), (113, TILED), (116, TILED), (122, TILED), (133, TILED), (136, TILED)])
+@pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (2, 4, 4), (1, 8, 8)])
+def test_gemm_batch_chooses_the_smallest_ring_tile(N, M, bits):
+    """Query, key and value of a few sentences, too many tiles for the kernels of few tokens: one launch on 64 x 48."""
+    _gemm_batch(N, M, bits, TILED, 0, [(256, 768, 768), (256, 768, 768), (250, 768, 700)], seed=14)
+    assert binding.raw().nm_bench_last_gemm_tile() == 130
+
+
+@pytest.mark.parametrize("tile,layout", [(0, ROWS), (2, ROWS), (0, TILED), (113, TILED), (116, TILED), (122, TILED), (130, TILED), (133, TILED), (136, TILED)])
 @pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 4, 4), (2, 8, 4), (4, 4, 8)])
 def test_gemm_q8_fast_paths(N, M, bits, tile, layout):
     """Every kernel family, whole and ragged tiles, rows of 16-byte, 8-byte and 4-byte granularity, with and
@@ -1285,7 +1292,14 @@ def test_quantize_act_feeds_the_sparse_gemm():
     (4096, 768, 3072, 2, 8, 4, torch.bfloat16, {133}),          # a decoded pattern on a short reduction
     (4096, 768, 3072, 4, 4, 4, torch.bfloat16, {133}),          # dense int4
     (4096, 768, 3072, 4, 8, 4, torch.bfloat16, {126}),          # 4:8 int4 keeps 256 x 192 with the wavefronts 2 x 4
-    (128, 768, 768, 2, 4, 8, torch.bfloat16, {130}),            # few tokens: the smallest tile
+    (128, 768, 768, 2, 4, 8, torch.bfloat16, {143}),            # few tokens: K split over the wavefronts, 16 x 32
+    (16, 768, 768, 2, 4, 8, torch.bfloat16, {141}),             # ... 16 x 16
+    (128, 768, 2048, 2, 4, 8, torch.bfloat16, {142}),           # ... 32 x 32
+    (128, 1024, 4096, 2, 4, 8, torch.bfloat16, {144}),          # ... 32 x 64
+    (256, 768, 2304, 2, 4, 8, torch.bfloat16, {130}),           # beyond one round of those: the ring's smallest tile
+    (200, 768, 3072, 2, 4, 4, torch.bfloat16, {130}),
+    (520, 512, 1024, 1, 8, 8, torch.bfloat16, {130}),
+    (384, 1024, 3072, 2, 4, 8, torch.bfloat16, {132}),          # ... 64 x 96
 ])
 def test_tile_choice_on_the_paper_shapes(T, K, O, N, M, bits, dtype, expect):
     """The launcher's tile choice on the layer shapes the benchmarks run, read back through the measurement hook
