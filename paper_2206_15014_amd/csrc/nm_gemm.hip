@@ -287,26 +287,42 @@ void launch_pattern(const GemmArgs& a, hipStream_t st, int tile_cfg)
 
 }  // namespace
 
-bool launch_gemm_dma_set0(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set1(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set2(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set3(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set4(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set5(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set6(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set7(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set8(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set9(const GemmArgs* items, int count, hipStream_t st, int cfg);
-bool launch_gemm_dma_set10(const GemmArgs* items, int count, hipStream_t st, int cfg);
+// The tiled-layout kernels: one function per set of patterns (nm_gemm_sets.h) and family, true when it launched.
+#define NM_SETS(f) f##0, f##1, f##2, f##3, f##4, f##5, f##6, f##7, f##8, f##9, f##10
+typedef bool GemmSet(const GemmArgs* items, int count, hipStream_t st, int cfg);
+GemmSet NM_SETS(launch_gemm_dma_set);
+GemmSet NM_SETS(launch_gemm_few_set);
+
+namespace {
+
+// The tile for a launch: the smallest of 16 x 16, 16 x 32, 32 x 32, 32 x 64 (tokens x outputs; ids 141,
+// 143, 142, 144) of which the CUs take all workgroups at once, 0 when there is none.  Smaller tiles pull
+// the weights in through more CUs, and a second round costs more than a larger tile does (2:4 int8, 128
+// tokens: 1024 -> 1024 has 512 / 256 / 128 / 64 workgroups, 3.39 / 2.90 / 3.39 / 3.69 us; 1024 -> 4096 2048 /
+// 1024 / 512 / 256, 7.49 / 5.76 / 5.85 / 4.24).  Past 256 of the largest the ring tiles are the better ones
+// (256 tokens 768 -> 2304, 288 workgroups: 6.41 against 4.69 us).
+int few_tile(const GemmArgs* items, int count)
+{
+    struct Shape { int cfg, t, o; };
+    static const Shape shapes[] = {{141, 16, 16}, {143, 16, 32}, {142, 32, 32}, {144, 32, 64}};
+    for (const Shape& s : shapes) {
+        long long n = 0;
+        for (int i = 0; i < count; ++i) n += ((items[i].tokens + s.t - 1ll) / s.t) * ((items[i].O + s.o - 1ll) / s.o);
+        if (n <= 256) return s.cfg;
+    }
+    return 0;
+}
+
+}  // namespace
 
 bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
-    return launch_gemm_dma_set0(items, count, st, cfg) || launch_gemm_dma_set1(items, count, st, cfg) ||
-           launch_gemm_dma_set2(items, count, st, cfg) || launch_gemm_dma_set3(items, count, st, cfg) ||
-           launch_gemm_dma_set4(items, count, st, cfg) || launch_gemm_dma_set5(items, count, st, cfg) ||
-           launch_gemm_dma_set6(items, count, st, cfg) || launch_gemm_dma_set7(items, count, st, cfg) ||
-           launch_gemm_dma_set8(items, count, st, cfg) || launch_gemm_dma_set9(items, count, st, cfg) ||
-           launch_gemm_dma_set10(items, count, st, cfg);
+    static GemmSet* const rings[] = {NM_SETS(launch_gemm_dma_set)};
+    static GemmSet* const fews[] = {NM_SETS(launch_gemm_few_set)};
+    const int few = cfg == 0 ? few_tile(items, count) : cfg >= 141 && cfg <= 144 ? cfg : 0;
+    for (GemmSet* const set : few ? fews : rings)
+        if (set(items, count, st, few ? few : cfg)) return true;
+    return false;
 }
 
 int launch_smfmac_probe(int blocks, int iters, unsigned long long* counters, hipStream_t st)

@@ -37,7 +37,7 @@
 
 #include "nm_internal.h"
 #include "nm_gemm_common.h"
-#include "nm_gemm_few.h"
+#include "nm_gemm_sets.h"
 
 namespace nm {
 
@@ -806,12 +806,11 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         const long long n96 = (long long)((a.tokens + 127) / 128) * ((a.O + 95) / 96);
         const long long n64x96 = (long long)((a.tokens + 63) / 64) * ((a.O + 95) / 96);
         const long long n64x48 = (long long)((a.tokens + 63) / 64) * ((a.O + 47) / 48);
-        // A problem of one round of the small tiles that split K inside the workgroup runs on those
-        // (nm_gemm_few.h has the measurements).  One of fewer than 128 tiles of 128 x 96 beyond that leaves
-        // half the chip idle while every workgroup pulls its whole share of X and W through one CU's
-        // fill path: the smallest tile that still runs in one round (384 x 1024 -> 3072 6.1 -> 5.0 us).
-        if (const int few = few_tile(items, count)) cfg = few;
-        else if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 130;
+        // A problem of fewer than 128 tiles of 128 x 96 leaves half the chip idle while every workgroup
+        // pulls its whole share of X and W through one CU's fill path: the smallest tile that still
+        // runs in one round (measured: 384 x 1024 -> 3072 6.1 -> 5.0 us).  Most calls of fewer tokens than that
+        // do not come here: see few_tile.
+        if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 130;
         else if (!U::DUAL && n96 < 128 && n64x96 <= 256 && count == 1) cfg = 132;
         else if (NARROW_ONCE && count == 1 && ((DECODE_BOUND && ALWAYS_ONCE) || a.O <= 1024)) cfg = 127;
         else if (U::IDENTITY && count == 1 && n96 >= 256) cfg = modelled_tile(a);
@@ -829,7 +828,6 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
     if constexpr (!ODD8) {
         if (cfg == 112) return launch_dma_tile<N, M, BITS, 256, 96, 4, 2, 3, 1>(items, count, st);
     }
-    if (cfg >= 141 && cfg <= 144) return launch_few<N, M, BITS>(items, count, st, cfg);
     if (cfg == 116) return launch_dma_tile<N, M, BITS, 128, 96, 4, 2, 3, 1, true>(items, count, st);
     if (cfg == 115) return launch_dma_tile<N, M, BITS, 128, 96, 2, 2, 3, 1, true>(items, count, st);
     if (cfg == 117) return launch_dma_tile<N, M, BITS, 128, 128, 4, 2, 3, 1, true>(items, count, st);
@@ -863,39 +861,12 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
 
 }  // namespace
 
-// One translation unit per set of patterns (NM_DMA_SET, given on the command line), so that the
-// many instantiations compile in parallel.  Returns true when it launched a kernel.
-#define NM_CAT2(a, b) a##b
-#define NM_CAT(a, b) NM_CAT2(a, b)
-bool NM_CAT(launch_gemm_dma_set, NM_DMA_SET)(const GemmArgs* items, int count, hipStream_t st, int cfg)
+// The patterns of this unit's set.  Returns true when it launched a kernel.
+bool NM_SET_NAME(launch_gemm_dma_set)(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
     const GemmArgs& a = items[0];
 #define NM_CASE(n, m, b) if (a.N == n && a.M == m && a.bits == b) return launch_dma_pattern<n, m, b>(items, count, st, cfg)
-#if NM_DMA_SET == 0
-    NM_CASE(2, 4, 8);
-#elif NM_DMA_SET == 1
-    NM_CASE(1, 4, 8); NM_CASE(2, 4, 4);
-#elif NM_DMA_SET == 2
-    NM_CASE(1, 4, 4); NM_CASE(1, 8, 8);
-#elif NM_DMA_SET == 3
-    NM_CASE(2, 8, 8); NM_CASE(1, 8, 4);
-#elif NM_DMA_SET == 4
-    NM_CASE(2, 8, 4);
-#elif NM_DMA_SET == 5
-    NM_CASE(4, 4, 8); NM_CASE(4, 4, 4); NM_CASE(3, 4, 8);
-#elif NM_DMA_SET == 6
-    NM_CASE(3, 4, 4); NM_CASE(4, 8, 8); NM_CASE(4, 8, 4);
-#elif NM_DMA_SET == 7
-    NM_CASE(3, 8, 8); NM_CASE(3, 8, 4);
-#elif NM_DMA_SET == 8
-    NM_CASE(5, 8, 8); NM_CASE(5, 8, 4);
-#elif NM_DMA_SET == 9
-    NM_CASE(6, 8, 8); NM_CASE(6, 8, 4);
-#elif NM_DMA_SET == 10
-    NM_CASE(7, 8, 8); NM_CASE(7, 8, 4);
-#else
-#error "NM_DMA_SET must be 0 .. 10"
-#endif
+    NM_SET_PATTERNS
 #undef NM_CASE
     return false;
 }

@@ -15,10 +15,17 @@
 // 9.28 -> 3.23; 128 tokens 768 -> 768 4.29 -> 2.88, 1024 -> 4096 5.00 -> 4.24, 4096 -> 1024 9.43 -> 5.06;
 // 512 tokens 1024 -> 1024 5.08 -> 3.93.  Dense int8, which had no small tile: 1 token 4096 -> 1024
 // 15.40 -> 3.77, 128 tokens 768 -> 768 5.95 -> 3.00.
-#ifndef NM_GEMM_FEW_H
-#define NM_GEMM_FEW_H
+//
+// These kernels are translation units of their own, and so code objects of their own.  In one code object with the
+// ring kernels of nm_gemm_dma.hip (in front of them: 48 KB) those, the same instructions at other offsets, ran slower
+// where one kernel follows another: the four layers of a BERT-large block at 49152 tokens 617 -> 622 to 627 us a
+// pass, back at 617 with the code objects apart.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
 
+#include "nm_internal.h"
 #include "nm_gemm_common.h"
+#include "nm_gemm_sets.h"
 
 namespace nm {
 namespace {
@@ -203,34 +210,27 @@ bool launch_few_tile(const GemmArgs* items, int count, hipStream_t st)
     return true;
 }
 
-// The tile for a launch: the smallest of 16 x 16, 16 x 32, 32 x 32, 32 x 64 (tokens x outputs; ids 141,
-// 143, 142, 144) of which the CUs take all workgroups at once, 0 when there is none.  Smaller tiles pull
-// the weights in through more CUs, and a second round costs more than a larger tile does (2:4 int8, 128
-// tokens: 1024 -> 1024 has 512 / 256 / 128 / 64 workgroups, 3.39 / 2.90 / 3.39 / 3.69 us; 1024 -> 4096 2048 /
-// 1024 / 512 / 256, 7.49 / 5.76 / 5.85 / 4.24).  Past 256 of the largest the ring tiles are the better ones
-// (256 tokens 768 -> 2304, 288 workgroups: 6.41 against 4.69 us).
-inline int few_tile(const GemmArgs* items, int count)
-{
-    struct Shape { int cfg, t, o; };
-    static const Shape shapes[] = {{141, 16, 16}, {143, 16, 32}, {142, 32, 32}, {144, 32, 64}};
-    for (const Shape& s : shapes) {
-        long long n = 0;
-        for (int i = 0; i < count; ++i) n += ((items[i].tokens + s.t - 1ll) / s.t) * ((items[i].O + s.o - 1ll) / s.o);
-        if (n <= 256) return s.cfg;
-    }
-    return 0;
-}
-
 template <int N, int M, int BITS>
 bool launch_few(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
+    note_gemm_tile(cfg);
     if (cfg == 141) return launch_few_tile<N, M, BITS, 1, 1>(items, count, st);
     if (cfg == 143) return launch_few_tile<N, M, BITS, 1, 2>(items, count, st);
     if (cfg == 142) return launch_few_tile<N, M, BITS, 2, 2>(items, count, st);
-    return launch_few_tile<N, M, BITS, 2, 4>(items, count, st);
+    if (cfg == 144) return launch_few_tile<N, M, BITS, 2, 4>(items, count, st);
+    return false;
 }
 
 }  // namespace
-}  // namespace nm
 
-#endif
+// The patterns of this unit's set.  Returns true when it launched a kernel.
+bool NM_SET_NAME(launch_gemm_few_set)(const GemmArgs* items, int count, hipStream_t st, int cfg)
+{
+    const GemmArgs& a = items[0];
+#define NM_CASE(n, m, b) if (a.N == n && a.M == m && a.bits == b) return launch_few<n, m, b>(items, count, st, cfg)
+    NM_SET_PATTERNS
+#undef NM_CASE
+    return false;
+}
+
+}  // namespace nm

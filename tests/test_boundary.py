@@ -3,6 +3,7 @@ symbol, sizes buffers like the oracle, and rejects bad arguments before touching
 import ctypes
 import os
 import re
+import struct
 
 import pytest
 
@@ -23,6 +24,21 @@ def test_library_exports_every_declared_symbol():
     lib = ctypes.CDLL(binding.library_path())
     for n in names:
         assert hasattr(lib, n), n
+
+
+def test_ring_kernels_share_no_code_object_with_others():
+    """Where a ring kernel lies in its code object shows in its time, so kernels added elsewhere must not move it."""
+    data, ring = open(binding.library_path(), "rb").read(), []
+    for m in re.finditer(b"\x7fELF", data):
+        head = data[m.start():m.start() + 64]
+        machine, table, size, count = struct.unpack_from("<H20xQ10xHH", head, 18)
+        o = data[m.start():m.start() + table + size * count]
+        if machine == 224 and b"15gemm_dma_kernelI" in o:      # EM_AMDGPU
+            ring.append(o)
+    assert len(ring) == 11                    # one per set of patterns
+    for o in ring:
+        kernels = set(re.findall(rb"_ZN2nm12_GLOBAL__N_1\d+([a-z0-9_]+_kernel)I", o))
+        assert kernels <= {b"gemm_dma_kernel", b"gemm_dma_batch_kernel"}, kernels
 
 
 @pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 4, 4), (2, 8, 4), (3, 4, 8), (7, 8, 4), (1, 8, 8), (4, 4, 8), (8, 8, 4)])
