@@ -301,11 +301,22 @@ namespace {
 // tokens: 1024 -> 1024 has 512 / 256 / 128 / 64 workgroups, 3.39 / 2.90 / 3.39 / 3.69 us; 1024 -> 4096 2048 /
 // 1024 / 512 / 256, 7.49 / 5.76 / 5.85 / 4.24).  Past 256 of the largest the ring tiles are the better ones
 // (256 tokens 768 -> 2304, 288 workgroups: 6.41 against 4.69 us).
+// On the shortest reductions there is little to split: all but one to four of the eight wavefronts then only
+// wait at the meeting in LDS, which is longest for the large tiles, and the ring's 64 x 48 tile is done earlier.
+// Each large tile therefore has a least K, by what the ring spends per slice: nothing on decoding (2:4 int8), a
+// decode, or two operands (N >= 3, which had no small ring tile).  Measured on 22 patterns, K 128 to 896,
+// time on the ring over time here, least / median of the shapes: 32 x 64, 2:4 int8 0.82 / 0.90 at K = 128, 0.96 / 0.99
+// at 384, 0.97 / 1.02 at 512, 1.06 / 1.08 at 640; other N <= 2 0.97 / 1.03 at 256, 1.03 / 1.12 at 384; N >= 3 0.90 / 1.05
+// at 128, 1.06 / 1.20 at 256.  32 x 32, N <= 2 0.95 / 0.98 at 128, 1.00 / 1.08 at 256.
 int few_tile(const GemmArgs* items, int count)
 {
-    struct Shape { int cfg, t, o; };
-    static const Shape shapes[] = {{141, 16, 16}, {143, 16, 32}, {142, 32, 32}, {144, 32, 64}};
+    struct Shape { int cfg, t, o, least_k[3]; };
+    static const Shape shapes[] = {{141, 16, 16, {0, 0, 0}}, {143, 16, 32, {0, 0, 0}}, {142, 32, 32, {256, 256, 0}}, {144, 32, 64, {640, 384, 256}}};
+    const int work = items[0].N > 2 ? 2 : (items[0].N == 2 && items[0].M == 4 && items[0].bits == 8) ? 0 : 1;
+    int K = 0;                                 // the longest reduction lasts as long as the launch
+    for (int i = 0; i < count; ++i) K = items[i].K > K ? items[i].K : K;
     for (const Shape& s : shapes) {
+        if (K < s.least_k[work]) continue;
         long long n = 0;
         for (int i = 0; i < count; ++i) n += ((items[i].tokens + s.t - 1ll) / s.t) * ((items[i].O + s.o - 1ll) / s.o);
         if (n <= 256) return s.cfg;

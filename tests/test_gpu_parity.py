@@ -1296,6 +1296,14 @@ def test_quantize_act_feeds_the_sparse_gemm():
     (16, 768, 768, 2, 4, 8, torch.bfloat16, {141}),             # ... 16 x 16
     (128, 768, 2048, 2, 4, 8, torch.bfloat16, {142}),           # ... 32 x 32
     (128, 1024, 4096, 2, 4, 8, torch.bfloat16, {144}),          # ... 32 x 64
+    (64, 128, 3072, 2, 4, 8, torch.bfloat16, {130}),            # reductions too short to split: the ring's smallest tile ...
+    (64, 256, 3072, 2, 4, 8, torch.bfloat16, {142}),
+    (512, 512, 768, 2, 4, 8, torch.bfloat16, {130}),
+    (512, 640, 768, 2, 4, 8, torch.bfloat16, {144}),
+    (512, 256, 768, 1, 4, 8, torch.bfloat16, {130}),
+    (512, 384, 768, 1, 4, 8, torch.bfloat16, {144}),
+    (512, 128, 768, 7, 8, 8, torch.bfloat16, {115, 117, 127}),  # ... or what takes the two-operand patterns
+    (512, 256, 768, 7, 8, 8, torch.bfloat16, {144}),
     (256, 768, 2304, 2, 4, 8, torch.bfloat16, {130}),           # beyond one round of those: the ring's smallest tile
     (200, 768, 3072, 2, 4, 4, torch.bfloat16, {130}),
     (520, 512, 1024, 1, 8, 8, torch.bfloat16, {130}),
