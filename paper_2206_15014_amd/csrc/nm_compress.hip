@@ -594,19 +594,6 @@ compress_generic_kernel(const float* __restrict__ W, int rows, int cols, int ldw
     if (mfill > 0) meta[pm.at((uint32_t)row, mpos)] = (uint8_t)macc;
 }
 
-// Quotient and remainder of a thread number.  A division of 64 bits is on the order of a hundred instructions,
-// so a grid that fits 32 bits divides in 32.
-__device__ __forceinline__ void split_id(long long id, uint32_t by, bool narrow, uint32_t& quotient, uint32_t& remainder)
-{
-    if (narrow) {
-        quotient = (uint32_t)id / by;
-        remainder = (uint32_t)id - quotient * by;
-    } else {
-        quotient = (uint32_t)(id / by);
-        remainder = (uint32_t)(id - (long long)quotient * by);
-    }
-}
-
 // Packed -> dense int8, one thread per (row, group); the group's bytes are all requested before the first is used.
 // 2:4 int8, 3072 x 768 from the tiled layout 7.8 -> 6.8 us (its loads used to wait for one another).
 template <int N, int M, int BITS>

@@ -40,6 +40,19 @@ struct PackedArray {
     }
 };
 
+// Quotient and remainder of a thread number.  A division of 64 bits is on the order of a hundred instructions,
+// so a grid that fits 32 bits divides in 32.
+__device__ __forceinline__ void split_id(long long id, uint32_t by, bool narrow, uint32_t& quotient, uint32_t& remainder)
+{
+    if (narrow) {
+        quotient = (uint32_t)id / by;
+        remainder = (uint32_t)id - quotient * by;
+    } else {
+        quotient = (uint32_t)(id / by);
+        remainder = (uint32_t)(id - (long long)quotient * by);
+    }
+}
+
 inline int index_bits(int N, int M) { return N >= M ? 0 : (M == 4 ? 2 : 4); }
 
 inline PackedArray packed_values(int cols, int N, int M, int bits, int layout)

@@ -6,19 +6,22 @@
 // one more read of W and U for the scales where a scale group is too large for the wavefronts that
 // hold its values (the second read mostly hits the last-level cache).  At these sizes a launch is a
 // few microseconds, so what counts is loads in flight and the number of launches: every lane
-// requests all it needs before its first use (8 loads of 16 bytes), and there are one launch (one row
-// per scale) or two.  The per-row scale array is the only scratch: it first receives the rows'
-// largest magnitudes, negated, and the projection replaces them by the scales while it runs - a
-// value with the sign bit set is a maximum, one without is a scale, and either tells a reader what
-// it needs.  Every arithmetic step is one fp32 operation, in the order the declaration of nm_project
-// states.
+// requests all it needs before its first use.  With one row per scale and up to 4096 columns there is one launch.
+// Otherwise there are two, and three only for large scale groups:
+//  - row maxima, then the projection, which forms the scales.  The per-row scale array is the only scratch: it
+//    first receives the rows' largest magnitudes, negated, and the projection replaces them by the scales
+//    while it runs - a value with the sign bit set is a maximum, one without is a scale, and either tells a
+//    reader what it needs;
+//  - the scales, one workgroup or wavefront per scale group, then the projection (groups of up to 4096 values);
+//  - row maxima, scales, projection.
+// Every arithmetic step is one fp32 operation, in the order the declaration of nm_project states.
 //
-// Measured against three launches (maxima, scales, one thread per group of M columns, a load at a time):
-// 3072 x 768 (2:4 int8, 32 rows per scale) 7.3 + 2.4 + 6.7 -> 7.0 + 5.6 us, 768 x 3072 10.0 + 2.4 + 8.2 -> 7.0 +
-// 7.0, 768 x 768 3.6 + 2.4 + 3.8 -> 3.7 + 4.8; the 48 matrices of a BERT-base encoder 748 -> 597 us, of
-// which moving every byte once takes about 250.
+// Measurements stand at the rules of launch_project_m.  The 48 matrices of a BERT-base encoder (32 rows per scale, operands from
+// HBM), against three launches a matrix with a load at a time per thread: 748 -> 598 us, of which moving every byte once takes about 250.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "nm_internal.h"
 
@@ -43,9 +46,9 @@ __device__ __forceinline__ int wave_max_i(int m)
 
 __device__ __forceinline__ float scale_of_max(float m, float qmax) { return (m == 0.0f) ? 1.0f : __fdiv_rn(m, qmax); }
 
-// COUNT groups of F float4s of W + U, at a time: every load is requested before the first sum (one
-// test of U for all of them: a test per load would leave each to wait for the one before it).
-template <int COUNT, int F, typename At>
+// COUNT groups of F float4s of W + U: one test of U for all of them (a test per load would leave each to wait for the one
+// before it), and, where TOGETHER, every load requested before the first sum.
+template <int COUNT, int F, bool TOGETHER = true, typename At>
 __device__ __forceinline__ void sums_at(const float* W, const float* U, At at, float4 (&x)[COUNT][F])
 {
 #pragma unroll
@@ -58,7 +61,7 @@ __device__ __forceinline__ void sums_at(const float* W, const float* U, At at, f
     for (int i = 0; i < COUNT; ++i)
 #pragma unroll
         for (int f = 0; f < F; ++f) u[i][f] = *reinterpret_cast<const float4*>(U + at(i) + 4 * f);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (TOGETHER) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < COUNT; ++i)
 #pragma unroll
@@ -70,50 +73,73 @@ __device__ __forceinline__ void sums_at(const float* W, const float* U, At at, f
         }
 }
 
+// f(std::integral_constant<int, min(count, MOST)>): `count` (at least 1) is uniform over the wavefront, so a wavefront
+// requests no more than the row has left for it, and still all of that at once.
+template <int MOST, typename F>
+__device__ __forceinline__ void with_count(int count, F f)
+{
+    if constexpr (MOST > 1) {
+        if (count < MOST) return with_count<MOST - 1>(count, f);
+    }
+    f(std::integral_constant<int, MOST>{});
+}
+
 __device__ __forceinline__ float max4(float m, const float4& v)
 {
     return fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
 }
 
-// -(largest |W + U|) of every row: -0 for a row of zeros.  WAVES wavefronts per row (1: four rows per
-// workgroup), four 16-byte pieces of W and of U per lane in flight.
-template <int WAVES>
+// max over aligned groups of LANES lanes
+template <int LANES>
+__device__ __forceinline__ float lanes_max_f(float m)
+{
+#pragma unroll
+    for (int d = LANES / 2; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+    return m;
+}
+
+// -(largest |W + U|) of every row: -0 for a row of zeros.  LANES lanes per row: 16 (16 rows per workgroup), a
+// wavefront, or the whole workgroup; four or five 16-byte pieces of W and of U per lane in flight.
+template <int LANES>
 __global__ void __launch_bounds__(256)
 project_amax_kernel(const float* __restrict__ W, const float* __restrict__ U, int rows, int cols, int ldw,
                     float* __restrict__ amax, int vec)         // vec: rows are whole, 16-byte aligned float4s
 {
     __shared__ float part[4];
-    constexpr int STEP = 64 * WAVES;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = WAVES == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
-    if (row >= rows) return;                   // WAVES > 1: one row per workgroup, none leaves before the barrier
-    const int at = WAVES == 1 ? lane : (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int row = (int)(blockIdx.x * (256 / LANES) + threadIdx.x / LANES), at = (int)threadIdx.x % LANES;
+    if (row >= rows) return;                   // LANES = 256: one row per workgroup, none leaves before the barrier
     const size_t base = (size_t)row * ldw;
     float m = 0.0f;
     if (vec) {
-        const int last = cols / 4 - 1;
-        for (int i = at; i <= last; i += 4 * STEP) {
-            float4 v[4][1];
-            sums_at<4, 1>(W, U, [&](int k) __attribute__((always_inline)) { return base + 4 * (size_t)min(i + k * STEP, last); }, v);    // (the last piece again past the end)
+        const int pieces = cols / 4;
+        int i = LANES == 256 ? 64 * wave : 0;  // the wavefront's first piece (of each of its rows)
+        while (i < pieces) {
+            const int left = (pieces - i + LANES - 1) / LANES, take = left > 5 ? 4 : left;
+            with_count<5>(take, [&](auto count) __attribute__((always_inline)) {
+                constexpr int C = decltype(count)::value;
+                float4 v[C][1];
+                const int from = LANES == 256 ? i + (at & 63) : i + at;
+                sums_at<C, 1>(W, U, [&](int k) __attribute__((always_inline)) { return base + 4 * (size_t)min(from + k * LANES, pieces - 1); }, v);    // (the last piece again past the end)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) m = max4(m, v[k][0]);
+                for (int k = 0; k < C; ++k) m = max4(m, v[k][0]);
+            });
+            i += take * LANES;
         }
     } else {                                   // any alignment, any width: one float at a time
-        for (int c = at; c < cols; c += STEP) {
+        for (int c = at; c < cols; c += LANES) {
             float v = W[base + c];
             if (U) v = __fadd_rn(v, U[base + c]);
             m = fmaxf(m, fabsf(v));
         }
     }
-    m = wave_max_f(m);
-    if constexpr (WAVES > 1) {
-        if (lane == 0) part[wave] = m;
+    m = lanes_max_f<LANES < 64 ? LANES : 64>(m);
+    if constexpr (LANES == 256) {
+        if (at % 64 == 0) part[wave] = m;
         __syncthreads();
         m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
-        if (threadIdx.x == 0) amax[row] = -m;
-    } else {
-        if (lane == 0) amax[row] = -m;
     }
+    if (at == 0) amax[row] = -m;
 }
 
 // Row maxima -> scales of the row groups, in place: one wavefront per group of rows_per_scale
@@ -130,6 +156,41 @@ project_scale_kernel(float* __restrict__ s, int rows, int rows_per_scale, float 
     m = wave_max_f(m);
     const float scale = scale_of_max(m, qmax);
     for (int r = (int)r0 + lane; r < r1; r += 64) s[r] = scale;
+}
+
+// Maxima and scales in one launch for scale groups of up to 16 values per lane, every value of the group in flight at
+// once: LANES = 64, a wavefront per group (1024 values), or 256, a workgroup (4096).
+template <int LANES>
+__global__ void __launch_bounds__(256)
+project_group_scale_kernel(const float* __restrict__ W, const float* __restrict__ U, int rows, int cols, int ldw, int rows_per_scale,
+                           int groups, float qmax, float* __restrict__ s)
+{
+    __shared__ float part[4];
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int group = LANES == 64 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x, at = LANES == 64 ? lane : (int)threadIdx.x;
+    if (group >= groups) return;               // LANES = 256: none leaves before the barrier
+    const int r0 = group * rows_per_scale, r1 = rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale;
+    const int width = cols / 4, pieces = (r1 - r0) * width, first = LANES == 64 ? 0 : 64 * wave;
+    float m = 0.0f;
+    if (first < pieces)
+        with_count<4>((pieces - first + LANES - 1) / LANES, [&](auto count) __attribute__((always_inline)) {
+            constexpr int C = decltype(count)::value;
+            float4 v[C][1];
+            sums_at<C, 1>(W, U, [&](int k) __attribute__((always_inline)) {
+                const unsigned i = (unsigned)min(at + LANES * k, pieces - 1), r = i / (unsigned)width;
+                return (size_t)(r0 + (int)r) * ldw + 4 * (size_t)(i - r * (unsigned)width);
+            }, v);
+#pragma unroll
+            for (int k = 0; k < C; ++k) m = max4(m, v[k][0]);
+        });
+    m = wave_max_f(m);
+    if constexpr (LANES == 256) {
+        if (lane == 0) part[wave] = m;
+        __syncthreads();
+        m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    }
+    const float scale = scale_of_max(m, qmax);
+    for (int r = r0 + at; r < r1; r += LANES) s[r] = scale;
 }
 
 // One group of M consecutive columns: z = Pi(v), the kept entries at scale s where bits > 0.
@@ -193,11 +254,11 @@ __device__ __forceinline__ void project_group(const float (&v)[M], int N, int bi
 }
 
 // P groups of M columns; at(i) is the place of the i-th.
-template <int M, int P, typename At>
+template <int M, int P, bool TOGETHER = true, typename At>
 __device__ __forceinline__ void load_groups(const float* W, const float* U, At at, float (&v)[P][M])
 {
     float4 x[P][M / 4];
-    sums_at<P, M / 4>(W, U, at, x);
+    sums_at<P, M / 4, TOGETHER>(W, U, at, x);
 #pragma unroll
     for (int i = 0; i < P; ++i)
 #pragma unroll
@@ -260,26 +321,25 @@ project_row_kernel(const float* __restrict__ W, const float* U, int rows, int co
     }
 }
 
-// One wavefront per 64 * P groups of a row.  rows_per_scale > 0: scales[] holds the row maxima, negated,
-// and this launch turns them into scales: the wavefront at a row's start writes the row's, while
+// One wavefront per PER * 64 groups of a row, `chunks` of them.  rows_per_scale > 0: scales[] holds the row maxima,
+// negated, and this launch turns them into scales: the wavefront at a row's start writes the row's, while
 // others still read.  A reader takes the largest of its group's values as signed integers: any scale (sign
 // bit clear, and all rows of a group get the same one) is above every maximum, and among maxima (sign bit
 // set) the larger magnitude is the larger integer.  So it ends with the scale itself or with the group's
 // largest magnitude, whichever mixture it met.
 // rows_per_scale = 0: scales[row] is final.
-template <int M>
+template <int M, int PER>
 __global__ void __launch_bounds__(256)
 project_wave_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw, int N, int bits, int rows_per_scale,
                     float* scales, float* __restrict__ Z, float* U_out, int ldz, int chunks)
 {
-    constexpr int P = 16 / M;
     const int lane = threadIdx.x & 63;
     const unsigned id = (unsigned)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4u + (threadIdx.x >> 6)));
     const int row = (int)(id / (unsigned)chunks), chunk = (int)(id - (unsigned)row * (unsigned)chunks);
     if (row >= rows) return;                   // no barrier below
-    const int groups = cols / M, g0 = chunk * (64 * P) + lane;
-    float v[P][M];
-    load_groups<M, P>(W, U, [&](int i) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)min(g0 + i * 64, groups - 1) * M; }, v);
+    const int groups = cols / M, g0 = chunk * (64 * PER) + lane;
+    float v[PER][M];
+    load_groups<M, PER>(W, U, [&](int i) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)min(g0 + i * 64, groups - 1) * M; }, v);
     float s = 1.0f;
     if (bits && rows_per_scale > 0) {
         const int r0 = row / rows_per_scale * rows_per_scale, r1 = rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale;
@@ -295,7 +355,7 @@ project_wave_kernel(const float* __restrict__ W, const float* U, int rows, int c
         s = scales[row];
     }
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
+    for (int i = 0; i < PER; ++i) {
         if (g0 + i * 64 >= groups) break;
         float z[M];
         project_group<M>(v[i], N, bits, s, z);
@@ -303,30 +363,46 @@ project_wave_kernel(const float* __restrict__ W, const float* U, int rows, int c
     }
 }
 
+// `per` up to MOST
+template <int M, int MOST, typename... Args>
+void launch_project_wave(int per, unsigned blocks, hipStream_t st, Args... args)
+{
+    if constexpr (MOST > 1) {
+        if (per < MOST) return launch_project_wave<M, MOST - 1>(per, blocks, st, args...);
+    }
+    hipLaunchKernelGGL((project_wave_kernel<M, MOST>), dim3(blocks), dim3(256), 0, st, args...);
+}
+
 // One thread per group of M consecutive columns, rows of any length one after the other; scales[row] is final.
-template <int M>
+// NARROW: the threads' numbers fit 32 bits.
+template <int M, bool NARROW>
 __global__ void __launch_bounds__(256)
 project_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw,
                int N, int bits, const float* __restrict__ scales, float* __restrict__ Z, float* U_out, int ldz)
 {
     const int groups = cols / M;
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (id >= (long long)rows * groups) return;
-    const int row = (int)(id / groups), g = (int)(id - (long long)row * groups);
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x, total = (long long)rows * groups;
+    if (id >= total) return;
+    uint32_t row, g;
+    split_id(id, (uint32_t)groups, NARROW, row, g);
+    const float s = bits ? scales[row] : 1.0f;
     float v[1][M], z[M];
-    load_groups<M, 1>(W, U, [&](int) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)g * M; }, v);
-    project_group<M>(v[0], N, bits, bits ? scales[row] : 1.0f, z);
+    load_groups<M, 1, false>(W, U, [&](int) __attribute__((always_inline)) { return (size_t)row * ldw + (size_t)g * M; }, v);
+    project_group<M>(v[0], N, bits, s, z);
     store_group<M>(v[0], z, Z, U_out, (size_t)row * ldz + (size_t)g * M);
 }
 
-// Four wavefronts per row once a row is more than four 16-byte pieces per lane of one: 768 x 3072 on one wavefront
-// per row is three rounds of loads one after the other on 768 wavefronts, 10.0 us against 7.0.
+// Lanes per row by the pieces a row has: a lane holds up to five, and fewer rows than fill the chip are better spread
+// out.  30522 x 64: a wavefront per row 7.2 us, 16 lanes 3.6; 4096 x 768 maxima 5.8 -> 4.8 with all pieces in flight;
+// 768 x 3072 on one wavefront per row is three rounds of loads one after the other on 768 wavefronts, 7.1 against 4.6.
 void launch_row_maxima(const float* W, const float* U, int rows, int cols, int ldw, float* amax, int vec, hipStream_t st)
 {
-    if (cols > 1024 && rows <= (1 << 23))
-        hipLaunchKernelGGL(project_amax_kernel<4>, dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
+    if (cols <= 64 || (cols <= 256 && rows >= 8192))
+        hipLaunchKernelGGL(project_amax_kernel<16>, dim3((rows + 15) / 16), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
+    else if (cols <= 1280 || rows > (1 << 23))
+        hipLaunchKernelGGL(project_amax_kernel<64>, dim3((rows + 3) / 4), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
     else
-        hipLaunchKernelGGL(project_amax_kernel<1>, dim3((rows + 3) / 4), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
+        hipLaunchKernelGGL(project_amax_kernel<256>, dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, amax, vec);
 }
 
 void launch_max_to_scale(float* scales, int rows, int rows_per_scale, float qmax, hipStream_t st)
@@ -349,20 +425,57 @@ void launch_project_m(const float* W, const float* U, int rows, int cols, int ld
         hipLaunchKernelGGL((project_row_kernel<M, 4>), dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
         return;
     }
-    // Wavefronts within a row need rows that fill one (and a launch holds fewer than 2^32 threads); every one
-    // of them reads its group's maxima, which stays cheaper than a launch of its own up to a few hundred rows.
-    const long long chunks = (groups + 1024 / M - 1) / (1024 / M), waves = chunks * rows;
-    const bool wide = groups >= 64 && waves <= (1 << 25);
-    const bool finish = wide && rows_per_scale <= 256;
-    if (bits) {
+    // Two ways to project.  project_wave_kernel has a row's groups in one or a few wavefronts, so it can form the
+    // scales, and its loads are all in flight; project_kernel wastes no lane and needs no row of 64 groups.  Three ways to
+    // the scales.  The lines below are where the measured times cross (16 to 30522 rows, 8 to 8192 columns, 1 to 300
+    // rows per scale, U given; the first figure is maxima, scales and projection in three launches unless it says otherwise):
+    //  - forming the scales in the projection saves a launch, which counts up to a few million values (4096 x 768, 2:4,
+    //    32 rows per scale 17.0 -> 12.4 us; 768 x 4096 19.6 -> 12.9), while beyond, the second kernel is bound by its
+    //    bytes and lanes without a group cost more (30522 x 776, 194 of 256 lanes used: 91.8 -> 95.8, so in three).  For
+    //    M = 8 it stays ahead at any size (30522 x 640, 4:8: 82.2 -> 76.8): a thread of project_kernel has less in flight;
+    //  - every wavefront reads its scale group's maxima: free up to 64 rows, later only with few wavefronts (256 rows per
+    //    scale: 4096 x 768 17.9 -> 13.1, but 30522 x 768 93.7 -> 112, so in three);
+    //  - small scale groups in a launch of their own (4096 x 128, 8 rows per scale 8.1 -> 5.5; 30522 x 8, 32 rows
+    //    13.4 -> 4.5), except for wide rows of medium-sized matrices (4096 x 768, 2 rows per scale: 15.6, scales in the
+    //    projection 12.4);
+    //  - with final scales the wave kernel is ahead between 2 and 8 million values (4096 x 768, no scales 9.5 -> 8.1), for M =
+    //    8 to 24 million.
+    const int turns = (groups + 63) / 64;
+    constexpr int P = 16 / M;                  // a lane holds 16 columns, 20 (M = 4) or 24 to save a nearly empty wavefront, one group in a small matrix
+    const long long elements = (long long)rows * cols;
+    const int by = (long long)rows * turns <= 2048 ? turns : (turns + (M == 4 ? 2 : 0)) / P;
+    const int chunks = by > 0 ? by : 1, per = (turns + chunks - 1) / chunks;
+    const long long waves = (long long)chunks * rows;
+    const bool fits = groups >= 64 && waves <= (1 << 25);                          // (a launch holds fewer than 2^32 threads)
+    const int used = (int)(groups * 100ll / (turns * 64ll));                       // percent of the lanes' loads that are the row's
+    const int span = rows_per_scale < rows ? rows_per_scale : rows;                // rows of a full scale group
+    const long long n_groups = ((long long)rows + rows_per_scale - 1) / rows_per_scale;
+    const bool small_group = bits && (long long)span * cols <= 4096 && n_groups <= (1 << 23);
+    const bool group_first = small_group && (elements <= (3 << 19) || (M == 4 ? cols <= 512 : used < 60 || elements >= (24 << 20)));
+    const bool finish = bits && fits && (span <= 64 || (span <= 256 && waves <= 4096)) && !group_first &&
+                        (M == 8 || elements < (1 << 20) || (used >= 60 && elements < (6 << 20)) || (used >= 90 && elements < (12 << 20)));
+    if (bits && !finish && small_group) {
+        // A wavefront per group where a workgroup would be mostly idle.  At 1024 values and above a workgroup's group is one
+        // or more whole workgroups of project_kernel, which then finds W and U in its own XCD's L2 (30522 x 128, 8 rows
+        // per scale 16.8 us, a wavefront per group 19.4).
+        if ((long long)span * cols < 1024)
+            hipLaunchKernelGGL(project_group_scale_kernel<64>, dim3((unsigned)((n_groups + 3) / 4)), dim3(256), 0, st, W, U, rows, cols, ldw,
+                               rows_per_scale, (int)n_groups, qmax, scales);
+        else
+            hipLaunchKernelGGL(project_group_scale_kernel<256>, dim3((unsigned)n_groups), dim3(256), 0, st, W, U, rows, cols, ldw,
+                               rows_per_scale, (int)n_groups, qmax, scales);
+    } else if (bits) {
         launch_row_maxima(W, U, rows, cols, ldw, scales, 1, st);
         if (!finish) launch_max_to_scale(scales, rows, rows_per_scale, qmax, st);
     }
-    if (wide)
-        hipLaunchKernelGGL(project_wave_kernel<M>, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits,
-                           finish ? rows_per_scale : 0, scales, Z, U_out, ldz, (int)chunks);
+    if (finish || (fits && !small_group && used >= 60 && elements >= (2 << 20) && elements < (M == 4 ? 8 << 20 : 24 << 20)))
+        launch_project_wave<M, M == 4 ? 5 : 3>(per, (unsigned)((waves + 3) / 4), st, W, U, rows, cols, ldw, N, bits, finish ? rows_per_scale : 0,
+                                               scales, Z, U_out, ldz, chunks);
+    else if ((long long)rows * groups <= 0xFFFFFFFFll)
+        hipLaunchKernelGGL((project_kernel<M, true>), dim3((unsigned)(((long long)rows * groups + 255) / 256)), dim3(256), 0, st, W, U, rows, cols,
+                           ldw, N, bits, scales, Z, U_out, ldz);
     else
-        hipLaunchKernelGGL(project_kernel<M>, dim3((unsigned)(((long long)rows * groups + 255) / 256)), dim3(256), 0, st, W, U, rows, cols,
+        hipLaunchKernelGGL((project_kernel<M, false>), dim3((unsigned)(((long long)rows * groups + 255) / 256)), dim3(256), 0, st, W, U, rows, cols,
                            ldw, N, bits, scales, Z, U_out, ldz);
 }
 

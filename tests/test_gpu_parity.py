@@ -6,6 +6,7 @@ bf16 step of the oracle's rounding; int8 output codes equal to the oracle's exce
 stated distance of a half-way point (see check_q8).
 """
 import contextlib
+import ctypes
 
 import numpy as np
 import pytest
@@ -899,6 +900,56 @@ def test_project_rows_at_the_edges_of_its_kernels(M):
             assert np.array_equal(Uo.view(np.uint32), Ur.view(np.uint32)), what + ": U differs"
             if bits:
                 assert np.array_equal(s, sr), what + ": scales differ"
+
+
+@pytest.mark.parametrize("M,rows,cols,cases", [
+    (4, 9, 256, [(4, 2, 8), (5, 2, 8)]),                   # groups of 1024 values (a workgroup each) and just above
+    (4, 70, 252, [(4, 1, 4), (16, 2, 8), (17, 3, 8)]),     # just below (a wavefront each); just below 4096 values and above
+    (8, 70, 256, [(3, 2, 8), (16, 4, 8), (17, 2, 4)]),
+    (4, 300, 12, [(7, 2, 8), (85, 1, 8), (300, 2, 8), (500, 2, 8)]),     # the last group shorter, one group for all rows
+    (4, 40, 64, [(65, 2, 8)]), (4, 80, 64, [(65, 2, 8)]), (4, 40, 68, [(70, 2, 8)]),      # rows on 16 lanes and on 64
+    (8, 8200, 256, [(32, 2, 8)]),
+    (4, 5, 1280, [(5, 2, 8)]), (4, 5, 1284, [(5, 2, 8)]),  # five pieces per lane; the workgroup's row
+    (4, 700, 1288, [(32, 2, 8), (700, 1, 4)]),             # six turns of 64 groups: two wavefronts of three
+    (4, 2100, 264, [(32, 2, 8)]), (4, 2100, 1088, [(70, 2, 8), (1, 2, 0)]),      # a wavefront nearly empty; five turns on one
+    (8, 1000, 1288, [(40, 2, 8)]), (8, 2100, 1040, [(64, 4, 8), (65, 4, 8), (1, 3, 0)]),
+    (4, 1050, 2056, [(33, 2, 8), (300, 2, 8)]),
+])
+def test_project_every_way_to_the_scales_and_to_share_a_row(M, rows, cols, cases):
+    """Scales from the maxima inside the projection, from one launch per scale group, or in a launch of their own;
+    rows on one to five groups per lane and any number of wavefronts; with and without U, in place."""
+    rng = np.random.default_rng([M, rows, cols])
+    W = (rng.standard_normal((rows, cols)) * rng.random((rows, 1)) * 0.05).astype(np.float32)
+    W[rng.integers(0, rows)] = 0.0
+    U = (rng.standard_normal((rows, cols)) * 0.004).astype(np.float32)
+    for rps, N, bits in cases:
+        say("project ways", rows, cols, N, M, bits, rps)
+        for u in (U, None):
+            Zr, Ur, sr = oracle.admm_project(W, u if u is not None else np.zeros_like(W), N, M, bits, rps)
+            Z, Uo, s = run_project(W, u, N, M, bits, rps, in_place=u is not None and rps % 2 == 0)
+            assert np.array_equal(Z.view(np.uint32), Zr.view(np.uint32)), "rps %d: Z differs" % rps
+            assert np.array_equal(Uo.view(np.uint32), Ur.view(np.uint32)), "rps %d: U differs" % rps
+            assert not bits or np.array_equal(s, sr), "rps %d: scales differ" % rps
+
+
+@pytest.mark.parametrize("rows,cols,N,M,bits,rps,launches", [
+    (3072, 768, 2, 4, 8, 1, 1), (3072, 768, 2, 4, 0, 1, 1), (3072, 768, 2, 4, 8, 32, 2),
+    (4096, 128, 2, 4, 8, 8, 2), (2048, 256, 4, 8, 8, 2, 2), (768, 64, 2, 4, 8, 32, 2), (30522, 8, 2, 4, 8, 32, 2),      # narrow rows
+    (768, 768, 2, 4, 8, 256, 2), (768, 768, 2, 4, 8, 300, 3),
+])
+def test_project_number_of_launches(rows, cols, N, M, bits, rps, launches):
+    """A launch is a large part of a small projection: scale groups of up to 4096 values, and wide rows at up to 256
+    rows per scale, need two."""
+    say("project launches", rows, cols, N, M, bits, rps)
+    W, U = (torch.zeros((rows, cols), dtype=torch.float32, device=DEV) for _ in range(2))
+    Z, V, s = torch.empty_like(W), torch.empty_like(W), torch.empty(rows, dtype=torch.float32, device=DEV)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        nm.nm_project(W, U, N, M, bits, rps, Z=Z, U_out=V, scales=s if bits else None)
+    nodes = ctypes.c_size_t(0)
+    hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))      # the process's one copy
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    assert nodes.value == launches
 
 
 # ---- one scale per group of rows (nm_compress_grouped): packed bytes and scales bit-exact --------
