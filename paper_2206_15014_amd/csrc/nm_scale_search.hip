@@ -4,7 +4,7 @@
 // fixes (the paper states the criterion, not an algorithm).
 //
 // Three launches: the rows' largest magnitudes (into the scales array, negated), the error of every
-// candidate per row (one workgroup per row, double precision, into the workspace), and per group
+// candidate per row (a workgroup or a wavefront per row, double precision, into the workspace), and per group
 // the sum over its rows and the choice; the last two form the group's max-rule scale themselves.
 // The per-row partial errors are the only scratch memory: [rows][candidates / 2 + 1] doubles.  Sums
 // run in a fixed order (lane-strided partial sums, a fixed butterfly over the wavefront, then the
@@ -130,21 +130,25 @@ __device__ __forceinline__ void row_sums(const float* __restrict__ w, int groups
 }
 
 // scales[]: the rows' maxima, negated (maxima != 0), or every row's max-rule scale.  err[row][k] = the row's
-// sum for candidate k = c - candidates / 2.  Wavefront w of the workgroup takes candidates w, w + 4, ...
-template <int N, int M, int CPW>
+// sum for candidate k = c - candidates / 2.  WAVES = 4 wavefronts per row: wavefront w of the workgroup takes candidates
+// w, w + 4, ...; WAVES = 1: a wavefront takes a row with all its candidates.
+template <int N, int M, int WAVES, int CPW>
 __global__ void __launch_bounds__(256)
 row_errors_kernel(const float* __restrict__ W, int rows, int cols, int ldw, float qmax, int rows_per_scale, int maxima, int candidates,
                   const float* __restrict__ scales, double* __restrict__ err)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nc = candidates / 2 + 1;
-    for (int row = blockIdx.x; row < rows; row += gridDim.x) {           // no barrier below
+    const int first = WAVES == 4 ? wave : 0;
+    if (first >= nc) return;                   // no barrier below
+    for (long long at = WAVES == 4 ? blockIdx.x : 4ll * blockIdx.x + wave; at < rows; at += (WAVES == 4 ? 1ll : 4ll) * gridDim.x) {
+        const int row = (int)at;
         const int r0 = maxima ? row / rows_per_scale * rows_per_scale : row;
         const float smax = max_rule_scale(scales, r0, rows - r0 < rows_per_scale ? rows : r0 + rows_per_scale, maxima, qmax, lane);
         double e[CPW];
         float s[CPW];
 #pragma unroll
-        for (int i = 0; i < CPW; ++i) s[i] = candidate_scale(smax, candidates / 2 + min(wave + 4 * i, nc - 1), candidates);
+        for (int i = 0; i < CPW; ++i) s[i] = candidate_scale(smax, candidates / 2 + min(first + WAVES * i, nc - 1), candidates);
         // The candidates lie between half of smax and smax, and |w| is at most 127 smax: within the range of the
         // reciprocal route, which holds up to |w| = 254 s as it does up to 127 s.
         if (smax >= 0x1p-59f && smax <= 0x1p60f) {
@@ -163,7 +167,7 @@ row_errors_kernel(const float* __restrict__ W, int rows, int cols, int ldw, floa
             double t = e[i];
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) t = __dadd_rn(t, __shfl_xor(t, d, 64));
-            if (lane == 0 && wave + 4 * i < nc) err[(size_t)row * nc + wave + 4 * i] = t;
+            if (lane == 0 && first + WAVES * i < nc) err[(size_t)row * nc + first + WAVES * i] = t;
         }
     }
 }
@@ -207,12 +211,25 @@ template <int N, int M>
 void launch_row_errors(const float* W, int rows, int cols, int ldw, float qmax, int rows_per_scale, int maxima, int candidates,
                        const float* scales, double* err, hipStream_t st)
 {
-    const dim3 grid((unsigned)(rows < (1 << 20) ? rows : (1 << 20))), wg(256);       // a launch holds fewer than 2^32 threads
-    const int share = (candidates / 2 + 1 + 3) / 4;                                   // candidates per wavefront: 1 .. 9
-#define NM_SHARE(n) hipLaunchKernelGGL((row_errors_kernel<N, M, n>), grid, wg, 0, st, W, rows, cols, ldw, qmax, rows_per_scale, maxima, candidates, scales, err)
-    if (share <= 3) NM_SHARE(3);
-    else if (share <= 5) NM_SHARE(5);
-    else NM_SHARE(9);
+    const int nc = candidates / 2 + 1;
+    // Picking out the kept entries is work that every wavefront of a row repeats.  With few candidates it is most of the
+    // work, and once the rows alone fill the chip a row is one wavefront's (7:8, 4096 x 3072, one row per scale: 2
+    // candidates in the call, so 2 errors, 87 us on four wavefronts, 35.6 on one; 8, so 5, 87 and 49; 2:4, 4096 x 768, 32 rows
+    // per scale, 2 candidates: 20.8 and 11.9).  The kernels are compiled for 2, 4 and 6 errors, and for 3, 5 and 9 on each of four wavefronts: 16, 32
+    // and 64 candidates in the call need 9, 17 and 33; between them a few sums are formed in vain.
+    const int wgs = nc <= 6 && rows >= 2048 ? (rows + 3) / 4 : rows;
+    const dim3 grid((unsigned)(wgs < (1 << 20) ? wgs : (1 << 20))), wg(256);         // a launch holds fewer than 2^32 threads
+#define NM_SHARE(w, n) hipLaunchKernelGGL((row_errors_kernel<N, M, w, n>), grid, wg, 0, st, W, rows, cols, ldw, qmax, rows_per_scale, maxima, candidates, scales, err)
+    if (wgs != rows) {
+        if (nc <= 2) NM_SHARE(1, 2);
+        else if (nc <= 4) NM_SHARE(1, 4);
+        else NM_SHARE(1, 6);
+        return;
+    }
+    const int share = (nc + 3) / 4;            // candidates per wavefront: 1 .. 9
+    if (share <= 3) NM_SHARE(4, 3);
+    else if (share <= 5) NM_SHARE(4, 5);
+    else NM_SHARE(4, 9);
 #undef NM_SHARE
 }
 

@@ -1041,15 +1041,23 @@ def test_scale_search_matches_oracle_and_feeds_compress(N, M, bits, rps):
     check_outputs(acc_ref, sx, s_dev.cpu().numpy(), bias, res["acc"], res["f32"], None, what="gemm on searched scales")
 
 
+@pytest.mark.parametrize("C", [2, 4, 6, 8, 10, 12])
+@pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (7, 8, 8)])
+@pytest.mark.parametrize("rows", [2047, 2048, 2051])
+def test_scale_search_few_candidates_on_many_rows(N, M, bits, C, rows):
+    """From 2048 rows on a wavefront takes a whole row where the candidates are few."""
+    test_scale_search_candidate_counts_and_scale_ranges(N, M, bits, C, shapes=[(rows, 3 * M, 1), (rows, 72, 100)])
+
+
 @pytest.mark.parametrize("C", [2, 8, 22, 24, 38, 40, 64])
 @pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (3, 4, 4), (4, 4, 8), (7, 8, 8), (8, 8, 4)])
-def test_scale_search_candidate_counts_and_scale_ranges(N, M, bits, C):
+def test_scale_search_candidate_counts_and_scale_ranges(N, M, bits, C, shapes=None):
     """Candidate counts at the edges of the wavefronts' shares; rows of zeros, rows whose scale lies outside the
     range of the reciprocal route, an unaligned matrix; groups above and below 256 rows.  The oracle's choice, or one
     whose error the oracle puts within 1e-12 of the least."""
     say("scale search shares", N, M, bits, C)
     rng = np.random.default_rng([N, M, bits, C])
-    for rows, cols, rps in [(6, 64 * M + M, 1), (300, 40, 256), (300, 40, 300)]:
+    for rows, cols, rps in shapes or [(6, 64 * M + M, 1), (300, 40, 256), (300, 40, 300)]:
         W = (rng.standard_normal((rows, cols)) * rng.random((rows, 1)) * 0.05).astype(np.float32)
         W[1] = 0.0
         if rps == 1:
