@@ -594,37 +594,48 @@ compress_generic_kernel(const float* __restrict__ W, int rows, int cols, int ldw
     if (mfill > 0) meta[pm.at((uint32_t)row, mpos)] = (uint8_t)macc;
 }
 
-// Packed -> dense int8, one thread per (row, group); the group's bytes are all requested before the first is used.
-// 2:4 int8, 3072 x 768 from the tiled layout 7.8 -> 6.8 us (its loads used to wait for one another).
+// Packed -> dense int8, one thread per (row, group); the group's bytes are all requested before the first is used, each
+// once.  Bound by the number of byte loads (captured, from the tiled layout): 2:4 int8, 3072 x 768 6.8 us with a load waiting
+// for the one before it, 6.2 with a load per entry of codes and of offsets in flight, 5.2 with one per byte; 7:8 int4, 30522 x
+// 768 62, 65 and 43 us.
 template <int N, int M, int BITS>
 __global__ void __launch_bounds__(256)
 decompress_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int rows, int cols,
                   PackedArray pv, PackedArray pm, int8_t* __restrict__ Wq)
 {
     constexpr int IB = (N >= M) ? 0 : (M == 4) ? 2 : 4;
+    constexpr int VB = BITS == 8 ? N : (N + 1) / 2;                    // bytes a group's codes touch (an odd N: from either half of the first)
+    constexpr int MB = IB == 4 ? (N + 1) / 2 : N == 3 ? 2 : 1;         // and its offsets
     const int groups = cols / M;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x, total = (long long)rows * groups;
     if (id >= total) return;
     uint32_t row, g;
     split_id(id, (uint32_t)groups, total <= 0xFFFFFFFFll, row, g);
-    uint8_t v[N], m[N];
+    const uint32_t e = g * (uint32_t)N;        // the group's first entry
+    uint8_t v[VB], m[MB];
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-        const uint32_t e = g * (uint32_t)N + (uint32_t)j;
-        v[j] = vals[pv.at(row, BITS == 8 ? e : e >> 1)];
-        if constexpr (IB > 0) m[j] = meta[pm.at(row, IB == 2 ? e >> 2 : e >> 1)];
+    for (int i = 0; i < VB; ++i) v[i] = vals[pv.at(row, (BITS == 8 ? e : e >> 1) + (uint32_t)i)];
+    if constexpr (IB > 0) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) m[i] = meta[pm.at(row, IB == 4 ? (e >> 1) + (uint32_t)i : i ? (e + 2) >> 2 : e >> 2)];
+    }
+    uint64_t codes = 0, offsets = 0;
+#pragma unroll
+    for (int i = 0; i < VB; ++i) codes |= (uint64_t)v[i] << (8 * i);
+    if constexpr (BITS == 4) codes >>= 4 * (e & 1u);
+    if constexpr (IB > 0) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) offsets |= (uint64_t)m[i] << (8 * i);
+        offsets >>= IB == 4 ? 4 * (e & 1u) : 2 * (e & 3u);
     }
     uint64_t out = 0;                          // byte c = column c of the group
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        const uint32_t e = g * (uint32_t)N + (uint32_t)j;
-        int q, off;
-        if constexpr (BITS == 8) q = (int8_t)v[j];
-        else { const int nib = (v[j] >> ((e & 1) * 4)) & 15; q = (nib ^ 8) - 8; }
-        if constexpr (IB == 0) off = j;
-        else if constexpr (IB == 2) off = (m[j] >> ((e & 3) * 2)) & 3;
-        else off = (m[j] >> ((e & 1) * 4)) & 15;
-        const int sh = 8 * (off & 7);
+        int q, off = j;
+        if constexpr (BITS == 8) q = (int8_t)(codes >> (8 * j));
+        else q = (((int)(codes >> (4 * j)) & 15) ^ 8) - 8;
+        if constexpr (IB > 0) off = (int)(offsets >> (IB * j)) & (IB == 4 ? 7 : 3);
+        const int sh = 8 * off;
         out = (out & ~(0xFFull << sh)) | ((uint64_t)(uint8_t)q << sh);
     }
     int8_t* dst = Wq + (size_t)row * cols + (size_t)g * M;
@@ -640,8 +651,7 @@ decompress_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ 
 // The packed arrays from one layout to the other, `width` bytes per thread: the widest word that stays
 // within one piece of a unit in the tiled layout and is aligned on both sides (the launcher's choice, per
 // array).  Rows that only pad the tiled layout to a multiple of 16 are written as zeros.  Both arrays in
-// one launch: 2:4 int8, 3072 x 768 5.5 + 3.0 us at a byte
-// per thread -> 3.2 us.
+// one launch: 2:4 int8, 3072 x 768 5.5 + 3.0 us at a byte per thread -> 3.2 us.
 struct RepackArray {
     const uint8_t* src;
     uint8_t* dst;
@@ -661,10 +671,11 @@ __device__ __forceinline__ void repack_word(const RepackArray& p, int rows, long
     *reinterpret_cast<T*>(p.dst + p.pd.at(row, b)) = x;
 }
 
+template <bool TWO>
 __global__ void __launch_bounds__(256)
 repack_kernel(const RepackArray values, const RepackArray meta, int rows, unsigned value_blocks)
 {
-    const bool second = blockIdx.x >= value_blocks;
+    const bool second = TWO && blockIdx.x >= value_blocks;
     const RepackArray& p = second ? meta : values;
     const long long id = (long long)(blockIdx.x - (second ? value_blocks : 0u)) * 256 + threadIdx.x;
     if (id >= p.words) return;
@@ -876,11 +887,11 @@ int launch_repack(const void* vals_in, const void* meta_in, int rows, int cols, 
     const RepackArray v = array(vals_in, vals_out, packed_values(cols, N, M, bits, layout_in), packed_values(cols, N, M, bits, layout_out));
     const RepackArray m = array(meta_in, meta_out, packed_meta(cols, N, M, layout_in), packed_meta(cols, N, M, layout_out));
     const long long bv = (v.words + 255) / 256, bm = (m.words + 255) / 256;
-    if (bv + bm < (1 << 24)) {                 // a launch holds fewer than 2^32 threads
-        hipLaunchKernelGGL(repack_kernel, dim3((unsigned)(bv + bm)), dim3(256), 0, st, v, m, rows, (unsigned)bv);
+    if (bm > 0 && bv + bm < (1 << 24)) {       // a launch holds fewer than 2^32 threads
+        hipLaunchKernelGGL(repack_kernel<true>, dim3((unsigned)(bv + bm)), dim3(256), 0, st, v, m, rows, (unsigned)bv);
     } else {
-        hipLaunchKernelGGL(repack_kernel, dim3((unsigned)bv), dim3(256), 0, st, v, m, rows, (unsigned)bv);
-        if (bm > 0) hipLaunchKernelGGL(repack_kernel, dim3((unsigned)bm), dim3(256), 0, st, m, m, rows, (unsigned)bm);
+        hipLaunchKernelGGL(repack_kernel<false>, dim3((unsigned)bv), dim3(256), 0, st, v, v, rows, (unsigned)bv);
+        if (bm > 0) hipLaunchKernelGGL(repack_kernel<false>, dim3((unsigned)bm), dim3(256), 0, st, m, m, rows, (unsigned)bm);
     }
     return launch_status();
 }

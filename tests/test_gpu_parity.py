@@ -210,6 +210,60 @@ def test_repack_between_the_layouts(N, M, bits):
         assert np.array_equal(v3.cpu().numpy(), vr) and np.array_equal(m3.cpu().numpy(), mr)
 
 
+class Guarded:
+    """A device byte array that begins `off` bytes into an aligned allocation, with marked bytes on both sides."""
+
+    def __init__(self, size, off, data=None):
+        self.buf = torch.full((off + size + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+        self.off, self.size, self.ptr = off, size, self.buf.data_ptr() + off
+        if data is not None and size:
+            self.buf[off:off + size] = torch.from_numpy(np.ascontiguousarray(data).view(np.uint8).reshape(-1)).to(DEV)
+
+    def read(self):
+        b = self.buf.cpu().numpy()
+        assert np.all(b[:self.off] == 0xA5) and np.all(b[self.off + self.size:] == 0xA5), "bytes beside the array touched"
+        return b[self.off:self.off + self.size]
+
+
+@pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 8, 4), (4, 4, 8), (4, 4, 4), (7, 8, 4), (3, 4, 8)])
+def test_repack_words_narrow_with_the_alignment_of_either_side(N, M, bits):
+    """Arrays at any byte address: the word of a thread is what both sides allow, 16 bytes down to one."""
+    rng = np.random.default_rng([N, M, bits, 45])
+    st = torch.cuda.current_stream().cuda_stream
+    for rows, cols in [(21, 128), (16, 384)]:
+        W = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)
+        vr, mr, _ = oracle.compress(W, N, M, bits)
+        vt, mt = oracle.to_tiled(vr, mr, cols, N, M, bits)
+        for src, dst in [(0, 0), (8, 0), (0, 8), (4, 0), (0, 4), (2, 0), (0, 2), (1, 0), (0, 1), (3, 5)]:
+            say("repack offsets", N, M, bits, rows, cols, src, dst)
+            for layout, (vi, mi), (vo, mo) in ((ROWS, (vr, mr), (vt, mt)), (TILED, (vt, mt), (vr, mr))):
+                a, b = Guarded(vi.size, src, vi), Guarded(mi.size, src, mi)
+                c, d = Guarded(vo.size, dst), Guarded(mo.size, dst)
+                rc = binding.raw().nm_repack(a.ptr, b.ptr, rows, cols, N, M, bits, layout, c.ptr, d.ptr, st)
+                torch.cuda.synchronize()
+                assert rc == 0 and np.array_equal(c.read(), vo.reshape(-1)) and np.array_equal(d.read(), mo.reshape(-1))
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_decompress_to_and_from_any_address(layout):
+    """Whole dwords where the output allows them, else bytes; packed arrays at odd addresses."""
+    rng = np.random.default_rng(6)
+    st = torch.cuda.current_stream().cuda_stream
+    for N, M, bits in ALL_SCHEMES + [(3, 8, 8), (5, 8, 4), (6, 8, 4), (7, 8, 8)]:
+        rows, cols = 19, 128 if layout == TILED else 11 * M        # (row layout: odd numbers of entries, half-filled last bytes)
+        W = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)
+        vals, meta, _ = oracle.compress(W, N, M, bits)
+        want = oracle.decompress(vals, meta, rows, cols, N, M, bits)
+        if layout == TILED:
+            vals, meta = oracle.to_tiled(vals, meta, cols, N, M, bits)
+        for src, dst in [(0, 0), (0, 4), (0, 1), (0, 2), (3, 0), (1, 3)]:
+            say("decompress offsets", N, M, bits, layout, src, dst)
+            v, m, out = Guarded(vals.size, src, vals), Guarded(meta.size, src, meta), Guarded(rows * cols, dst)
+            rc = binding.raw().nm_decompress_i8(v.ptr, m.ptr, rows, cols, N, M, bits, layout, out.ptr, st)
+            torch.cuda.synchronize()
+            assert rc == 0 and np.array_equal(out.read().view(np.int8).reshape(rows, cols), want), (N, M, bits, src, dst)
+
+
 # ---- GEMM, small shapes spanning several tiles with ragged edges ------------------------------
 
 def small_case(N, M, bits, T, K, O, seed, with_bias=True):
