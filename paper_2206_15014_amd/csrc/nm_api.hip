@@ -45,6 +45,11 @@ int nm_test_force_gemm_tile(int cfg) { return g_forced_tile.exchange(cfg, std::m
 
 int nm_bench_last_gemm_tile(void) { return g_last_tile.load(std::memory_order_relaxed); }
 
+int nm_test_gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)
+{
+    return nm::gemm_any_launches(tokens, O, tiles, most_workgroups);
+}
+
 int nm_bench_smfmac_probe(int blocks, int iters, unsigned long long* counters_dev, void* hip_stream)
 {
     if (!counters_dev) return NM_ERR_NULL;

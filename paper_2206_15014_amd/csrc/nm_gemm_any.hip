@@ -28,6 +28,22 @@ namespace nm {
 
 namespace {
 
+// A launch holds fewer than 2^32 threads: more tiles than this go in several, none of which can be too large, so a
+// call is enqueued whole.  (Tiles are numbered in 32 bits: 2^31 of them would have outputs that no memory holds.)
+constexpr long long ANY_LAUNCH_TILES = 1 << 23;
+constexpr unsigned any_workgroups(long long tiles) { return (unsigned)(8 * ((tiles + 7) / 8)); }
+static_assert((unsigned long long)any_workgroups(ANY_LAUNCH_TILES) * 256 < (1ull << 32), "threads of a launch");
+
+struct AnyPlan { int side; long long tiles_o, tiles; };        // of side x side outputs
+AnyPlan any_plan(int tokens, int O)
+{
+    const long long big = ((tokens + 63ll) / 64) * ((O + 63ll) / 64);
+    // Fewer than two 64 x 64 tiles per CU leave it short of wavefronts to cover the latency of a chunk.
+    const int side = big < 512 ? 32 : 64;
+    const long long tiles_o = (O - 1ll + side) / side;
+    return AnyPlan{side, tiles_o, ((tokens - 1ll + side) / side) * tiles_o};
+}
+
 constexpr int KC = 256;                        // columns per chunk
 constexpr int ROW = KC + 16;                   // LDS bytes per row: 16-byte reads of 8 consecutive rows cover all banks once
 constexpr int CROW = KC / 2 + 16;              // the same for rows of sparse-MFMA codes (16 bytes per 32 columns) ...
@@ -147,7 +163,7 @@ struct PackedUnit {
 
 template <int N, int M, int BITS, int BT, int BO>
 __global__ void __launch_bounds__(256)
-gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const int vec)
+gemm_any_kernel(const GemmArgs a, const int tiles_o, const int first_tile, const int n_tiles, const int vec)
 {
     constexpr int FT = BT / 32, FO = BO / 32;          // 16x16 fragments per wavefront along each side (2 x 2 wavefronts)
     constexpr int XCH = BT * (KC / 16) / 256;          // 16-byte pieces of X per thread and chunk
@@ -160,8 +176,9 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
 
     // each XCD (workgroups are dealt to the eight in turn) takes a contiguous run of tiles
     const int per_xcd = (n_tiles + 7) >> 3;
-    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= n_tiles) return;                       // whole workgroup leaves before any barrier
+    const int place = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (place >= n_tiles) return;                      // whole workgroup leaves before any barrier
+    const int tile = first_tile + place;
     const int t0 = (tile / tiles_o) * BT, o0 = (tile % tiles_o) * BO;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wt = wave & 1, wo = wave >> 1;
@@ -178,8 +195,8 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
     auto load = [&](int k0, Chunk& r) __attribute__((always_inline)) {
         if (k0 >= a.K) return;                         // this and all conditions below: uniform
         const bool whole = k0 + KC <= a.K;
-        const bool x_whole = whole || (t0 + BT < a.tokens && a.ldx >= 16);     // (a piece may run into the next row)
-        const bool w_whole = whole || (o0 + BO < a.O && a.K >= 32);
+        const bool x_whole = whole || (t0 < a.tokens - BT && a.ldx >= 16);     // (a piece may run into the next row)
+        const bool w_whole = whole || (o0 < a.O - BO && a.K >= 32);
 #pragma unroll
         for (int i = 0; i < XCH; ++i) {
             const int c = tid + 256 * i;
@@ -341,37 +358,25 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int n_tiles, const in
     if (a.out_dtype == 3) absmax_commit(m, s_out, a.absmax);
 }
 
-template <int N, int M, int BITS, int BT, int BO>
-void launch_any_tile(const GemmArgs& a, long long tiles_t, long long tiles_o, bool vec, hipStream_t st)
+template <int N, int M, int BITS, int B>
+void launch_any_tile(const GemmArgs& a, bool vec, hipStream_t st)
 {
-    const long long n = tiles_t * tiles_o;
-    hipLaunchKernelGGL((gemm_any_kernel<N, M, BITS, BT, BO>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(256), 0, st, a, (int)tiles_o, (int)n,
-                       vec ? 1 : 0);
+    const AnyPlan plan = any_plan(a.tokens, a.O);
+    for (long long first = 0; first < plan.tiles; first += ANY_LAUNCH_TILES) {
+        const int n = (int)(plan.tiles - first < ANY_LAUNCH_TILES ? plan.tiles - first : ANY_LAUNCH_TILES);
+        hipLaunchKernelGGL((gemm_any_kernel<N, M, BITS, B, B>), dim3(any_workgroups(n)), dim3(256), 0, st, a, (int)plan.tiles_o, (int)first, n,
+                           vec ? 1 : 0);
+    }
 }
 
 template <int N, int M, int BITS>
-void launch_any(const GemmArgs& a_in, hipStream_t st)
+void launch_any(const GemmArgs& a, hipStream_t st)
 {
-    GemmArgs a = a_in;
-    // a launch holds fewer than 2^32 threads: beyond 2^28 tokens (2^22 tiles of 64 along them) one per range
-    constexpr int MOST = 1 << 28;
-    if (a.tokens > MOST) {
-        GemmArgs rest = a;
-        const size_t esize = a.out_dtype == 1 ? 4 : a.out_dtype == 2 ? 2 : 1;
-        rest.tokens -= MOST;
-        rest.X += (size_t)MOST * a.ldx;
-        if (a.acc) rest.acc += (size_t)MOST * a.ldo;
-        if (a.out) rest.out = reinterpret_cast<uint8_t*>(a.out) + (size_t)MOST * a.ldo * esize;
-        a.tokens = MOST;
-        launch_any<N, M, BITS>(rest, st);
-    }
     // Stores of four outputs at a time need rows of whole groups of four, all of them aligned.
     const bool vec = a.O % 4 == 0 && a.ldo % 4 == 0 && (uintptr_t)a.scales % 16 == 0 && (uintptr_t)a.bias % 16 == 0 &&
                      (uintptr_t)a.acc % 16 == 0 && (uintptr_t)a.out % 16 == 0;
-    const long long big = ((a.tokens + 63ll) / 64) * ((a.O + 63ll) / 64);
-    // Fewer than two 64 x 64 tiles per CU leave it short of wavefronts to cover the latency of a chunk.
-    if (big < 512) launch_any_tile<N, M, BITS, 32, 32>(a, (a.tokens + 31ll) / 32, (a.O + 31ll) / 32, vec, st);
-    else launch_any_tile<N, M, BITS, 64, 64>(a, (a.tokens + 63ll) / 64, (a.O + 63ll) / 64, vec, st);
+    if (any_plan(a.tokens, a.O).side == 32) launch_any_tile<N, M, BITS, 32>(a, vec, st);
+    else launch_any_tile<N, M, BITS, 64>(a, vec, st);
 }
 
 }  // namespace
@@ -383,6 +388,14 @@ void launch_gemm_any(const GemmArgs& a, hipStream_t st)
     NM_CASE(1, 4); NM_CASE(2, 4); NM_CASE(3, 4); NM_CASE(4, 4);
     NM_CASE(1, 8); NM_CASE(2, 8); NM_CASE(3, 8); NM_CASE(4, 8); NM_CASE(5, 8); NM_CASE(6, 8); NM_CASE(7, 8);
 #undef NM_CASE
+}
+
+int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)
+{
+    const AnyPlan plan = any_plan(tokens, O);
+    *tiles = plan.tiles;
+    *most_workgroups = any_workgroups(plan.tiles < ANY_LAUNCH_TILES ? plan.tiles : ANY_LAUNCH_TILES);
+    return (int)((plan.tiles + ANY_LAUNCH_TILES - 1) / ANY_LAUNCH_TILES);
 }
 
 }  // namespace nm

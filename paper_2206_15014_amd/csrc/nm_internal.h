@@ -160,6 +160,8 @@ int launch_smfmac_probe(int blocks, int iters, unsigned long long* counters, hip
 int launch_gemm(const GemmArgs& a, hipStream_t st);
 // Every call the sparse-MFMA kernels do not take (nm_gemm_any.hip); part of launch_gemm's bracket.
 void launch_gemm_any(const GemmArgs& a, hipStream_t st);
+// How it divides a call (for the tests): launches, output tiles, workgroups of the largest launch.
+int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups);
 // `count` (1 .. GEMM_BATCH_MAX) GEMMs of one pattern, layout and output type: one launch where the
 // LDS-direct kernels cover every item, else one launch per item.
 int launch_gemm_batch(const GemmArgs* items, int count, hipStream_t st);

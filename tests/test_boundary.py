@@ -192,3 +192,14 @@ def test_gemm_batch_validates_before_launch():
     assert call([item()], bits=5) == -4
     assert call([item()], layout=9) == -8
     assert call([item()], layout=1) == -3                        # tiled layout needs K % 128 == 0
+
+
+@pytest.mark.parametrize("tokens,O", [(1, 1), (31, 3), (1 << 28, 193), (1 << 28, 64), ((1 << 31) - 1, 1), (1, (1 << 31) - 1), (1 << 24, 5000)])
+def test_odd_shape_gemm_never_launches_too_many_threads(tokens, O):
+    """nm_gemm on the kernel of the odd shapes: every launch has fewer than 2^32 threads, so a call cannot fail with
+    part of it enqueued, and the launches cover the tiles."""
+    tiles, most = ctypes.c_longlong(0), ctypes.c_uint(0)
+    n = binding.raw().nm_test_gemm_any_launches(tokens, O, ctypes.byref(tiles), ctypes.byref(most))
+    side = 32 if -(-tokens // 64) * -(-O // 64) < 512 else 64
+    assert tiles.value == -(-tokens // side) * -(-O // side)
+    assert 0 < most.value * 256 < 1 << 32 and n * most.value >= tiles.value > (n - 1) * (1 << 23)
