@@ -14,10 +14,11 @@
 // last bytes are read in guarded pieces, so no byte past its end is touched.  X is zero beyond K in
 // LDS, which makes the columns of a partial chunk contribute nothing, whatever the weights' bytes there.
 //
-// Against one thread per output walking the metadata, which this kernel replaces: the 16 layers of a
-// 312-wide encoder (F = 1200, 2:4 int8) at 1999 tokens 23.08 ms -> 0.106 ms a pass (0.139 with dense
-// rows in LDS, one chunk in flight and the bytes of a row's last unit loaded one after the other); eight layers of
-// BERT-base at 3001 tokens with a 3-output layer behind them (K = 768, 31 tokens) 293.6 -> 112.0 us.
+// Outputs of very short rows, and of one to a few columns on many tokens, are computed by a thread each, walking the
+// metadata (thread_per_output says when).  Against that, which took every call before: the 16 layers of a
+// 312-wide encoder (F = 1200, 2:4 int8) at 1999 tokens 23.08 ms -> 0.106 ms a pass (0.139 with dense rows in LDS, one
+// chunk in flight and the bytes of a row's last unit loaded one after the other); eight layers of BERT-base at 3001
+// tokens with a 3-output layer behind them (K = 768, 31 tokens) 293.6 -> 112.0 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,7 +57,7 @@ struct PackedUnit {
     static constexpr int VB = U::VBYTES, MB = U::MBYTES;
     uint32_t v[U::VD], m[U::MD];
 
-    // UB bytes from byte `at` on of an array of `bytes` bytes; past its end, anything.
+    // UB bytes from byte `at` on of an array of `bytes` bytes, at least UB (the launcher sees to it); past its end, anything.
     template <int UB, int WORDS>
     static __device__ __forceinline__ void read_inside(const uint8_t* base, size_t at, uint32_t (&dst)[WORDS])
     {
@@ -68,15 +69,6 @@ struct PackedUnit {
     {
 #pragma unroll
         for (int w = 0; w < WORDS; ++w) dst[w] = 0u;
-        if (bytes < UB) {                      // uniform; an array of a few bytes
-#pragma unroll 1
-            for (int b = 0; b < UB; ++b) {
-                const uint32_t x = (uint32_t)base[at + b < bytes ? at + b : bytes - 1] << (8 * (b % 4));
-#pragma unroll
-                for (int w = 0; w < WORDS; ++w) dst[w] |= b / 4 == w ? x : 0u;
-            }
-            return;
-        }
         // the array's last UB bytes at the most, moved down by as many as they begin too early
         const size_t from = at + UB <= bytes ? at : bytes - UB;
         const int d = (int)(at - from);
@@ -358,6 +350,87 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int first_tile, const
     if (a.out_dtype == 3) absmax_commit(m, s_out, a.absmax);
 }
 
+// The smallest reductions: one thread per output, walking the metadata.  See thread_per_output.
+__global__ void __launch_bounds__(256)
+gemm_thread_kernel(const GemmArgs a, const long long first)
+{
+    const long long id_raw = first + (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long total = (long long)a.tokens * a.O;
+    const bool live = id_raw < total;          // threads past the end recompute the last output and store nothing
+    const long long id = live ? id_raw : total - 1;
+    const int t = (int)(id / a.O), o = (int)(id % a.O);
+    const int ib = (a.N >= a.M) ? 0 : (a.M == 4) ? 2 : 4;
+    const int kc = a.K / a.M * a.N;
+    const int8_t* x = a.X + (size_t)t * a.ldx;
+    int sum = 0;
+    for (int e = 0; e < kc; ++e) {
+        int q, off;
+        if (a.bits == 8) q = (int8_t)a.vals[a.pv.at((uint32_t)o, (uint32_t)e)];
+        else { int nib = (a.vals[a.pv.at((uint32_t)o, (uint32_t)e >> 1)] >> ((e & 1) * 4)) & 15; q = (nib ^ 8) - 8; }
+        if (ib == 0) off = e % a.N;
+        else if (ib == 2) off = (a.meta[a.pm.at((uint32_t)o, (uint32_t)e >> 2)] >> ((e & 3) * 2)) & 3;
+        else off = (a.meta[a.pm.at((uint32_t)o, (uint32_t)e >> 1)] >> ((e & 1) * 4)) & 15;
+        sum += (int)x[(e / a.N) * a.M + off] * q;
+    }
+    const size_t at = (size_t)t * a.ldo + o;
+    const float s_act = act_scale_of(a);
+    if (a.out_dtype == 3) {                    // requantised output: every lane takes part in the reduction of max |y|
+        const float s_out = out_scale_of(a);
+        float g[4] = {0.f, 0.f, 0.f, 0.f}, h[4] = {0.f, 0.f, 0.f, 0.f};
+        requant_column(s_act, a.scales[o], a.bias ? a.bias[o] : 0.0f, s_out, g[0], h[0]);
+        float m = 0.0f;
+        const uint32_t q = requant4(v4i{sum, 0, 0, 0}, g, h, m);
+        if (live) reinterpret_cast<uint8_t*>(a.out)[at] = (uint8_t)q;
+        absmax_commit(m, s_out, a.absmax);
+        return;
+    }
+    if (!live) return;
+    if (a.acc) a.acc[at] = sum;
+    if (a.out_dtype != 0) {
+        float y = (float)sum * (s_act * a.scales[o]) + (a.bias ? a.bias[o] : 0.0f);
+        if (a.out_dtype == 1) reinterpret_cast<float*>(a.out)[at] = y;
+        else reinterpret_cast<uint16_t*>(a.out)[at] = (uint16_t)pack_bf16x2(y, 0.0f);
+    }
+}
+
+// Stores of four outputs at a time need rows of whole groups of four, all of them aligned.
+bool whole_groups_of_four(const GemmArgs& a)
+{
+    return a.O % 4 == 0 && a.ldo % 4 == 0 && (uintptr_t)a.scales % 16 == 0 && (uintptr_t)a.bias % 16 == 0 &&
+           (uintptr_t)a.acc % 16 == 0 && (uintptr_t)a.out % 16 == 0;
+}
+
+// Whether a thread per output is done sooner than tiles, from a duration model of both (microseconds, fitted to 2462 calls
+// of 1 to 1000000 tokens, 1 to 1200 outputs and 1 to 40 kept entries a row; captured, operands in the caches).  A thread
+// walks its row's kept entries one after the other: 0.27 us each (dense, without offsets, 0.2), and 1.65 us per million of
+// them over the chip.  A tile costs its latency whatever it holds, and one of few columns is mostly padding.  So threads
+// win on the shortest rows (2:8 int8, K = 8, 128 x 3: 2.8 us against 3.7; 2:4 int8, K = 8, 300 x 700 4.7 against 3.5) and on
+// many tokens of a few outputs (2:4 int8, K = 24, 1000000 x 1: 22 against 74; 7:8 int8, K = 16: 24 against 152).
+bool thread_per_output(const GemmArgs& a, bool vec)
+{
+    if ((long long)a.K * a.O < 32) return true;                                    // packed arrays shorter than a unit, which tiles do not read
+    const double kept = (double)(a.K / a.M) * a.N, outputs = (double)a.tokens * a.O;
+    if (kept > 128) return false;
+    double thread = 2.15 + (a.N == a.M ? 0.2 : 0.27) * kept + 1.65e-6 * outputs * kept;
+    double tile, more;                                                             // one round; each further 64 x 64 tile
+    if (vec || a.O <= 16) {
+        tile = a.O <= 2 ? 3.25 : !vec ? 3.5 : a.tokens < 16 ? 3.0 : 3.2;
+        more = vec || a.O <= 4 ? 0.0048 : 0.0063;
+    } else {                                                                       // single values stored side by side
+        if (a.O > 64 && outputs > 1e6) return false;
+        tile = (a.tokens < 16 ? 3.4 : a.tokens < 128 ? 3.75 : 4.1) + 4.2e-6 * outputs;
+        more = 0.0015;
+        thread += 2.6e-6 * outputs;
+    }
+    if (a.N >= 3 && a.N < a.M) {                                                   // the costlier expansions
+        const bool costly = a.M == 4 || a.N != 4;
+        tile += a.M == 4 ? (a.O <= 2 ? 0.55 : 0.2) : costly ? 0.7 : 0.1;
+        more *= costly ? (a.M == 4 ? 1.45 : 2.0) : 1.15;
+    }
+    const double tiles = (double)((a.tokens - 1ll + 64) / 64) * (double)((a.O - 1ll + 64) / 64);
+    return thread < tile + more * (tiles > 256.0 ? tiles - 256.0 : 0.0);
+}
+
 template <int N, int M, int BITS, int B>
 void launch_any_tile(const GemmArgs& a, bool vec, hipStream_t st)
 {
@@ -372,9 +445,7 @@ void launch_any_tile(const GemmArgs& a, bool vec, hipStream_t st)
 template <int N, int M, int BITS>
 void launch_any(const GemmArgs& a, hipStream_t st)
 {
-    // Stores of four outputs at a time need rows of whole groups of four, all of them aligned.
-    const bool vec = a.O % 4 == 0 && a.ldo % 4 == 0 && (uintptr_t)a.scales % 16 == 0 && (uintptr_t)a.bias % 16 == 0 &&
-                     (uintptr_t)a.acc % 16 == 0 && (uintptr_t)a.out % 16 == 0;
+    const bool vec = whole_groups_of_four(a);
     if (any_plan(a.tokens, a.O).side == 32) launch_any_tile<N, M, BITS, 32>(a, vec, st);
     else launch_any_tile<N, M, BITS, 64>(a, vec, st);
 }
@@ -383,6 +454,12 @@ void launch_any(const GemmArgs& a, hipStream_t st)
 
 void launch_gemm_any(const GemmArgs& a, hipStream_t st)
 {
+    if (thread_per_output(a, whole_groups_of_four(a))) {
+        const long long outputs = (long long)a.tokens * a.O, most = 1ll << 31;     // a launch holds fewer than 2^32 threads
+        for (long long first = 0; first < outputs; first += most)
+            hipLaunchKernelGGL(gemm_thread_kernel, dim3((unsigned)(((outputs - first < most ? outputs - first : most) + 255) / 256)), dim3(256), 0, st, a, first);
+        return;
+    }
 #define NM_CASE(n, m) \
     if (a.N == n && a.M == m) return a.bits == 8 ? launch_any<n, m, 8>(a, st) : launch_any<n, m, 4>(a, st)
     NM_CASE(1, 4); NM_CASE(2, 4); NM_CASE(3, 4); NM_CASE(4, 4);

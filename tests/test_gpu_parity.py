@@ -511,6 +511,7 @@ def test_gemm_any_shape_alignment_and_pattern(N, M, bits, T, K, O, ldx, x_off, l
     (33, 40, 34, 40),                      # the last row's last unit begins just before the array's end
     (65, 776, 65, 784),                    # four chunks, ragged last tiles
     (32, 272, 32, 272),                    # one whole tile, which is also the last
+    (200001, 24, 1, 24), (40000, 32, 2, 32), (300, 16, 129, 16),      # a thread per output, or tiles: many tokens, short rows
 ])
 def test_gemm_any_ends_of_its_buffers(N, M, bits, T, K, O, ldx):
     """Loads at the ends of the packed arrays and of X, which are taken apart or moved."""
