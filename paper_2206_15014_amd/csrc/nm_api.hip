@@ -50,6 +50,13 @@ int nm_test_gemm_any_launches(int tokens, int O, long long* tiles, unsigned* mos
     return nm::gemm_any_launches(tokens, O, tiles, most_workgroups);
 }
 
+int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits)
+{
+    nm::GemmArgs a = {};
+    a.tokens = tokens; a.K = K; a.O = O; a.N = N; a.M = M; a.bits = bits;
+    return nm::few_tile(&a, 1);
+}
+
 int nm_bench_smfmac_probe(int blocks, int iters, unsigned long long* counters_dev, void* hip_stream)
 {
     if (!counters_dev) return NM_ERR_NULL;

@@ -293,8 +293,6 @@ typedef bool GemmSet(const GemmArgs* items, int count, hipStream_t st, int cfg);
 GemmSet NM_SETS(launch_gemm_dma_set);
 GemmSet NM_SETS(launch_gemm_few_set);
 
-namespace {
-
 // The tile for a launch: the smallest of 16 x 16, 16 x 32, 32 x 32, 32 x 64 (tokens x outputs; ids 141,
 // 143, 142, 144) of which the CUs take all workgroups at once, 0 when there is none.  Smaller tiles pull
 // the weights in through more CUs, and a second round costs more than a larger tile does (2:4 int8, 128
@@ -318,13 +316,11 @@ int few_tile(const GemmArgs* items, int count)
     for (const Shape& s : shapes) {
         if (K < s.least_k[work]) continue;
         long long n = 0;
-        for (int i = 0; i < count; ++i) n += ((items[i].tokens + s.t - 1ll) / s.t) * ((items[i].O + s.o - 1ll) / s.o);
+        for (int i = 0; i < count; ++i) n += ((items[i].tokens - 1ll + s.t) / s.t) * ((items[i].O - 1ll + s.o) / s.o);
         if (n <= 256) return s.cfg;
     }
     return 0;
 }
-
-}  // namespace
 
 bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {

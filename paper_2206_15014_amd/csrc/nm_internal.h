@@ -169,6 +169,9 @@ int launch_gemm_batch(const GemmArgs* items, int count, hipStream_t st);
 // tile choice, otherwise a forced variant; false: not handled, nothing launched.
 bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg);
 
+// Tile id of the few-token kernels for a launch, 0 where they are not the choice (host arithmetic only).
+int few_tile(const GemmArgs* items, int count);
+
 // Tile variant forced by the tests (0 = automatic), see nm_test_hooks.h.
 int forced_gemm_tile();
 // Records which kernel variant the last nm_gemm / nm_gemm_q8 / nm_gemm_batch call launched (the tile ids

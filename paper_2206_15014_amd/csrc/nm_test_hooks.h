@@ -40,6 +40,12 @@ int nm_bench_last_gemm_tile(void);
  * launch.  Host arithmetic only.
  */
 int nm_test_gemm_any_launches(int tokens, int O, long long *tiles, unsigned *most_workgroups);
+
+/*
+ * Test hook: the tile id of the few-token kernels that nm_gemm would choose for one call in the
+ * tiled layout, 0 where it would choose another family.  Host arithmetic only.
+ */
+int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits);
 #ifdef __cplusplus
 }
 #endif

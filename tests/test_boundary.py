@@ -203,3 +203,12 @@ def test_odd_shape_gemm_never_launches_too_many_threads(tokens, O):
     side = 32 if -(-tokens // 64) * -(-O // 64) < 512 else 64
     assert tiles.value == -(-tokens // side) * -(-O // side)
     assert 0 < most.value * 256 < 1 << 32 and n * most.value >= tiles.value > (n - 1) * (1 << 23)
+
+
+@pytest.mark.parametrize("tokens,K,O,N,M,bits,tile", [
+    (128, 768, 768, 2, 4, 8, 143), (1, 128, 4, 2, 4, 8, 141), (256, 768, 2304, 2, 4, 8, 0),
+    (512, 512, 768, 2, 4, 8, 0), (512, 640, 768, 2, 4, 8, 144), (512, 256, 768, 4, 4, 8, 144), (64, 128, 3072, 1, 4, 4, 0),
+    ((1 << 31) - 1, 4096, 4, 2, 4, 8, 0), (1, 4096, (1 << 31) - 4, 2, 4, 8, 0), ((1 << 31) - 33, 128, 16, 2, 4, 8, 0),
+])
+def test_few_token_tile_choice_up_to_the_largest_sizes(tokens, K, O, N, M, bits, tile):
+    assert binding.raw().nm_test_few_tile(tokens, K, O, N, M, bits) == tile
