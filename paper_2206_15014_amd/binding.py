@@ -128,10 +128,14 @@ def _ptr(t) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # The current stream's handle without the Stream object around it: 0.3 us instead of 3.1 us, a
-        # third of a whole nm_gemm call from Python (9.1 -> 6.2 us), which bounds the small layers.
+        # third of a whole nm_gemm call from Python (9.1 -> 6.2 us), which bounds the small layers.  The two
+        # names are private to torch: a version without them goes by the Stream object.
         cuda, c = _cuda
         if cuda.is_initialized():
-            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+            try:
+                return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+            except AttributeError:
+                pass
         return cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

@@ -212,3 +212,14 @@ def test_odd_shape_gemm_never_launches_too_many_threads(tokens, O):
 ])
 def test_few_token_tile_choice_up_to_the_largest_sizes(tokens, K, O, N, M, bits, tile):
     assert binding.raw().nm_test_few_tile(tokens, K, O, N, M, bits) == tile
+
+
+def test_current_stream_without_torchs_private_names(monkeypatch):
+    """A torch version that lacks the raw-handle functions: the handle of the current Stream object."""
+    import types
+    cuda = types.SimpleNamespace(is_initialized=lambda: True, current_stream=lambda: types.SimpleNamespace(cuda_stream=4321))
+    monkeypatch.setattr(binding, "_cuda", (cuda, types.SimpleNamespace()))
+    assert binding._stream(None) == 4321
+    monkeypatch.setattr(binding, "_cuda", (cuda, types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: 1000 + d)))
+    assert binding._stream(None) == 1003
+    assert binding._stream(77) == 77 and binding._stream(types.SimpleNamespace(cuda_stream=5)) == 5
