@@ -218,6 +218,16 @@ int gemm_args(nm::GemmArgs& a, const int8_t* X_dev, int tokens, int K, int ldx, 
 
 }  // namespace
 
+int nm_test_gemm_any_reads(int tokens, int K, int ldx, int O, int N, int M, int bits, int layout, size_t* x_end, size_t* v_end, size_t* m_end)
+{
+    nm::GemmArgs a = {};
+    static const int8_t some[4] = {};
+    static const float one = 1.0f;
+    const int rc = gemm_args(a, some, tokens, K, ldx, 1.0f, nullptr, some, some, &one, O, N, M, bits, layout, nullptr, O);
+    if (rc) return rc;
+    return nm::gemm_any_reads(a, x_end, v_end, m_end) ? 1 : 0;
+}
+
 int nm_gemm(const int8_t* X_dev, int tokens, int K, int ldx, float act_scale, const float* act_scale_dev,
             const void* vals_dev, const void* meta_dev, const float* scales_dev,
             int O, int N, int M, int bits, int layout,

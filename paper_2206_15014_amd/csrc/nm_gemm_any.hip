@@ -50,6 +50,20 @@ constexpr int ROW = KC + 16;                   // LDS bytes per row: 16-byte rea
 constexpr int CROW = KC / 2 + 16;              // the same for rows of sparse-MFMA codes (16 bytes per 32 columns) ...
 constexpr int PROW = KC / 8 + 4;               // ... and of their positions (4 bytes per 32 columns)
 
+// Where a chunk's loads go; the kernel and the check of its bounds on the host share these.  What a chunk loads past
+// column K is dropped (X, in stage) or meets zeros of X (weights), so addresses are clamped to what the buffers hold and
+// no load waits behind a branch of its lanes: pieces of X past K become the row's last columns, units past K the row's
+// last unit.  Only a piece or unit that begins before a buffer's end and would reach past it is taken apart: the last
+// token's, the last output row's.
+__host__ __device__ inline int least(int a, int b) { return a < b ? a : b; }
+__host__ __device__ inline bool x_whole(const GemmArgs& a, int t0, int side, int k0) { return k0 + KC <= a.K || (t0 < a.tokens - side && a.ldx >= 16); }      // (a piece may run into the next row)
+__host__ __device__ inline bool w_whole(const GemmArgs& a, int o0, int side, int k0) { return k0 + KC <= a.K || (o0 < a.O - side && a.K >= 32); }
+__host__ __device__ inline int x_row(const GemmArgs& a, int t0, int piece) { return least(t0 + piece / (KC / 16), a.tokens - 1); }
+__host__ __device__ inline int x_column(const GemmArgs& a, int k) { return least(k, a.K - 4); }
+__host__ __device__ inline int w_row(const GemmArgs& a, int o0, int unit) { return least(o0 + unit / (KC / 32), a.O - 1); }
+__host__ __device__ inline int w_unit(const GemmArgs& a, int k0, int unit) { return least(k0 / 32 + unit % (KC / 32), (a.K - 1) / 32); }
+__host__ __device__ inline size_t w_at_end(size_t at, size_t bytes, int unit_bytes) { return at + unit_bytes <= bytes ? at : bytes - unit_bytes; }
+
 // The packed bytes of 32 consecutive columns of one weight row, and their expansion to 32 dense codes.
 template <int N, int M, int BITS>
 struct PackedUnit {
@@ -70,7 +84,7 @@ struct PackedUnit {
 #pragma unroll
         for (int w = 0; w < WORDS; ++w) dst[w] = 0u;
         // the array's last UB bytes at the most, moved down by as many as they begin too early
-        const size_t from = at + UB <= bytes ? at : bytes - UB;
+        const size_t from = w_at_end(at, bytes, UB);
         const int d = (int)(at - from);
         __builtin_memcpy(dst, base + from, UB);
 #pragma unroll
@@ -180,27 +194,21 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int first_tile, const
         v4i x[XCH];
         PackedUnit<N, M, BITS> w[WUN];
     };
-    // What a chunk loads past column K is dropped (X, in stage) or meets zeros of X (weights), so addresses are
-    // clamped to what the buffers hold and no load waits behind a branch of its lanes: pieces of X past K become
-    // the row's last columns, units past K the row's last unit.  Only a piece or unit that begins before
-    // a buffer's end and would reach past it is taken apart: the last token's, the last output row's.
     auto load = [&](int k0, Chunk& r) __attribute__((always_inline)) {
         if (k0 >= a.K) return;                         // this and all conditions below: uniform
-        const bool whole = k0 + KC <= a.K;
-        const bool x_whole = whole || (t0 < a.tokens - BT && a.ldx >= 16);     // (a piece may run into the next row)
-        const bool w_whole = whole || (o0 < a.O - BO && a.K >= 32);
+        const bool xw = x_whole(a, t0, BT, k0), ww = w_whole(a, o0, BO, k0);
 #pragma unroll
         for (int i = 0; i < XCH; ++i) {
             const int c = tid + 256 * i;
-            const int8_t* row = a.X + (size_t)min(t0 + c / (KC / 16), a.tokens - 1) * a.ldx;
+            const int8_t* row = a.X + (size_t)x_row(a, t0, c) * a.ldx;
             const int k = k0 + (c % (KC / 16)) * 16;
-            if (x_whole) {
-                __builtin_memcpy(&r.x[i], row + min(k, a.K - 4), 16);          // (k < K: k is K - 4 at most)
+            if (xw) {
+                __builtin_memcpy(&r.x[i], row + x_column(a, k), 16);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     int w;
-                    __builtin_memcpy(&w, row + min(k + 4 * j, a.K - 4), 4);
+                    __builtin_memcpy(&w, row + x_column(a, k + 4 * j), 4);
                     r.x[i][j] = w;
                 }
             }
@@ -208,9 +216,9 @@ gemm_any_kernel(const GemmArgs a, const int tiles_o, const int first_tile, const
 #pragma unroll
         for (int i = 0; i < WUN; ++i) {
             const int u = tid + 256 * i;
-            const int row = min(o0 + u / (KC / 32), a.O - 1), unit = min(k0 / 32 + u % (KC / 32), (a.K - 1) / 32);
+            const int row = w_row(a, o0, u), unit = w_unit(a, k0, u);
             if (a.pv.tiled) r.w[i].load_tiled(a, row, unit);
-            else if (w_whole) r.w[i].template load_rows<false>(a, row, unit);
+            else if (ww) r.w[i].template load_rows<false>(a, row, unit);
             else r.w[i].template load_rows<true>(a, row, unit);
         }
     };
@@ -465,6 +473,35 @@ void launch_gemm_any(const GemmArgs& a, hipStream_t st)
     NM_CASE(1, 4); NM_CASE(2, 4); NM_CASE(3, 4); NM_CASE(4, 4);
     NM_CASE(1, 8); NM_CASE(2, 8); NM_CASE(3, 8); NM_CASE(4, 8); NM_CASE(5, 8); NM_CASE(6, 8); NM_CASE(7, 8);
 #undef NM_CASE
+}
+
+bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_end)
+{
+    if (thread_per_output(a, false)) return false;
+    const AnyPlan plan = any_plan(a.tokens, a.O);
+    const int side = plan.side;
+    auto reach = [](size_t* end, size_t at, size_t bytes) { if (bytes && at + bytes > *end) *end = at + bytes; };
+    auto unit_reach = [&](const PackedArray& p, size_t* end, int row, int unit, bool whole) {
+        const size_t at = (size_t)row * p.stride + (size_t)unit * p.ub;
+        if (p.ub == 0) return;
+        if (p.tiled) reach(end, tiled_offset(row, unit * p.ub + p.ub - 1, p.ub, p.slices), 1);
+        else reach(end, whole ? at : w_at_end(at, (size_t)a.O * p.stride, (int)p.ub), p.ub);
+    };
+    *x_end = *v_end = *m_end = 0;
+    for (long long tile = 0; tile < plan.tiles; ++tile) {
+        const int t0 = (int)(tile / plan.tiles_o) * side, o0 = (int)(tile % plan.tiles_o) * side;
+        for (int k0 = 0; k0 < a.K; k0 += KC) {
+            const bool xw = x_whole(a, t0, side, k0), ww = w_whole(a, o0, side, k0);
+            for (int c = 0; c < side * (KC / 16); ++c)
+                for (int j = 0; j < (xw ? 1 : 4); ++j)
+                    reach(x_end, (size_t)x_row(a, t0, c) * a.ldx + x_column(a, k0 + (c % (KC / 16)) * 16 + 4 * j), xw ? 16 : 4);
+            for (int u = 0; u < side * (KC / 32); ++u) {
+                unit_reach(a.pv, v_end, w_row(a, o0, u), w_unit(a, k0, u), ww);
+                unit_reach(a.pm, m_end, w_row(a, o0, u), w_unit(a, k0, u), ww);
+            }
+        }
+    }
+    return true;
 }
 
 int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)

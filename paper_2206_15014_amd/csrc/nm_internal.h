@@ -162,6 +162,8 @@ int launch_gemm(const GemmArgs& a, hipStream_t st);
 void launch_gemm_any(const GemmArgs& a, hipStream_t st);
 // How it divides a call (for the tests): launches, output tiles, workgroups of the largest launch.
 int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups);
+// Ends of the bytes its tiles read of X, vals and meta; false: no tiles, a thread per output.
+bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_end);
 // `count` (1 .. GEMM_BATCH_MAX) GEMMs of one pattern, layout and output type: one launch where the
 // LDS-direct kernels cover every item, else one launch per item.
 int launch_gemm_batch(const GemmArgs* items, int count, hipStream_t st);

@@ -7,6 +7,7 @@
  */
 #ifndef NM_TEST_HOOKS_H
 #define NM_TEST_HOOKS_H
+#include <stddef.h>
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -46,6 +47,14 @@ int nm_test_gemm_any_launches(int tokens, int O, long long *tiles, unsigned *mos
  * tiled layout, 0 where it would choose another family.  Host arithmetic only.
  */
 int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits);
+
+/*
+ * Test hook: walks every load that the tiles of the kernel of the odd shapes would make for a call
+ * and gives the ends of the bytes read (offsets of the last byte + 1) of X, vals and meta.  Returns 1,
+ * 0 where the call would not go on tiles, or a negative status.  Host arithmetic only.
+ */
+int nm_test_gemm_any_reads(int tokens, int K, int ldx, int O, int N, int M, int bits, int layout,
+                           size_t *x_end, size_t *v_end, size_t *m_end);
 #ifdef __cplusplus
 }
 #endif

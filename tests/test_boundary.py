@@ -223,3 +223,28 @@ def test_current_stream_without_torchs_private_names(monkeypatch):
     monkeypatch.setattr(binding, "_cuda", (cuda, types.SimpleNamespace(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda d: 1000 + d)))
     assert binding._stream(None) == 1003
     assert binding._stream(77) == 77 and binding._stream(types.SimpleNamespace(cuda_stream=5)) == 5
+
+
+@pytest.mark.parametrize("N,M,bits", [(2, 4, 8), (1, 4, 4), (3, 4, 4), (4, 4, 8), (4, 4, 4), (1, 8, 4), (2, 8, 8), (4, 8, 4), (7, 8, 8), (7, 8, 4)])
+def test_odd_shape_gemm_reads_only_what_its_buffers_hold(N, M, bits):
+    """Every load address of the tiles, walked on the host by the functions the kernel uses, against buffers that end with
+    the last byte a call may touch: ragged tiles, chunks and units, rows shorter than a load, padded and unpadded X."""
+    raw, ends = binding.raw(), [ctypes.c_size_t(0) for _ in range(3)]
+    seen = 0
+    for layout in (nm.NM_LAYOUT_ROWS, nm.NM_LAYOUT_TILED):
+        for K in (M, 2 * M, 24, 32, 40, 128, 248, 256, 264, 384, 520, 776):
+            if layout == nm.NM_LAYOUT_TILED and K % 128:
+                continue
+            for O in (1, 2, 3, 31, 32, 33, 64, 65, 700):
+                v, m, _ = nm.nm_packed_sizes(O, K, N, M, bits, layout)
+                for tokens in (1, 2, 31, 32, 33, 63, 65, 70, 3300 if O == 700 and K <= 40 else 5):
+                    for ldx in (K, K + 1, K + 20):
+                        rc = raw.nm_test_gemm_any_reads(tokens, K, ldx, O, N, M, bits, layout, *[ctypes.byref(e) for e in ends])
+                        assert rc >= 0
+                        if rc == 0:
+                            continue
+                        seen += 1
+                        x, vv, mm = (e.value for e in ends)
+                        assert x <= (tokens - 1) * ldx + K and vv <= v and mm <= m, (layout, tokens, K, ldx, O, x, vv, mm)
+                        assert x >= (tokens - 1) * ldx + K and vv == v or layout == nm.NM_LAYOUT_TILED      # and all of it
+    assert seen > 1000

@@ -483,8 +483,9 @@ def test_gemm_generic_path_odd_shapes(N, M, bits, layout):
     (1285, 256, 1601, 256, 0, 1601, 0),
 ])
 def test_gemm_any_shape_alignment_and_pattern(N, M, bits, T, K, O, ldx, x_off, ldo, out_off):
-    """The kernel of the odd shapes at the edges of its chunks and tiles, on buffers at any byte address
-    that end with the last byte the call may touch."""
+    """The kernels of the odd shapes at the edges of chunks and tiles, on buffers at any byte address; output padding stays as
+    it was.  (The allocator rounds sizes up, so a read past a buffer's end does not show here; the loads' addresses are
+    walked on the host in test_boundary.py.)"""
     say("gemm any", N, M, bits, "T", T, "K", K, "O", O, "ldx", ldx, x_off, "ldo", ldo, out_off)
     W, Xq, sx, bias, ref, acc_ref = small_case(N, M, bits, T, K, O, 31)
     vals, meta, scales = gpu_compress(W, N, M, bits)
