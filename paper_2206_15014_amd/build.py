@@ -9,10 +9,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnm.so")
-# (source, extra flags, object name).  The tiled-layout GEMM kernels, through an LDS ring and of few tokens, are
-# one source each, compiled once per set of N:M patterns, so that their many instantiations build in parallel.
+# (source, extra flags, object name).  The LDS-direct GEMM kernels are one source compiled once per
+# set of N:M patterns, so that their many instantiations build in parallel.
 DMA_SETS = 11
-SOURCES = [("nm_gemm_%s.hip" % s, ["-DNM_DMA_SET=%d" % k], "nm_gemm_%s_%d.o" % (s, k)) for s in ("dma", "few") for k in range(DMA_SETS)] + \
+SOURCES = [("nm_gemm_dma.hip", ["-DNM_DMA_SET=%d" % k], "nm_gemm_dma_%d.o" % k) for k in range(DMA_SETS)] + \
           [(s, [], s.replace(".hip", ".o")) for s in ["nm_api.hip", "nm_compress.hip", "nm_gemm.hip", "nm_gemm_any.hip", "nm_project.hip", "nm_quantize_act.hip", "nm_scale_search.hip"]]
 
 HIPCC_FLAGS = [

@@ -599,10 +599,20 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
     }
 }
 
+// Where a ring kernel's code lies shows in its time.  It is 59 to 145 KB long, as much as two CUs' shared instruction cache
+// of 64 KB holds or more, so its place decides what its fetches meet: the same instructions at other offsets of the
+// code object, or in an object that the loader put elsewhere, were up to 8 % faster or slower where kernels follow one
+// another (one library loaded eight times, the same buffers: int8 chain at 12288 tokens 112 to 122 us).  So ring kernels
+// start at whole kilobytes, in front of everything else in their object.  BERT-large block at 49152 tokens, int8 chain at
+// 12288, BERT-base layers at 3001 tokens, us a pass on one box: the few-token kernels in front, 256 bytes 585, 106, 111; in
+// an object of their own 585, 114, 110; behind, 1 KB 582, 106, 110; 2 KB 582, 108, 109; 4 KB 580, 107, 108; of their own, 4
+// KB 580, 108, 108.
+#define NM_RING_ALIGNED __attribute__((aligned(1024)))
+
 // One GEMM per launch.  Workgroup -> tile: each XCD (workgroups are dealt to the eight XCDs in
 // turn) takes a contiguous run of tiles, so that the CUs behind one L2 share token rows.
 template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU>
-__global__ void __launch_bounds__(64 * WAVES_T * WAVES_O, STAGES == 2 ? 2 : 1)
+__global__ NM_RING_ALIGNED void __launch_bounds__(64 * WAVES_T * WAVES_O, STAGES == 2 ? 2 : 1)
 gemm_dma_kernel(const GemmArgs a_in, const int tiles_o, const int n_tiles)
 {
     GemmArgs a = a_in;
@@ -617,7 +627,7 @@ gemm_dma_kernel(const GemmArgs a_in, const int tiles_o, const int n_tiles)
 // to - a second, dependent round trip to the argument memory before the first loads, which a
 // launch of one GEMM does without (it costs that launch 0.1 to 0.5 us), hence a kernel of its own.
 template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU>
-__global__ void __launch_bounds__(64 * WAVES_T * WAVES_O, STAGES == 2 ? 2 : 1)
+__global__ NM_RING_ALIGNED void __launch_bounds__(64 * WAVES_T * WAVES_O, STAGES == 2 ? 2 : 1)
 gemm_dma_batch_kernel(const GemmBatch p)
 {
     const int n_tiles = p.first_tile[p.count];
@@ -872,3 +882,5 @@ bool NM_SET_NAME(launch_gemm_dma_set)(const GemmArgs* items, int count, hipStrea
 }
 
 }  // namespace nm
+
+#include "nm_gemm_few.h"

@@ -16,14 +16,10 @@
 // 512 tokens 1024 -> 1024 5.08 -> 3.93.  Dense int8, which had no small tile: 1 token 4096 -> 1024
 // 15.40 -> 3.77, 128 tokens 768 -> 768 5.95 -> 3.00.
 //
-// These kernels are translation units of their own, and so code objects of their own.  In one code object with the
-// ring kernels of nm_gemm_dma.hip (in front of them: 48 KB) those, the same instructions at other offsets, ran slower
-// where one kernel follows another: the four layers of a BERT-large block at 49152 tokens 617 -> 622 to 627 us a
-// pass, back at 617 with the code objects apart.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+// Included behind the ring kernels of nm_gemm_dma.hip, not in front of them: see there.
+#ifndef NM_GEMM_FEW_H
+#define NM_GEMM_FEW_H
 
-#include "nm_internal.h"
 #include "nm_gemm_common.h"
 #include "nm_gemm_sets.h"
 
@@ -234,3 +230,5 @@ bool NM_SET_NAME(launch_gemm_few_set)(const GemmArgs* items, int count, hipStrea
 }
 
 }  // namespace nm
+
+#endif
