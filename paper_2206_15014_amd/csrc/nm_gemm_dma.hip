@@ -604,7 +604,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
 // code object, or in an object that the loader put elsewhere, were up to 8 % faster or slower where kernels follow one
 // another (one library loaded eight times, the same buffers: int8 chain at 12288 tokens 112 to 122 us).  So ring kernels
 // start at whole kilobytes, in front of everything else in their object.  BERT-large block at 49152 tokens, int8 chain at
-// 12288, BERT-base layers at 3001 tokens, us a pass on one box: the few-token kernels in front, 256 bytes 585, 106, 111; in
+// 12288, BERT-base layers at 3001 tokens, us a pass on one GPU: the few-token kernels in front, 256 bytes 585, 106, 111; in
 // an object of their own 585, 114, 110; behind, 1 KB 582, 106, 110; 2 KB 582, 108, 109; 4 KB 580, 107, 108; of their own, 4
 // KB 580, 108, 108.
 #define NM_RING_ALIGNED __attribute__((aligned(1024)))
