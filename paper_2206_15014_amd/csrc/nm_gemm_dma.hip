@@ -107,14 +107,14 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
     uint32_t voff[PER_WAVE];                   // this lane's byte offset from sbase[p], at the next stage to issue
     const uint8_t* sbase[PER_WAVE];
     uint32_t stepb[PER_WAVE];                  // bytes per stage along the source row
-    // With several rounds of tiles per CU, workgroups walk K in rotated order (stage j of this
-    // workgroup is K block (kstart + j) mod ns; integer sums do not care), so that workgroups
-    // sharing rows of X do not all miss on the same lines at the same moment (8-9 % on the
-    // 12288- to 49152-token layer sets).  With a single round every workgroup starts at the same
-    // instant on inputs that no L2 holds yet, and rotated starts would ask the memory for all of X
-    // and W at once, the first stages queueing behind everybody's later ones: there all start at
-    // block 0 (3.5-4.5 % on the 4096-token layer sets).
-    const int kstart = a.k_rotate ? (int)(((unsigned)tile * 7u) % (unsigned)ns) : 0;
+    // Workgroups walk K in rotated order: stage j of this workgroup is K block (kstart + j) mod ns (integer sums do
+    // not care).  The tiles of one token row (consecutive workgroups of an XCD) start a.k_rotate blocks apart, the
+    // first one in the lead, so that what the leader has fetched is in the XCD's L2 when the others come to it:
+    // started together they all miss on the same lines at once, started far apart the L2 has lost the lines by then
+    // (eight token tiles of 256 x 4096 are twice its size).  With a CU to itself a tile also starts one block on from the
+    // token row before it, which spreads the reads of the packed weights; two-stage tiles do without (the int8 chain at
+    // 12288 tokens 111 us with it, 109 without).
+    const int kstart = (int)(((STAGES > 2 ? (unsigned)(tile / tiles_o) : 0u) + (unsigned)(ns - 1) * (unsigned)a.k_rotate * (unsigned)(tile % tiles_o)) % (unsigned)ns);
     const int rb_last = (a.O + 15) / 16 - 1;   // last row block of the packed arrays
     const uint32_t lds_mine = (uint32_t)(uintptr_t)smem + (uint32_t)wave_u * 1024u;
 #pragma unroll
@@ -603,11 +603,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
 // of 64 KB holds or more, so its place decides what its fetches meet: the same instructions at other offsets of the
 // code object, or in an object that the loader put elsewhere, were up to 8 % faster or slower where kernels follow one
 // another (one library loaded eight times, the same buffers: int8 chain at 12288 tokens 112 to 122 us).  So ring kernels
-// start at whole kilobytes, in front of everything else in their object.  BERT-large block at 49152 tokens, int8 chain at
-// 12288, BERT-base layers at 3001 tokens, us a pass on one GPU: the few-token kernels in front, 256 bytes 585, 106, 111; in
-// an object of their own 585, 114, 110; behind, 1 KB 582, 106, 110; 2 KB 582, 108, 109; 4 KB 580, 107, 108; of their own, 4
-// KB 580, 108, 108.
-#define NM_RING_ALIGNED __attribute__((aligned(1024)))
+// start at multiples of 4 KB, in front of everything else in their object.  BERT-large block at 49152 tokens, int8 chain at
+// 12288, BERT-base layers at 3001 tokens, us a pass on one GPU, each library alone in a process: 1 KB 513, 109 to 111, 100;
+// 2 KB 514, 111, 100; 4 KB 512, 107, 99; 8 KB 514, 108, 99; 16 KB 513, 108, 100; 64 KB 514, 106, 99.
+#define NM_RING_ALIGNED __attribute__((aligned(4096)))
 
 // One GEMM per launch.  Workgroup -> tile: each XCD (workgroups are dealt to the eight XCDs in
 // turn) takes a contiguous run of tiles, so that the CUs behind one L2 share token rows.
@@ -677,9 +676,18 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
     // (measured at 4096 tokens: equal at 12.6 MB, 17 % faster at 18.9 MB, slower below), int8
     // codes from 8 MB (9.4 MB: 11.4 -> 10.4 us, 12.6 MB: 12.5 -> 11.8 us, 50 MB: 56.9 -> 52.9 us);
     // fp32 always is, in the kernel.
+    // K blocks between the starts of neighbouring column tiles (see the kernel).  Against starts 7 tiles apart with
+    // more than 256 tiles and none with fewer, us, operands in the last-level cache / in HBM, [tile]:
+    //   one block, several rounds of tiles on CUs of their own: 49152 x 4096 -> 1024 200 -> 123 / 189 -> 130 [256 x 256]
+    //   (two blocks the same), 49152 x 1024 -> 4096 188 -> 177 / 186 -> 180 (two: 189 / 188);
+    //   two blocks, two-stage rings: 49152 x 1024 -> 1024 60 -> 49 / 58 -> 49 [128 x 256] (one: 59 / 58), 24576 x 4096 ->
+    //   1024 98 -> 85 / 99 -> 83 (one: 88 / 86), 4096 x 768 -> 2304 10.4 -> 10.2 / 11.6 -> 10.6 [128 x 192] (one: the same);
+    //   two blocks, one round: 4096 x 3072 -> 768 11.8 -> 11.9 / 15.4 -> 13.6 [128 x 96] (one: 11.7 / 14.5), 3001 x 3072 -> 768
+    //   11.0 -> 11.3 / 15.0 -> 12.4, 4096 x 768 -> 768 6.3 -> 6.4 / 7.5 -> 7.0; the worst, 8192 x 3072 -> 768, 16.8 -> 18.3 / 23.6 -> 21.8
+    //   [256 x 96] (one: 17.8 / 22.5).  Operands that the L2s themselves hold: no difference.
     for (int i = 0; i < count; ++i) {
         b.item[i].store_through = out_bytes >= ((items[0].out_dtype == 3 ? 8ll : 14ll) << 20);
-        b.item[i].k_rotate = n_tiles > 256;     // more tiles than CUs: see the kernel
+        b.item[i].k_rotate = n_tiles > 256 && STAGES > 2 ? 1 : 2;
     }
     if constexpr (BATCHABLE) {
         if (count > 1) {

@@ -88,7 +88,7 @@ struct GemmArgs {
     int out_dtype;         // nm_out_dtype; 3 = int8 codes (nm_gemm_q8)
     int ldo;
     int store_through;     // set by a launcher: output stores bypass the L2's write-back (large outputs)
-    int k_rotate;          // set by a launcher: workgroups start their walk along K at different blocks
+    int k_rotate;          // set by a launcher: K blocks between the starts of neighbouring column tiles
     float out_scale;       // out_dtype 3: scale of the output codes
     const float* out_scale_dev;   // replaces out_scale when given
     float* absmax;         // out_dtype 3: max |y| is max-combined into it, or null
