@@ -33,6 +33,7 @@ class GemmItem(ctypes.Structure):
 
 _lib = None
 _cuda = None          # (torch.cuda, torch._C), bound with the library
+_native = None        # the marshalling of the hot calls in C (csrc/nm_python.c); without it they go through ctypes
 
 
 class NMError(RuntimeError):
@@ -46,7 +47,7 @@ def library_path() -> str:
 
 
 def _load():
-    global _lib, _cuda
+    global _lib, _cuda, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -104,6 +105,13 @@ def _load():
     lib.nm_bench_smfmac_probe.argtypes = [c_int, c_int, c_vp, c_vp]
     lib.nm_status_string.restype = ctypes.c_char_p
     lib.nm_status_string.argtypes = [c_int]
+    try:
+        from . import _nm_python
+    except ImportError:       # not built for this interpreter
+        _native = None
+    else:
+        _nm_python.bind(ctypes.cast(lib.nm_gemm, ctypes.c_void_p).value)
+        _native = _nm_python
     _lib = lib
     return lib
 
@@ -282,16 +290,27 @@ def nm_gemm(X, act_scale: float, vals, meta, scales, O: int, N: int, M: int, bit
             stream=None, layout: int = NM_LAYOUT_ROWS, act_scale_dev=None):
     """X: int8 CUDA tensor [tokens, K].  acc (int32) and out (float32 / bfloat16), when
     given, are [tokens, ldo] buffers written in place; returns (acc, out)."""
+    lib = _lib or _load()
+    rc = None
+    if _native is not None:
+        rc = _native.gemm(X, act_scale, vals, meta, scales, O, N, M, bits, bias, acc, out, out_dtype, ldo, _stream(stream), layout, act_scale_dev)
+        if rc == 0:
+            return acc, out
+    if rc is None:
+        rc = _gemm_ctypes(lib, X, act_scale, vals, meta, scales, O, N, M, bits, bias, acc, out, out_dtype, ldo, stream, layout, act_scale_dev)
+    if rc:
+        raise NMError(rc, "nm_gemm")
+    return acc, out
+
+
+def _gemm_ctypes(lib, X, act_scale, vals, meta, scales, O, N, M, bits, bias, acc, out, out_dtype, ldo, stream, layout, act_scale_dev):
     tokens, K = X.shape
     if ldo is None:
         ref = out if out is not None else acc
         ldo = ref.stride(0) if ref is not None and hasattr(ref, "stride") else O
-    rc = _load().nm_gemm(_ptr(X), tokens, K, X.stride(0), float(act_scale), _ptr(act_scale_dev),
-                         _ptr(vals), _ptr(meta), _ptr(scales), O, N, M, bits, layout,
-                         _ptr(bias), _ptr(acc), _ptr(out), out_dtype, ldo, _stream(stream))
-    if rc:
-        raise NMError(rc, "nm_gemm")
-    return acc, out
+    return lib.nm_gemm(_ptr(X), tokens, K, X.stride(0), float(act_scale), _ptr(act_scale_dev),
+                       _ptr(vals), _ptr(meta), _ptr(scales), O, N, M, bits, layout,
+                       _ptr(bias), _ptr(acc), _ptr(out), out_dtype, ldo, _stream(stream))
 
 
 def gemm_items(calls):

@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnm.so")
+PYTHON_MODULE = os.path.join(HERE, "_nm_python.so")      # argument marshalling of the binding's hot calls
 # (source, extra flags, object name).  The LDS-direct GEMM kernels are one source compiled once per
 # set of N:M patterns, so that their many instantiations build in parallel.
 DMA_SETS = 11
@@ -53,6 +55,9 @@ def build(verbose: bool = False) -> str:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
         os.replace(tmp, LIB)
+        _run([hipcc, "-x", "c", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+              os.path.join(CSRC, "nm_python.c"), "-o", tmp], verbose)
+        os.replace(tmp, PYTHON_MODULE)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
         if os.path.exists(tmp):
