@@ -236,6 +236,39 @@ __device__ __forceinline__ void store_packed(uint8_t* __restrict__ base, int til
     }
 }
 
+// One group of a row: encoded, its bits joined with the neighbouring lanes', the dwords stored.  Every lane of the wavefront
+// calls it; groups past the row's end, and rows with !store, write nothing, rows with !live zeros.
+template <int N, int M, int BITS>
+struct RowWork {
+    static constexpr bool HAS_META = N < M;       // a dense matrix stores no index bits
+    static constexpr int IB = (M == 4) ? 2 : 4;
+    static constexpr int VB = N * BITS;           // value bits per group
+    static constexpr int MB = HAS_META ? N * IB : 32;   // index bits per group
+    static constexpr int VL = 32 / VB;            // lanes per value dword
+    static constexpr int ML = 32 / MB;            // lanes per index dword
+    static constexpr int UV = 32 / M * N * BITS / 8;    // packed value / index bytes per 32 input columns
+    static constexpr int UM = HAS_META ? 32 / M * N * IB / 8 : 4;
+
+    template <bool RECIP>
+    static __device__ __forceinline__ void emit(const float (&grp)[M], int g, int groups, const Divisor<RECIP>& divisor, uint32_t* vals, uint32_t* meta,
+                                                int tiled, int row, bool live, bool store, int vstride_dw, int mstride_dw, uint32_t slices)
+    {
+        const int lane = threadIdx.x & 63;
+        uint8_t* __restrict__ vbase = reinterpret_cast<uint8_t*>(vals);
+        uint8_t* __restrict__ mbase = reinterpret_cast<uint8_t*>(meta);
+        uint32_t vb = 0, mb = 0;
+        if (g < groups) encode_group<N, M, BITS>(grp, divisor, vb, mb);
+        vb = group_or<VL>(vb << ((lane % VL) * VB));
+        if (store && g < groups && lane % VL == 0)
+            store_packed<UV>(vbase, tiled, (uint32_t)row, (uint32_t)g / VL, (uint32_t)vstride_dw, slices, live ? vb : 0u);
+        if constexpr (HAS_META) {
+            mb = group_or<ML>(mb << ((lane % ML) * MB));
+            if (store && g < groups && lane % ML == 0)
+                store_packed<UM>(mbase, tiled, (uint32_t)row, (uint32_t)g / ML, (uint32_t)mstride_dw, slices, live ? mb : 0u);
+        }
+    }
+};
+
 // The rows of one workgroup: `block` is the workgroup's index among those of this matrix, WPR
 // (1, 2 or 4) a compile-time constant in the single-matrix kernel and a per-matrix value in the
 // batched one (uniform over the workgroup, so the barrier below is too).
@@ -247,14 +280,6 @@ compress_rows(const float* __restrict__ W, int rows, int cols, int ldw,
 {
     const bool given = (flags & GIVEN_SCALES) != 0;
     const int tiled = (flags & TILED_LAYOUT) ? 1 : 0;
-    constexpr bool HAS_META = N < M;       // a dense matrix stores no index bits
-    constexpr int IB = (M == 4) ? 2 : 4;
-    constexpr int VB = N * BITS;           // value bits per group
-    constexpr int MB = HAS_META ? N * IB : 32;   // index bits per group
-    constexpr int VL = 32 / VB;            // lanes per value dword
-    constexpr int ML = 32 / MB;            // lanes per index dword
-    constexpr int UV = 32 / M * N * BITS / 8;    // packed value / index bytes per 32 input columns
-    constexpr int UM = HAS_META ? 32 / M * N * IB / 8 : 4;
     constexpr int F4 = M / 4;              // 16-byte loads per group
     static_assert(RES * F4 <= 16, "at most 64 floats per lane stay in registers");
     const int RPB = 4 / WPR;               // rows per workgroup
@@ -320,21 +345,9 @@ compress_rows(const float* __restrict__ W, int rows, int cols, int ldw,
         (int)__float_as_uint(given ? scales[row] : ((amax == 0.0f) ? 1.0f : amax / QMAX))));
     if (!given && live && w == 0 && lane == 0) scales[row] = s;
 
-    uint8_t* __restrict__ vbase = reinterpret_cast<uint8_t*>(vals);
-    uint8_t* __restrict__ mbase = reinterpret_cast<uint8_t*>(meta);
-
     auto encode_row = [&](auto divisor) __attribute__((always_inline)) {
         auto emit = [&](const float (&grp)[M], int g) __attribute__((always_inline)) {
-            uint32_t vb = 0, mb = 0;
-            if (g < groups) encode_group<N, M, BITS>(grp, divisor, vb, mb);
-            vb = group_or<VL>(vb << ((lane % VL) * VB));
-            if (store && g < groups && lane % VL == 0)
-                store_packed<UV>(vbase, tiled, (uint32_t)row_raw, (uint32_t)g / VL, (uint32_t)vstride_dw, slices, live ? vb : 0u);
-            if constexpr (HAS_META) {
-                mb = group_or<ML>(mb << ((lane % ML) * MB));
-                if (store && g < groups && lane % ML == 0)
-                    store_packed<UM>(mbase, tiled, (uint32_t)row_raw, (uint32_t)g / ML, (uint32_t)mstride_dw, slices, live ? mb : 0u);
-            }
+            RowWork<N, M, BITS>::emit(grp, g, groups, divisor, vals, meta, tiled, row_raw, live, store, vstride_dw, mstride_dw, slices);
         };
         if (resident) {
 #pragma unroll
@@ -367,6 +380,88 @@ compress_rows(const float* __restrict__ W, int rows, int cols, int ldw,
     // in the range for which that route is exact; any other scale takes the division operator.
     if (s >= 0x1p-60f && s <= 0x1p60f) encode_row(Divisor<true>{s, __fdiv_rn(1.0f, s)});
     else encode_row(Divisor<false>{s, 0.0f});
+}
+
+// The same for two consecutive shares of a matrix by one workgroup (2 * block and the next), every row within the RES passes a
+// wavefront holds: the second share's weights are requested before the first one's are encoded, so a wavefront has loads in flight
+// while it encodes.
+template <int N, int M, int BITS, int RES>
+__device__ __forceinline__ void
+compress_rows_stream(const float* __restrict__ W, int rows, int cols, int ldw,
+                     uint32_t* __restrict__ vals, uint32_t* __restrict__ meta, float* __restrict__ scales,
+                     int vstride_dw, int mstride_dw, int tiled, const int WPR, const int block, float (*part)[4])
+{
+    using R = RowWork<N, M, BITS>;
+    constexpr int F4 = M / 4;
+    const int RPB = 4 / WPR;
+    constexpr float QMAX = (float)((1 << (BITS - 1)) - 1);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(wave % WPR);
+    const int groups = cols / M;
+    const int passes = (groups + 63) >> 6;
+    const int mine = (passes - w + WPR - 1) / WPR;
+    const int rows_out = tiled ? (rows + 15) & ~15 : rows;
+    const uint32_t slices = (uint32_t)cols >> 7;
+    const int first = __builtin_amdgcn_readfirstlane(block * 2 * RPB + wave / WPR);
+    if (block * 2 * RPB >= rows_out) return;               // the whole workgroup
+
+    auto request = [&](int row_raw, float4 (&x)[RES * F4]) __attribute__((always_inline)) {
+        const int row = min(row_raw, rows - 1);
+        const float4* __restrict__ w4 = reinterpret_cast<const float4*>(W + (size_t)row * ldw);
+#pragma unroll
+        for (int i = 0; i < RES; ++i) {
+            if (i < mine) {                    // the same in all lanes
+                const int g = min((w + i * WPR) * 64 + lane, groups - 1);    // (the last group again past the end)
+#pragma unroll
+                for (int f = 0; f < F4; ++f) x[i * F4 + f] = load_w<true>(w4 + (unsigned)(g * F4 + f));
+            } else {
+#pragma unroll
+                for (int f = 0; f < F4; ++f) x[i * F4 + f] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+    };
+    auto turn = [&](int row_raw, const float4 (&x)[RES * F4], float* mark) __attribute__((always_inline)) {
+        float amax = 0.0f;
+#pragma unroll
+        for (int i = 0; i < RES * F4; ++i) {
+            const float4 v = x[i];
+            amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+        }
+        amax = wave_max(amax);
+        if (WPR > 1) {
+            if (lane == 0) mark[wave] = amax;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+            const int base = (wave / WPR) * WPR;
+            amax = mark[base];
+            for (int k = 1; k < WPR; ++k) amax = fmaxf(amax, mark[base + k]);
+        }
+        const bool live = row_raw < rows;
+        const float s = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint((amax == 0.0f) ? 1.0f : amax / QMAX)));
+        if (live && w == 0 && lane == 0) scales[row_raw] = s;
+        auto encode = [&](auto divisor) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < RES; ++i) {
+                if (i < mine) {
+                    float grp[M];
+#pragma unroll
+                    for (int f = 0; f < F4; ++f) {
+                        const float4 v = x[i * F4 + f];
+                        grp[4 * f + 0] = v.x; grp[4 * f + 1] = v.y; grp[4 * f + 2] = v.z; grp[4 * f + 3] = v.w;
+                    }
+                    R::emit(grp, (w + i * WPR) * 64 + lane, groups, divisor, vals, meta, tiled, row_raw, live, row_raw < rows_out, vstride_dw, mstride_dw, slices);
+                }
+            }
+        };
+        if (s >= 0x1p-60f && s <= 0x1p60f) encode(Divisor<true>{s, __fdiv_rn(1.0f, s)});
+        else encode(Divisor<false>{s, 0.0f});
+    };
+    float4 xa[RES * F4], xb[RES * F4];
+    request(first, xa);
+    request(first + RPB, xb);
+    turn(first, xa, part[0]);
+    turn(first + RPB, xb, part[1]);
 }
 
 // Workgroup -> its share of the rows.  Consecutive workgroups of a launch go to different XCDs
@@ -402,32 +497,58 @@ struct BatchItem {
     float* scales;
     int rows, cols, ldw, vstride_dw, mstride_dw, wpr, first_block, blocks;
 };
+// CAP = the most matrices of one launch: 16, or 48 for calls of more (3.3 KB of arguments, which a small call would
+// feel: four BERT-base matrices 10.8 us with 16, 12.3 with 48).
+template <int CAP>
 struct BatchArgs {
-    // the table a workgroup searches for its item, one aligned 64-byte run at the front of the
-    // argument block so that it arrives in one scalar load; unused entries hold INT_MAX
-    int first_block[BATCH_MAX];
+    static constexpr int MOST = CAP;
+    // the table a workgroup searches for its item, at the front of the argument block in aligned 64-byte runs
+    // so that it arrives in few scalar loads; unused entries hold INT_MAX
+    int first_block[CAP];
     int count;
     int flags;             // of compress_rows
     int stream_loads;      // the weights are loaded with the streaming hint
-    BatchItem it[BATCH_MAX];
+    BatchItem it[CAP];
 };
+static_assert(sizeof(BatchArgs<48>) <= 4096, "a launch passes at most 4 KB of arguments");
 
-template <int N, int M, int BITS, int RES, bool ONCE>
-__global__ void __launch_bounds__(256)
-compress_batch_kernel(const BatchArgs b)
+// The item of this workgroup.  Two round trips to the argument memory before the first weights are asked for: the table,
+// then every field of the item at once (fetched where first used they were four to seven).
+template <int CAP>
+__device__ __forceinline__ BatchItem item_of_workgroup(const BatchArgs<CAP>& b)
 {
-    __shared__ float part[4];
-    // Two round trips to the argument memory before the first weights are asked for: the table,
-    // then every field of the item at once (fetched where first used they were four to seven).
     int i = 0;
 #pragma unroll
-    for (int k = 1; k < BATCH_MAX; ++k)
+    for (int k = 1; k < CAP; ++k)
         if ((int)blockIdx.x >= b.first_block[k]) i = k;        // uniform
     BatchItem t = b.it[i];
     asm volatile("" : "+s"(t.W), "+s"(t.vals), "+s"(t.meta), "+s"(t.scales), "+s"(t.rows), "+s"(t.cols), "+s"(t.ldw),
                       "+s"(t.vstride_dw), "+s"(t.mstride_dw), "+s"(t.wpr), "+s"(t.first_block), "+s"(t.blocks));
+    return t;
+}
+
+template <int N, int M, int BITS, int RES, bool ONCE>
+__global__ void __launch_bounds__(256)
+compress_batch_kernel(const BatchArgs<BATCH_MAX> b)
+{
+    __shared__ float part[4];
+    const BatchItem t = item_of_workgroup(b);
     compress_rows<N, M, BITS, RES, ONCE>(t.W, t.rows, t.cols, t.ldw, t.vals, t.meta, t.scales, t.vstride_dw, t.mstride_dw, b.flags,
                                    t.wpr, xcd_block((int)blockIdx.x - t.first_block, t.blocks, b.flags), part);
+}
+
+// A call of more than 16 matrices, a whole encoder's: up to 48 per launch and two shares of rows per workgroup.  Bound by HBM.
+// Against launches of 16 matrices with one share: the 96 matrices of BERT-large (1.2 GB) 290 -> 284 us (4.9 TB/s read and
+// written; a large copy reaches 5.2), the 48 of BERT-base 90 -> 84, 24 of them 48 -> 45, 64 of 512 x 512 to 2048 63 -> 56, 64 of 256 x 256
+// to 1024 28 -> 24.  One share 270 and 90 for the first two, four 281 and 84.
+template <int N, int M, int BITS, int RES>
+__global__ void __launch_bounds__(256)
+compress_stream_kernel(const BatchArgs<3 * BATCH_MAX> b)
+{
+    __shared__ float part[2][4];
+    const BatchItem t = item_of_workgroup(b);
+    compress_rows_stream<N, M, BITS, RES>(t.W, t.rows, t.cols, t.ldw, t.vals, t.meta, t.scales, t.vstride_dw, t.mstride_dw,
+                                          (b.flags & TILED_LAYOUT) ? 1 : 0, t.wpr, xcd_block((int)blockIdx.x - t.first_block, t.blocks, b.flags), part);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -798,7 +919,7 @@ int wave_wpr(int cols, int M)
 }
 
 template <int N, int M, int BITS, bool ONCE>
-void launch_batch_res(const BatchArgs& b, int max_mine, int blocks, hipStream_t st)
+void launch_batch_res(const BatchArgs<BATCH_MAX>& b, int max_mine, int blocks, hipStream_t st)
 {
     constexpr int MAXRES = 16 / (M / 4);
     const dim3 grid((unsigned)blocks), wg(256);
@@ -810,24 +931,38 @@ void launch_batch_res(const BatchArgs& b, int max_mine, int blocks, hipStream_t 
 }
 
 template <int N, int M, int BITS>
-void launch_batch(const BatchArgs& b, int max_mine, int blocks, hipStream_t st)
+void launch_batch(const BatchArgs<BATCH_MAX>& b, int max_mine, int blocks, hipStream_t st)
 {
     if (b.stream_loads) launch_batch_res<N, M, BITS, true>(b, max_mine, blocks, st);
     else launch_batch_res<N, M, BITS, false>(b, max_mine, blocks, st);
 }
 
-}  // namespace
+constexpr int STREAM_PASSES = 4;               // per wavefront, the most that compress_stream_kernel holds twice
+template <int N, int M, int BITS>
+void launch_batch(const BatchArgs<3 * BATCH_MAX>& b, int max_mine, int blocks, hipStream_t st)
+{
+    const dim3 grid((unsigned)blocks), wg(256);
+    if (max_mine <= 2) hipLaunchKernelGGL((compress_stream_kernel<N, M, BITS, 2>), grid, wg, 0, st, b);
+    else if (max_mine <= 3) hipLaunchKernelGGL((compress_stream_kernel<N, M, BITS, 3>), grid, wg, 0, st, b);
+    else hipLaunchKernelGGL((compress_stream_kernel<N, M, BITS, STREAM_PASSES>), grid, wg, 0, st, b);
+}
 
-// Matrices that the wavefront kernel takes (alignment, whole dwords per packed row) go out in
-// launches of up to BATCH_MAX; the others one by one through launch_compress.
-int launch_compress_batch(const CompressItem* items, int count, int N, int M, int bits, int layout, hipStream_t st)
+// passes of 64 groups of the wavefront with the most
+int most_passes(int cols, int M)
+{
+    const int wpr = wave_wpr(cols, M);
+    return ((cols / M + 63) / 64 + wpr - 1) / wpr;
+}
+
+// Matrices that the wavefront kernel takes (alignment, whole dwords per packed row) go out in launches of up to
+// Args::MOST, `shares` shares of rows per workgroup; the others one by one through launch_compress.
+template <typename Args>
+int launch_batches(const CompressItem* items, int count, int N, int M, int bits, int layout, int shares, int stream_loads, hipStream_t st)
 {
     begin_launch();
-    BatchArgs b;
+    Args b;
     b.count = 0;
-    long long bytes = 0;
-    for (int i = 0; i < count; ++i) bytes += (long long)items[i].rows * items[i].cols * 4;
-    b.stream_loads = bytes > STREAM_ABOVE_BYTES ? 1 : 0;
+    b.stream_loads = stream_loads;
     b.flags = layout ? TILED_LAYOUT : 0;
     int blocks = 0, max_mine = 0;
     auto flush = [&]() {
@@ -839,9 +974,9 @@ int launch_compress_batch(const CompressItem* items, int count, int N, int M, in
         NM_CASE(1, 8, 4); NM_CASE(2, 8, 4); NM_CASE(4, 8, 4);
 #undef NM_CASE
         b.count = 0; blocks = 0; max_mine = 0;
-        for (int k = 0; k < BATCH_MAX; ++k) b.first_block[k] = 0x7FFFFFFF;
+        for (int k = 0; k < Args::MOST; ++k) b.first_block[k] = 0x7FFFFFFF;
     };
-    for (int k = 0; k < BATCH_MAX; ++k) b.first_block[k] = 0x7FFFFFFF;
+    for (int k = 0; k < Args::MOST; ++k) b.first_block[k] = 0x7FFFFFFF;
     for (int i = 0; i < count; ++i) {
         const CompressItem& c = items[i];
         const PackedArray pv = packed_values(c.cols, N, M, bits, layout), pm = packed_meta(c.cols, N, M, layout);
@@ -851,22 +986,40 @@ int launch_compress_batch(const CompressItem* items, int count, int N, int M, in
             if (rc) return rc;
             continue;
         }
-        const int wpr = wave_wpr(c.cols, M);
-        const int passes = (c.cols / M + 63) / 64, mine = (passes + wpr - 1) / wpr, rpb = 4 / wpr;
+        const int wpr = wave_wpr(c.cols, M), mine = most_passes(c.cols, M), rows_per_block = 4 / wpr * shares;
+        const int rows_out = layout ? ((c.rows + 15) & ~15) : c.rows;     // the tiled layout pads the rows
+        long long own = ((long long)rows_out + rows_per_block - 1) / rows_per_block;
+        if (layout) own = (own + 7) & ~7ll;                               // whole rounds over the XCDs, see xcd_block
         BatchItem& t = b.it[b.count++];
         t.W = c.W; t.vals = (uint32_t*)c.vals; t.meta = (uint32_t*)c.meta; t.scales = c.scales;
         t.rows = c.rows; t.cols = c.cols; t.ldw = c.ldw; t.vstride_dw = (int)pv.stride / 4; t.mstride_dw = (int)pm.stride / 4;
         t.wpr = wpr; t.first_block = blocks;
         b.first_block[b.count - 1] = blocks;
-        const int rows_out = layout ? ((c.rows + 15) & ~15) : c.rows;     // the tiled layout pads the rows
-        t.blocks = (rows_out + rpb - 1) / rpb;
-        if (layout) t.blocks = (t.blocks + 7) & ~7;                       // whole rounds over the XCDs, see xcd_block
+        t.blocks = (int)own;
         blocks += t.blocks;
         max_mine = mine > max_mine ? mine : max_mine;
-        if (b.count == BATCH_MAX) flush();
+        if (b.count == Args::MOST) flush();
     }
     flush();
     return launch_status();
+}
+
+}  // namespace
+
+int launch_compress_batch(const CompressItem* items, int count, int N, int M, int bits, int layout, hipStream_t st)
+{
+    long long bytes = 0, most_blocks = 0;
+    int mine = 0;
+    for (int i = 0; i < count; ++i) {
+        bytes += (long long)items[i].rows * items[i].cols * 4;
+        most_blocks += items[i].rows / 2 + 24;
+        mine = most_passes(items[i].cols, M) > mine ? most_passes(items[i].cols, M) : mine;
+    }
+    const int stream_loads = bytes > STREAM_ABOVE_BYTES ? 1 : 0;
+    // (fewer launches hold more workgroups: of 256 threads, fewer than 2^24 a launch)
+    if (stream_loads && count > BATCH_MAX && mine <= STREAM_PASSES && most_blocks < (1 << 23))
+        return launch_batches<BatchArgs<3 * BATCH_MAX>>(items, count, N, M, bits, layout, 2, 1, st);
+    return launch_batches<BatchArgs<BATCH_MAX>>(items, count, N, M, bits, layout, 1, stream_loads, st);
 }
 
 int launch_repack(const void* vals_in, const void* meta_in, int rows, int cols, int N, int M, int bits, int layout_in,
