@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "nm_gemm_common.h"
 #include "nm_internal.h"
 #include "nm_quantize.h"
 
@@ -769,6 +770,46 @@ decompress_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ 
     }
 }
 
+// The same from the tiled layout, a thread per unit (32 columns of one row): whole pieces in, lane-contiguous, 32 bytes out, so
+// that a wavefront's 16 rows x 128 columns are read as one run and written as whole lines.  Needs 16-byte aligned arrays.
+// 3072 x 768, 2:4 int8 6.1 -> 3.0 us.
+template <int N, int M, int BITS>
+__global__ void __launch_bounds__(256)
+decompress_units_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int rows, int cols, uint32_t blocks, int8_t* __restrict__ Wq)
+{
+    using U = Unit<N, M, BITS>;
+    const uint32_t block = blockIdx.x * 4u + (threadIdx.x >> 6), slices = (uint32_t)cols >> 7;
+    if (block >= blocks) return;
+    const int lane = threadIdx.x & 63;
+    const uint32_t rb = block / slices, slice = block - rb * slices;
+    const int row = (int)(rb * 16u) + (lane & 15);
+    if (row >= rows) return;
+    const typename U::Raw r = U::load_tiled(vals + (size_t)block * (64u * U::VBYTES), meta + (size_t)block * (64u * U::MBYTES), lane);
+    uint32_t out[8];
+#pragma unroll
+    for (int g = 0; g < 32 / M; ++g) {
+        uint64_t o = 0;                        // byte c = column c of the group
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int e = g * N + j;
+            uint32_t q = BITS == 8 ? r.v[e / 4] >> (8 * (e % 4)) & 0xFFu : r.v[e / 8] >> (4 * (e % 8)) & 0xFu;
+            if constexpr (BITS == 4) q = ((q ^ 8u) - 8u) & 0xFFu;
+            if constexpr (U::IB == 0) {
+                o |= (uint64_t)q << (8 * j);
+            } else {
+                const uint32_t sh = 8u * (r.m[e * U::IB / 32] >> (e * U::IB % 32) & (uint32_t)(M - 1));
+                if constexpr (M == 4) o = (uint32_t)((uint32_t)o & ~(0xFFu << sh)) | (q << sh);
+                else o = (o & ~(0xFFull << sh)) | ((uint64_t)q << sh);
+            }
+        }
+        out[g * M / 4] = (uint32_t)o;
+        if constexpr (M == 8) out[g * 2 + 1] = (uint32_t)(o >> 32);
+    }
+    uint4* dst = reinterpret_cast<uint4*>(Wq + (size_t)row * cols + slice * 128u + (uint32_t)(lane >> 4) * 32u);
+    dst[0] = make_uint4(out[0], out[1], out[2], out[3]);
+    dst[1] = make_uint4(out[4], out[5], out[6], out[7]);
+}
+
 // The packed arrays from one layout to the other, `width` bytes per thread: the widest word that stays
 // within one piece of a unit in the tiled layout and is aligned on both sides (the launcher's choice, per
 // array).  Rows that only pad the tiled layout to a multiple of 16 are written as zeros.  Both arrays in
@@ -1056,6 +1097,19 @@ int launch_decompress(const void* vals, const void* meta, int rows, int cols, in
     begin_launch();
     const PackedArray pv = packed_values(cols, N, M, bits, layout), pm = packed_meta(cols, N, M, layout);
     const dim3 grid((unsigned)((total + 255) / 256));
+    const long long blocks = (long long)((rows + 15) / 16) * (cols / 128);
+    if (layout && ((uintptr_t)vals | (uintptr_t)meta | (uintptr_t)Wq) % 16 == 0 && blocks < (1 << 25)) {      // (a launch holds fewer than 2^32 threads)
+        const dim3 wgs((unsigned)((blocks + 3) / 4));
+#define NM_CASE(n, m) \
+        if (N == n && M == m) { \
+            if (bits == 8) hipLaunchKernelGGL((decompress_units_kernel<n, m, 8>), wgs, dim3(256), 0, st, (const uint8_t*)vals, (const uint8_t*)meta, rows, cols, (uint32_t)blocks, Wq); \
+            else hipLaunchKernelGGL((decompress_units_kernel<n, m, 4>), wgs, dim3(256), 0, st, (const uint8_t*)vals, (const uint8_t*)meta, rows, cols, (uint32_t)blocks, Wq); \
+        }
+        NM_CASE(1, 4) NM_CASE(2, 4) NM_CASE(3, 4) NM_CASE(4, 4)
+        NM_CASE(1, 8) NM_CASE(2, 8) NM_CASE(3, 8) NM_CASE(4, 8) NM_CASE(5, 8) NM_CASE(6, 8) NM_CASE(7, 8)
+#undef NM_CASE
+        return launch_status();
+    }
 #define NM_CASE(n, m) \
     if (N == n && M == m) { \
         if (bits == 8) hipLaunchKernelGGL((decompress_kernel<n, m, 8>), grid, dim3(256), 0, st, (const uint8_t*)vals, (const uint8_t*)meta, rows, cols, pv, pm, Wq); \
