@@ -324,6 +324,8 @@ int few_tile(const GemmArgs* items, int count)
 
 bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
+    for (int i = 0; i < count; ++i)            // (a reduction of 131072 kept 4-bit weights and more: gemm_any_kernel)
+        if (items[i].bits == 4 && (long long)items[i].K / items[i].M * items[i].N > SCALED_MOST_KEPT) return false;
     static GemmSet* const rings[] = {NM_SETS(launch_gemm_dma_set)};
     static GemmSet* const fews[] = {NM_SETS(launch_gemm_few_set)};
     const int few = cfg == 0 ? few_tile(items, count) : cfg >= 141 && cfg <= 144 ? cfg : 0;

@@ -28,6 +28,20 @@ __device__ __forceinline__ uint32_t sext4x4(uint32_t nib)
     return ((nib ^ 0x88888888u) - 0x08080808u) ^ 0x80808080u;
 }
 
+// The eight nibbles of a dword as bytes, even entries in `lo`, odd ones in `hi`: as they are (sign-extended, nine operations), or
+// SCALED, sixteen times as large (three: the nibble in a byte's upper half is the product itself).
+template <bool SCALED>
+__device__ __forceinline__ void nibbles(uint32_t x, uint32_t& lo, uint32_t& hi)
+{
+    if constexpr (SCALED) {
+        lo = (x << 4) & 0xF0F0F0F0u;
+        hi = x & 0xF0F0F0F0u;
+    } else {
+        lo = sext4x4(x & 0x0F0F0F0Fu);
+        hi = sext4x4((x >> 4) & 0x0F0F0F0Fu);
+    }
+}
+
 template <int N, int M, int BITS>
 struct Unit {
     static constexpr int IB = (N >= M) ? 0 : (M == 4) ? 2 : 4;
@@ -103,7 +117,9 @@ struct Unit {
         return r;
     }
 
-    // Packed unit -> MFMA operand: 16 int8 codes (zero where nothing is kept) and 16 2-bit positions.
+    // Packed unit -> MFMA operand: 16 int8 codes (zero where nothing is kept) and 16 2-bit positions.  SCALED: 4-bit codes
+    // times 16, so the products' sums are too, for a caller that undoes it (unscale).
+    template <bool SCALED = false>
     static __device__ __forceinline__ void decode(const Raw& r_in, v4i& codes, int& pos)
     {
         static_assert(!DUAL, "one operand holds at most two entries per subgroup of four");
@@ -120,12 +136,11 @@ struct Unit {
             if constexpr (BITS == 8) {
 #pragma unroll
                 for (int d = 0; d < EPU / 4; ++d) w[d] = r.v[d];
-            } else {
+            } else if constexpr (N == 2) {
 #pragma unroll
                 for (int d = 0; d < EPU / 8; ++d) {
-                    const uint32_t x = r.v[d];
-                    const uint32_t lo = sext4x4(x & 0x0F0F0F0Fu);          // entries 0, 2, 4, 6 of this dword
-                    const uint32_t hi = sext4x4((x >> 4) & 0x0F0F0F0Fu);   // entries 1, 3, 5, 7
+                    uint32_t lo, hi;
+                    nibbles<SCALED>(r.v[d], lo, hi);
                     w[2 * d] = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
                     w[2 * d + 1] = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
                 }
@@ -135,8 +150,15 @@ struct Unit {
                 pos = (int)r.m;
             } else {
                 // entry i -> byte 2i, zero in byte 2i+1; its 2 position bits -> bits 4i, 4i+1
-                codes = v4i{(int)__builtin_amdgcn_perm(0u, w[0], 0x0c010c00u), (int)__builtin_amdgcn_perm(0u, w[0], 0x0c030c02u),
-                            (int)__builtin_amdgcn_perm(0u, w[1], 0x0c010c00u), (int)__builtin_amdgcn_perm(0u, w[1], 0x0c030c02u)};
+                if constexpr (BITS == 8) {
+                    codes = v4i{(int)__builtin_amdgcn_perm(0u, w[0], 0x0c010c00u), (int)__builtin_amdgcn_perm(0u, w[0], 0x0c030c02u),
+                                (int)__builtin_amdgcn_perm(0u, w[1], 0x0c010c00u), (int)__builtin_amdgcn_perm(0u, w[1], 0x0c030c02u)};
+                } else {
+                    uint32_t lo, hi;                           // entry i: byte i / 2 of lo (i even) or hi
+                    nibbles<SCALED>(r.v[0], lo, hi);
+                    codes = v4i{(int)__builtin_amdgcn_perm(hi, lo, 0x0c040c00u), (int)__builtin_amdgcn_perm(hi, lo, 0x0c050c01u),
+                                (int)__builtin_amdgcn_perm(hi, lo, 0x0c060c02u), (int)__builtin_amdgcn_perm(hi, lo, 0x0c070c03u)};
+                }
                 uint32_t x = r.m & 0xFFFFu;
                 x = (x | (x << 8)) & 0x00FF00FFu;
                 x = (x | (x << 4)) & 0x0F0F0F0Fu;
@@ -153,9 +175,8 @@ struct Unit {
                 if constexpr (N == 2) w[1] = r.v[1];
                 else w[1] = 0u;
             } else {
-                const uint32_t x = r.v[0];
-                const uint32_t lo = sext4x4(x & 0x0F0F0F0Fu);
-                const uint32_t hi = sext4x4((x >> 4) & 0x0F0F0F0Fu);
+                uint32_t lo, hi;
+                nibbles<SCALED>(r.v[0], lo, hi);
                 w[0] = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
                 w[1] = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
             }
@@ -197,7 +218,7 @@ struct Unit {
                     q = (r.v[e / 4] >> (8 * (e % 4))) & 0xFFu;
                 } else {
                     uint32_t nib = (r.v[e / 8] >> (4 * (e % 8))) & 0xFu;
-                    q = ((nib ^ 8u) - 8u) & 0xFFu;                 // sign-extend 4 -> 8 bits
+                    q = SCALED ? nib << 4 : ((nib ^ 8u) - 8u) & 0xFFu;     // sign-extend 4 -> 8 bits
                 }
                 const uint32_t off = (r.m >> (e * IB)) & (uint32_t)(M - 1);
                 const int g = e / N, j = e % N;                    // group inside the unit, rank inside the group
@@ -221,10 +242,23 @@ struct Unit {
     // other against the same activations.  Of the (up to four) entries a subgroup keeps, operand
     // 1 takes the first two and operand 2 the rest, zero where there is none.  The sparse
     // instruction at twice its issue count does the work of the dense one at the same rate, and
-    // the whole staging path stays as it is.
+    // the whole staging path stays as it is.  4-bit codes come out times 16 (see decode).
     static __device__ __forceinline__ void decode2(const Raw& r, v4i& c1, int& p1, v4i& c2, int& p2)
     {
         static_assert(DUAL, "patterns with more than two kept entries per group");
+        if constexpr (N == M && BITS == 4) {
+            // dense, two subgroups a dword: the even columns of each are operand 1 (positions 0, 2), the odd ones operand 2
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t lo, hi;
+                nibbles<true>(r.v[d], lo, hi);
+                c1[d] = (int)lo;
+                c2[d] = (int)hi;
+            }
+            p1 = (int)0x88888888u;
+            p2 = (int)0xDDDDDDDDu;
+            return;
+        }
         // the codes as bytes, in entry order (4-bit units may end in the middle of a dword)
         uint32_t w[2 * ((EPU + 7) / 8)];
         if constexpr (BITS == 8) {
@@ -233,9 +267,8 @@ struct Unit {
         } else {
 #pragma unroll
             for (int d = 0; d < (EPU + 7) / 8; ++d) {
-                const uint32_t x = r.v[d];
-                const uint32_t lo = sext4x4(x & 0x0F0F0F0Fu);          // entries 0, 2, 4, 6 of this dword
-                const uint32_t hi = sext4x4((x >> 4) & 0x0F0F0F0Fu);   // entries 1, 3, 5, 7
+                uint32_t lo, hi;
+                nibbles<true>(r.v[d], lo, hi);
                 w[2 * d] = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
                 w[2 * d + 1] = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
             }
@@ -293,6 +326,22 @@ struct Unit {
         }
     }
 };
+
+// 4-bit codes are multiplied as 16 times their value, which spares the sign extension (six of the nine to thirteen vector
+// operations per packed dword); the sums are 16 times the accumulator's value, exactly while kept entries x 16 x 8 x 128 stay below 2^31.
+// A dense 4-bit unit is 12 operations instead of 52, and its tiles were bound by them: 4096 x 768 -> 3072 19.1 -> 14.7 us, -> 2304 17.6 -> 13.9;
+// 2:4 int4 12.0 -> 11.3 and, 3072 -> 768, 16.0 -> 15.3; 1:4 int4 3 %, 2:8 int4 1 to 3 %.
+constexpr long long SCALED_MOST_KEPT = (1ll << 31) / (16 * 8 * 128) - 1;
+template <int BITS, int FO, int FT>
+__device__ __forceinline__ void unscale(v4i (&acc)[FO][FT])
+{
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int fo = 0; fo < FO; ++fo)
+#pragma unroll
+            for (int ft = 0; ft < FT; ++ft) acc[fo][ft] >>= 4;
+    }
+}
 
 // The arguments every workgroup needs before its first operand loads, fetched in one round trip
 // to the argument memory: left to itself the compiler fetches each where it is first used, four

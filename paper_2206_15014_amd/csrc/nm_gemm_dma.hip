@@ -253,7 +253,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
             }
         } else {
             v4i codes; int pos;
-            U::decode(w, codes, pos);
+            U::template decode<true>(w, codes, pos);
 #pragma unroll
             for (int ft = decltype(ft0)::value; ft < decltype(ft1)::value; ++ft)
                 acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(codes, bsrc[ft], acc[fo][ft], pos, 0, 0);
@@ -432,6 +432,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
         });
     }
 
+    unscale<BITS>(acc);
     // ---- epilogue: Eq. 4 with offset 0 on the product of two quantised operands --------------
     // The MFMA leaves each lane with 4 consecutive outputs of one token, so a plain store would
     // write 8-byte (bf16) pieces, 32 contiguous bytes per token and instruction.  Exact

@@ -98,7 +98,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
                     }
                 } else {
                     v4i codes; int pos;
-                    U::decode(w[i][fo], codes, pos);
+                    U::template decode<true>(w[i][fo], codes, pos);
 #pragma unroll
                     for (int ft = 0; ft < FT; ++ft)
                         acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(codes, b[i][ft], acc[fo][ft], pos, 0, 0);
@@ -138,6 +138,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
     v4i sum[1][1] = {{v4i{0, 0, 0, 0}}};
 #pragma unroll
     for (int w = 0; w < FEW_WAVES; ++w) sum[0][0] += part[(w * NF + ff) * 64 + lane];
+    unscale<BITS>(sum);
     if (a.out_dtype == 3) {                    // the columns' multipliers and offsets
         float g[4], h[4];
         requant_column(a.act_scale, sw[0].x, bw[0].x, a.out_scale, g[0], h[0]);

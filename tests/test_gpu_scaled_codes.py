@@ -1,0 +1,43 @@
+"""4-bit weights are multiplied as 16 times their value in the tiled-layout kernels: exact sums at the largest magnitudes the codes
+have, on both sides of the reduction length up to which 16 times the sum fits 32 bits, and at the sizes where the tile choice changes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2206_15014_amd as nm
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N, M", [(2, 4), (1, 4), (3, 4), (4, 4), (1, 8), (2, 8), (5, 8)])
+@pytest.mark.parametrize("T, K, O", [(3, 128, 96), (40, 4096, 192), (700, 256, 768), (1100, 640, 1056)])
+def test_extreme_codes(N, M, T, K, O):
+    rng = np.random.default_rng(T + N)
+    W = rng.choice(np.array([-1.0, 1.0], np.float32), (O, K))          # every kept code is -7 or 7
+    W[0], W[1] = 1.0, -1.0                                             # the largest sums of either sign
+    X = rng.choice(np.array([-128, 127], np.int8), (T, K))
+    X[0], X[-1] = 127, -128
+    v, m, s = oracle.compress(W, N, M, 4)
+    want = oracle.gemm_sparse(X, v, m, O, N, M, 4)
+    vals, meta, scales = nm.nm_compress(torch.from_numpy(W).cuda(), N, M, 4, layout=nm.NM_LAYOUT_TILED)
+    acc = torch.empty((T, O), dtype=torch.int32, device="cuda")
+    nm.nm_gemm(torch.from_numpy(X).cuda(), 1.0, vals, meta, scales, O, N, M, 4, acc=acc, layout=nm.NM_LAYOUT_TILED)
+    assert np.array_equal(acc.cpu().numpy(), want)
+
+
+# (2:4: K / 2 kept.)  131072 - 64 kept entries are the last whole slice below the limit, 131072 the first past it, whose products by -128
+# and -8 would reach 2^31
+@pytest.mark.parametrize("K", [2 * 131072 - 128, 2 * 131072])
+def test_longest_reductions(K):
+    T, O = 2, 16
+    codes = np.full((O, K // 4), 0x88, np.uint8)                       # two codes of -8 a byte, on columns 0 and 1 of each group
+    meta = np.full((O, K // 4 * 4 // 8), 0x44, np.uint8)
+    X = np.full((T, K), -128, np.int8)
+    X[1] = 127
+    v, m = oracle.to_tiled(codes, meta, K, 2, 4, 4)
+    acc = torch.empty((T, O), dtype=torch.int32, device="cuda")
+    nm.nm_gemm(torch.from_numpy(X).cuda(), 1.0, torch.from_numpy(v).cuda(), torch.from_numpy(m).cuda(), torch.ones(O, device="cuda"), O, 2, 4, 4,
+               acc=acc, layout=nm.NM_LAYOUT_TILED)
+    want = np.array([[K // 2 * 8 * 128] * O, [K // 2 * -8 * 127] * O], np.int64)
+    assert np.array_equal(acc.cpu().numpy().astype(np.int64), want)
