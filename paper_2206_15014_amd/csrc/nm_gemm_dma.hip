@@ -831,6 +831,14 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         // do not come here: see few_tile.
         if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 130;
         else if (!U::DUAL && n96 < 128 && n64x96 <= 256 && count == 1) cfg = 132;
+        // 4-bit codes in groups of four (2:4, 1:4, dense) decode so cheaply since they are multiplied as 16 times their value
+        // that decoding once is worth less than tiles that fit: four wavefronts on 128 x 96 where 96 divides the width (768
+        // wide, 1024 to 24576 tokens, K 768 and 3072: 0.79 to 1.01 of the time of decoding once; 512, 640 and 1024 wide 0.94 to 1.3),
+        // 128 x 128 by eight wavefronts 4 x 2 from 448 tiles on (8192 x 1024 -> 1024 15.1 -> 12.6 us, 24576 x 2048 -> 512
+        // 39 -> 28.5; 376 tiles, 6000 x 1024 -> 1024: 12.2 and 12.5; K = 4096: equal).
+        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.O % 96 == 0) cfg = 115;
+        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.K <= 2048 &&
+                 (long long)((a.tokens + 127) / 128) * ((a.O + 127) / 128) >= 448) cfg = 117;
         else if (NARROW_ONCE && count == 1 && ((DECODE_BOUND && ALWAYS_ONCE) || a.O <= 1024)) cfg = 127;
         else if (U::IDENTITY && count == 1 && n96 >= 256) cfg = modelled_tile(a);
         else if (pick == 122 && WIDE24) cfg = count == 1 ? 126 : (N == 3 ? 117 : 122);
