@@ -31,10 +31,12 @@ void canonical_dense(int& N, int& M)
 
 std::atomic<int> g_forced_tile{0};
 std::atomic<int> g_last_tile{0};
+std::atomic<int> g_project_patience{4096};     // a few milliseconds
 
 }  // namespace
 
 namespace nm {
+int project_patience() { return g_project_patience.load(std::memory_order_relaxed); }
 int forced_gemm_tile() { return g_forced_tile.load(std::memory_order_relaxed); }
 void note_gemm_tile(int cfg) { g_last_tile.store(cfg, std::memory_order_relaxed); }
 }
@@ -42,6 +44,8 @@ void note_gemm_tile(int cfg) { g_last_tile.store(cfg, std::memory_order_relaxed)
 extern "C" {
 
 int nm_test_force_gemm_tile(int cfg) { return g_forced_tile.exchange(cfg, std::memory_order_relaxed); }
+
+int nm_test_project_patience(int turns) { return g_project_patience.exchange(turns, std::memory_order_relaxed); }
 
 int nm_bench_last_gemm_tile(void) { return g_last_tile.load(std::memory_order_relaxed); }
 

@@ -174,6 +174,9 @@ bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg);
 // Tile id of the few-token kernels for a launch, 0 where they are not the choice (host arithmetic only).
 int few_tile(const GemmArgs* items, int count);
 
+// How many turns a workgroup of nm_project waits for the others of its scale group, see nm_test_hooks.h.
+int project_patience();
+
 // Tile variant forced by the tests (0 = automatic), see nm_test_hooks.h.
 int forced_gemm_tile();
 // Records which kernel variant the last nm_gemm / nm_gemm_q8 / nm_gemm_batch call launched (the tile ids

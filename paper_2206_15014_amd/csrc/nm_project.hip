@@ -6,8 +6,10 @@
 // one more read of W and U for the scales where a scale group is too large for the wavefronts that
 // hold its values (the second read mostly hits the last-level cache).  At these sizes a launch is a
 // few microseconds, so what counts is loads in flight and the number of launches: every lane
-// requests all it needs before its first use.  With one row per scale and up to 4096 columns there is one launch.
-// Otherwise there are two, and three only for large scale groups:
+// requests all it needs before its first use.  With one row per scale and up to 4096 columns there is one launch, and
+// with scale groups of several rows one whose workgroups tell one another their maxima (project_parts_kernel).
+// Otherwise - under stream capture, in place, very many small or a few very large scale groups - there are two, or three for large
+// scale groups:
 //  - row maxima, then the projection, which forms the scales.  The per-row scale array is the only scratch: it
 //    first receives the rows' largest magnitudes, negated, and the projection replaces them by the scales
 //    while it runs - a value with the sign bit set is a maximum, one without is a scale, and either tells a
@@ -17,13 +19,22 @@
 // Every arithmetic step is one fp32 operation, in the order the declaration of nm_project states.
 //
 // Measurements stand at the rules of launch_project_m.  The 48 matrices of a BERT-base encoder (32 rows per scale, operands from
-// HBM), against three launches a matrix with a load at a time per thread: 748 -> 598 us, of which moving every byte once takes about 250.
+// HBM), against three launches a matrix with a load at a time per thread: 748 -> 598 us on two launches, 504 on one, of which moving every
+// byte once takes about 250.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <type_traits>
 
 #include "nm_internal.h"
+
+#include <atomic>
+
+// Where the workgroups of project_parts_kernel tell one another their maxima: every GPU the library runs on holds its own copy. A
+// call uses one region of the 64 in turn, a word per workgroup; should two calls in flight ever share one, words of the other call are
+// seen for what they are by their number.
+constexpr int MEET_REGIONS = 64, MEET_WORDS = 4096;
+static __device__ unsigned long long meet_words[MEET_REGIONS * MEET_WORDS];
 
 namespace nm {
 
@@ -363,6 +374,169 @@ project_wave_kernel(const float* __restrict__ W, const float* U, int rows, int c
     }
 }
 
+// One launch for scale groups of several rows: `parts` (up to 64) workgroups per scale group, each with its part of the group's
+// values in registers (PER groups of M columns per thread), so W and U are read once.  The workgroups of a group tell one
+// another their parts' maxima through a 64-bit word each: the call's number above, the maximum's bits below, so a word
+// says by itself whether it belongs to this call, nothing has to be cleared and no order between two words matters.  They are neighbours
+// on one XCD and start together; one that has waited `patience` turns for the others (a chip that is busy with something else)
+// reads the rest of the group itself and waits no more.  So W and U must not change meanwhile: with several parts U_out is not U.
+// magic = ceil(2^32 / (cols / 4)), which divides every number up to the group's 16-byte pieces exactly (the launcher's condition).
+template <int M, int PER, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+project_parts_kernel(const float* __restrict__ W, const float* U, int rows, int cols, int ldw, int N, int bits, int rows_per_scale,
+                     int n_groups, int parts, uint32_t magic, float* __restrict__ scales, float* __restrict__ Z, float* U_out, int ldz,
+                     uint32_t call, int patience)
+{
+    constexpr int F = M / 4;
+    __shared__ float part_max[THREADS / 64];
+    __shared__ float group_max;
+    __shared__ int missing;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int total = n_groups * parts, per_xcd = (total + 7) >> 3;
+    const int id = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (id >= total) return;                   // the whole workgroup
+    const int group = id / parts, part = id - group * parts;
+    const int r0 = group * rows_per_scale, n = rows - r0 < rows_per_scale ? rows - r0 : rows_per_scale;
+    const int width = cols / 4, pieces = n * width;        // of 16 bytes
+    const int own = (pieces / F + parts - 1) / parts * F;  // pieces of a part (the last ones may have fewer, or none)
+    const int begin = min(part * own, pieces), end = min(begin + own, pieces);
+    auto place = [&](int piece, int ld) __attribute__((always_inline)) {
+        const int r = (int)__umulhi((uint32_t)piece, magic);
+        return (size_t)(r0 + r) * ld + 4 * (size_t)(piece - r * width);
+    };
+    float v[PER][M];
+    load_groups<M, PER>(W, U, [&](int i) __attribute__((always_inline)) { return place(min(begin + (tid + i * THREADS) * F, pieces - F), ldw); }, v);
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int c = 0; c < M; ++c) m = fmaxf(m, fabsf(v[i][c]));          // (a clamped place is one of the group's too)
+    auto workgroup_max = [&]() __attribute__((always_inline)) {
+        m = wave_max_f(m);
+        if (lane == 0) part_max[tid >> 6] = m;
+        __syncthreads();
+        m = part_max[0];
+#pragma unroll
+        for (int w = 1; w < THREADS / 64; ++w) m = fmaxf(m, part_max[w]);
+    };
+    workgroup_max();
+    if (parts > 1) {
+        if (tid < 64) {
+            unsigned long long* words = meet_words + (call % MEET_REGIONS) * MEET_WORDS + group * parts;
+            if (lane == 0)
+                __hip_atomic_store(words + part, ((unsigned long long)call << 32) | __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long word = 0;
+            bool here = lane >= parts;
+            for (int turn = 0;; ++turn) {
+                if (!here) {
+                    word = __hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    here = (uint32_t)(word >> 32) == call;
+                }
+                if (__all(here) || turn >= patience) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            const float top = wave_max_f(fmaxf(here && lane < parts ? __uint_as_float((uint32_t)word) : 0.0f, m));
+            const int all_here = __all(here);
+            if (lane == 0) {
+                group_max = top;
+                missing = !all_here;
+            }
+        }
+        __syncthreads();
+        if (missing) {
+            // from the end of this part round to its beginning
+            const int rest = pieces - (end - begin);
+            for (int i = tid; i < rest; i += 4 * THREADS) {
+                float4 x[4][1];
+                sums_at<4, 1>(W, U, [&](int k) __attribute__((always_inline)) {
+                    const int q = min(i + k * THREADS, rest - 1) + end;
+                    return place(q >= pieces ? q - pieces : q, ldw);
+                }, x);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) m = max4(m, x[k][0]);
+            }
+            workgroup_max();                   // (part_max: last read before the barrier above)
+        } else {
+            m = group_max;
+        }
+    }
+    const float s = scale_of_max(m, (float)((1 << (bits - 1)) - 1));
+    if (part == 0)
+        for (int r = tid; r < n; r += THREADS) scales[r0 + r] = s;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int piece = begin + (tid + i * THREADS) * F;
+        if (piece >= end) break;
+        float z[M];
+        project_group<M>(v[i], N, bits, s, z);
+        store_group<M>(v[i], z, Z, U_out, place(piece, ldz));
+    }
+}
+
+template <int M, int MOST, int THREADS, typename... Args>
+void launch_project_parts_per(int per, unsigned blocks, hipStream_t st, Args... args)
+{
+    if constexpr (MOST > 1) {
+        if (per < MOST) return launch_project_parts_per<M, MOST - 1, THREADS>(per, blocks, st, args...);
+    }
+    hipLaunchKernelGGL((project_parts_kernel<M, MOST, THREADS>), dim3(blocks), dim3(THREADS), 0, st, args...);
+}
+
+// A number for a call whose workgroups meet: 32 bits that no earlier call of this process had, 0 when there are none left (after
+// 2^32 calls) or when the launch would be replayed with the number it has now (stream capture: such calls go by the other launches).
+uint32_t meeting_call(hipStream_t st)
+{
+    static std::atomic<unsigned long long> calls{0};
+    hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    if (status != hipStreamCaptureStatusNone) return 0;
+    const unsigned long long call = 1 + calls.fetch_add(1, std::memory_order_relaxed);
+    return call <= 0xFFFFFFFFull ? (uint32_t)call : 0;
+}
+
+// Whether project_parts_kernel takes the call, and its launch.  The lines, over 700 shapes (16 to 30522 rows, 8 to 8192 columns, 2 to
+// 300 rows per scale, U given; launches one after the other, against the launches below): the mean is 0.72 of their time
+// and none is slower by more than 6 % (0.6 us).  3072 x 768, 32 rows per scale 13.6 -> 12.3 us from HBM and 9.9 -> 8.4 from the last-level
+// cache, 768 x 3072 15.7 -> 12.9 and 12.4 -> 9.2, 768 x 768 7.8 -> 6.6, 30522 x 768 106 -> 81; the 48 matrices of a BERT-base encoder 599 -> 504.
+//  - 1024 threads where that still gives 128 workgroups, else 256 (768 x 768: 7.7 and 6.6; 30522 x 768: 81 and 106);
+//  - up to 24 parts on 1024 threads, of which a CU holds two: an XCD then has room for all parts of a group at once (57 parts, 8192 x
+//    3072 at 300 rows per scale, 104 -> 910 us); on 256 threads up to 64, and no more workgroups than the chip holds;
+//  - many tiny groups leave most of a workgroup idle (15261 groups of 128 values 11.5 -> 15.0);
+//  - above 20 million values in more than two parts the waiting workgroups' place is missed (8192 x 3072, 12 parts, 101 -> 106).
+template <int M>
+bool launch_project_parts(const float* W, const float* U, int rows, int cols, int ldw, int N, int bits, int rows_per_scale,
+                          float* Z, float* U_out, int ldz, float* scales, hipStream_t st)
+{
+    constexpr int MOST = 16 / M;               // groups of M columns per thread
+    const int span = rows_per_scale < rows ? rows_per_scale : rows, width = cols / 4;
+    const long long n_groups = ((long long)rows + span - 1) / span, values = (long long)span * cols, elements = (long long)rows * cols;
+    if (width < 2 || (values < 512 && n_groups > 2048) || values / 4 * width >= (1ll << 32) || n_groups > (1 << 20)) return false;
+    long long parts = (values + 16 * 1024 - 1) / (16 * 1024);
+    const bool wide = values > 16 * 256 && n_groups * parts >= 128;
+    if (wide) {
+        if (parts > 24 || (parts > 2 && elements > 20000000)) return false;
+    } else {
+        parts = (values + 16 * 256 - 1) / (16 * 256);
+        if (parts > 64 || (parts > 1 && n_groups * parts > 2048)) return false;
+    }
+    if (parts > 1 && ((U_out == U && U) || n_groups * parts > MEET_WORDS)) return false;
+    const uint32_t call = meeting_call(st);
+    if (call == 0) return false;
+    const int threads = wide ? 1024 : 256;
+    const int per = (int)(((values / M + parts - 1) / parts + threads - 1) / threads);
+    const unsigned blocks = (unsigned)(8 * ((n_groups * parts + 7) / 8));
+    const uint32_t magic = (uint32_t)((0x100000000ull + width - 1) / width);
+    const int patience = project_patience();
+    if (wide)
+        launch_project_parts_per<M, MOST, 1024>(per, blocks, st, W, U, rows, cols, ldw, N, bits, span, (int)n_groups, (int)parts, magic, scales, Z, U_out, ldz, call, patience);
+    else
+        launch_project_parts_per<M, MOST, 256>(per, blocks, st, W, U, rows, cols, ldw, N, bits, span, (int)n_groups, (int)parts, magic, scales, Z, U_out, ldz, call, patience);
+    return true;
+}
+
 // `per` up to MOST
 template <int M, int MOST, typename... Args>
 void launch_project_wave(int per, unsigned blocks, hipStream_t st, Args... args)
@@ -425,6 +599,8 @@ void launch_project_m(const float* W, const float* U, int rows, int cols, int ld
         hipLaunchKernelGGL((project_row_kernel<M, 4>), dim3(rows), dim3(256), 0, st, W, U, rows, cols, ldw, N, bits, scales, Z, U_out, ldz);
         return;
     }
+    if (bits && rows_per_scale > 1 &&
+        launch_project_parts<M>(W, U, rows, cols, ldw, N, bits, rows_per_scale, Z, U_out, ldz, scales, st)) return;
     // Two ways to project.  project_wave_kernel has a row's groups in one or a few wavefronts, so it can form the
     // scales, and its loads are all in flight; project_kernel wastes no lane and needs no row of 64 groups.  Three ways to
     // the scales.  The lines below are where the measured times cross (16 to 30522 rows, 8 to 8192 columns, 1 to 300

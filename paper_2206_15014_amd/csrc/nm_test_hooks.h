@@ -55,6 +55,12 @@ int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits);
  */
 int nm_test_gemm_any_reads(int tokens, int K, int ldx, int O, int N, int M, int bits, int layout,
                            size_t *x_end, size_t *v_end, size_t *m_end);
+
+/*
+ * Test hook: how many turns a workgroup of nm_project waits for the other workgroups of its scale group before it reads their values
+ * itself; 0: it looks once.  Returns the previous value.  One process-wide atomic integer.
+ */
+int nm_test_project_patience(int turns);
 #ifdef __cplusplus
 }
 #endif
