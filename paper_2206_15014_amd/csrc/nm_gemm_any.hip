@@ -35,17 +35,23 @@ constexpr long long ANY_LAUNCH_TILES = 1 << 23;
 constexpr unsigned any_workgroups(long long tiles) { return (unsigned)(8 * ((tiles + 7) / 8)); }
 static_assert((unsigned long long)any_workgroups(ANY_LAUNCH_TILES) * 256 < (1ull << 32), "threads of a launch");
 
+constexpr int KC = 256;                        // columns per chunk
+
 struct AnyPlan { int side; long long tiles_o, tiles; };        // of side x side outputs
-AnyPlan any_plan(int tokens, int O)
+AnyPlan any_plan(int tokens, int O, bool chunks)
 {
     const long long big = ((tokens + 63ll) / 64) * ((O + 63ll) / 64);
-    // Fewer than two 64 x 64 tiles per CU leave it short of wavefronts to cover the latency of a chunk.
-    const int side = big < 512 ? 32 : 64;
+    // Fewer than two 64 x 64 tiles per CU leave it short of wavefronts to cover the latency of a chunk.  With several chunks
+    // the large tiles, which stage each operand half as often, are ahead from 400 on (2:4 int8, 1999 x 312 -> 936, 480 tiles: 7.0 -> 6.2 us,
+    // 1700 x 1000 -> 1020, 432 tiles: 11.3 -> 9.5, 3:4 15.6 -> 13.2; 264 tiles, 1500 x 2720 -> 680, 1:4: 15.0 and 15.4; with one
+    // chunk, dense, 2500 x 200 -> 696, 440 tiles: 5.7 and 5.1).
+    const int side = big < (chunks ? 400 : 512) ? 32 : 64;
     const long long tiles_o = (O - 1ll + side) / side;
     return AnyPlan{side, tiles_o, ((tokens - 1ll + side) / side) * tiles_o};
 }
+// (dense: two whole chunks; 1999 x 312 -> 872, 448 tiles: 6.6 us on the small tiles, 6.8)
+AnyPlan any_plan(const GemmArgs& a) { return any_plan(a.tokens, a.O, a.K > KC && (a.N < a.M || a.K >= 2 * KC)); }
 
-constexpr int KC = 256;                        // columns per chunk
 constexpr int ROW = KC + 16;                   // LDS bytes per row: 16-byte reads of 8 consecutive rows cover all banks once
 constexpr int CROW = KC / 2 + 16;              // the same for rows of sparse-MFMA codes (16 bytes per 32 columns) ...
 constexpr int PROW = KC / 8 + 4;               // ... and of their positions (4 bytes per 32 columns)
@@ -442,7 +448,7 @@ bool thread_per_output(const GemmArgs& a, bool vec)
 template <int N, int M, int BITS, int B>
 void launch_any_tile(const GemmArgs& a, bool vec, hipStream_t st)
 {
-    const AnyPlan plan = any_plan(a.tokens, a.O);
+    const AnyPlan plan = any_plan(a);
     for (long long first = 0; first < plan.tiles; first += ANY_LAUNCH_TILES) {
         const int n = (int)(plan.tiles - first < ANY_LAUNCH_TILES ? plan.tiles - first : ANY_LAUNCH_TILES);
         hipLaunchKernelGGL((gemm_any_kernel<N, M, BITS, B, B>), dim3(any_workgroups(n)), dim3(256), 0, st, a, (int)plan.tiles_o, (int)first, n,
@@ -454,7 +460,7 @@ template <int N, int M, int BITS>
 void launch_any(const GemmArgs& a, hipStream_t st)
 {
     const bool vec = whole_groups_of_four(a);
-    if (any_plan(a.tokens, a.O).side == 32) launch_any_tile<N, M, BITS, 32>(a, vec, st);
+    if (any_plan(a).side == 32) launch_any_tile<N, M, BITS, 32>(a, vec, st);
     else launch_any_tile<N, M, BITS, 64>(a, vec, st);
 }
 
@@ -478,7 +484,7 @@ void launch_gemm_any(const GemmArgs& a, hipStream_t st)
 bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_end)
 {
     if (thread_per_output(a, false)) return false;
-    const AnyPlan plan = any_plan(a.tokens, a.O);
+    const AnyPlan plan = any_plan(a);
     const int side = plan.side;
     auto reach = [](size_t* end, size_t at, size_t bytes) { if (bytes && at + bytes > *end) *end = at + bytes; };
     auto unit_reach = [&](const PackedArray& p, size_t* end, int row, int unit, bool whole) {
@@ -506,7 +512,7 @@ bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_e
 
 int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)
 {
-    const AnyPlan plan = any_plan(tokens, O);
+    const AnyPlan plan = any_plan(tokens, O, false);
     *tiles = plan.tiles;
     *most_workgroups = any_workgroups(plan.tiles < ANY_LAUNCH_TILES ? plan.tiles : ANY_LAUNCH_TILES);
     return (int)((plan.tiles + ANY_LAUNCH_TILES - 1) / ANY_LAUNCH_TILES);
