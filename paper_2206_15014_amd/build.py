@@ -55,9 +55,11 @@ def build(verbose: bool = False) -> str:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
         os.replace(tmp, LIB)
-        _run([hipcc, "-x", "c", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
-              os.path.join(CSRC, "nm_python.c"), "-o", tmp], verbose)
-        os.replace(tmp, PYTHON_MODULE)
+        include = sysconfig.get_paths()["include"]
+        if os.path.exists(os.path.join(include, "Python.h")):        # without it the binding goes through ctypes alone
+            _run([hipcc, "-x", "c", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", include,
+                  os.path.join(CSRC, "nm_python.c"), "-o", tmp], verbose)
+            os.replace(tmp, PYTHON_MODULE)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
         if os.path.exists(tmp):

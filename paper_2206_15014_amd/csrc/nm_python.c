@@ -99,7 +99,7 @@ static PyObject* py_gemm(PyObject* self, PyObject* const* a, Py_ssize_t n)
     TRY(shape_2d(a[0], &tokens, &K));
     if (a[13] == Py_None) {
         PyObject* ref = a[11] != Py_None ? a[11] : a[10];
-        if (ref == Py_None || PyLong_Check(ref)) ldo = O;
+        if (ref == Py_None || !PyObject_HasAttr(ref, s_stride)) ldo = O;
         else TRY(row_stride(ref, &ldo));
     } else {
         TRY(to_int(a[13], &ldo));
