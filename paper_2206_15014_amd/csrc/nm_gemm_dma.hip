@@ -453,12 +453,14 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
     }
     read_scales();
     if (a.acc != nullptr || a.out_dtype == 0 || !full_cols) {
-        store_tile_pre<FO, FT>(a, acc, sw, bw, o0 + wo * WO, t0 + wt * WT, li, lg);
+        const float m = store_tile_pre<FO, FT>(a, acc, sw, bw, o0 + wo * WO, t0 + wt * WT, li, lg);
+        if (a.out_dtype == 3) absmax_commit_group<NW>(m, out_scale_of(a), a.absmax, reinterpret_cast<float*>(smem));
         return;
     }
     const int esize = (a.out_dtype == 1) ? 4 : (a.out_dtype == 2) ? 2 : 1;
     if ((a.ldo * esize) % (a.out_dtype == 3 ? 8 : 16) != 0) {   // rows not 16-byte (int8 codes: 8-byte) aligned
-        store_tile_pre<FO, FT>(a, acc, sw, bw, o0 + wo * WO, t0 + wt * WT, li, lg);
+        const float m = store_tile_pre<FO, FT>(a, acc, sw, bw, o0 + wo * WO, t0 + wt * WT, li, lg);
+        if (a.out_dtype == 3) absmax_commit_group<NW>(m, out_scale_of(a), a.absmax, reinterpret_cast<float*>(smem));
         return;
     }
     uint8_t* out = reinterpret_cast<uint8_t*>(a.out);
@@ -539,7 +541,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
                 emit8(da, db, row0 + (ft + (lg & 1)) * 16, col0 + fo * 16 + (lg >> 1) * 8);
             });
         }
-        absmax_commit(m, out_scale_of(a), a.absmax);
+        absmax_commit_group<NW>(m, out_scale_of(a), a.absmax, reinterpret_cast<float*>(smem));    // (the ring is done with: a barrier lies behind)
         return;
     }
     if (a.out_dtype == 1) {

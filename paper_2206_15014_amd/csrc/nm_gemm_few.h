@@ -148,7 +148,8 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
         sw[0] = make_float4(g[0], g[1], g[2], g[3]);
         bw[0] = make_float4(h[0], h[1], h[2], h[3]);
     }
-    store_tile_pre<1, 1>(a, sum, sw, bw, o0 + ffo * 16, t0 + fft * 16, li, lg);
+    const float m = store_tile_pre<1, 1>(a, sum, sw, bw, o0 + ffo * 16, t0 + fft * 16, li, lg);
+    if (a.out_dtype == 3) absmax_commit(m, out_scale_of(a), a.absmax);
 }
 
 // One GEMM per launch; each XCD (workgroups are dealt to the eight in turn) takes a contiguous run of
