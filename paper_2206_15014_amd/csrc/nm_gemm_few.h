@@ -134,22 +134,32 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) part[(wave * NF + fo * FT + ft) * 64 + lane] = acc[fo][ft];
     __syncthreads();
-    if (wave >= NF) return;
-    v4i sum[1][1] = {{v4i{0, 0, 0, 0}}};
+    // the largest output: one commit per workgroup here too (layer chain 226 x 384, 1:8 int8 31.4 -> 19.8 us, 93 x 384, 2:4 int4 23.1 -> 18.2)
+    const bool meet = NF > 1 && a.out_dtype == 3 && a.absmax != nullptr;
+    if (wave >= NF && !meet) return;
+    float m = 0.0f;
+    if (wave < NF) {
+        v4i sum[1][1] = {{v4i{0, 0, 0, 0}}};
 #pragma unroll
-    for (int w = 0; w < FEW_WAVES; ++w) sum[0][0] += part[(w * NF + ff) * 64 + lane];
-    unscale<BITS>(sum);
-    if (a.out_dtype == 3) {                    // the columns' multipliers and offsets
-        float g[4], h[4];
-        requant_column(a.act_scale, sw[0].x, bw[0].x, a.out_scale, g[0], h[0]);
-        requant_column(a.act_scale, sw[0].y, bw[0].y, a.out_scale, g[1], h[1]);
-        requant_column(a.act_scale, sw[0].z, bw[0].z, a.out_scale, g[2], h[2]);
-        requant_column(a.act_scale, sw[0].w, bw[0].w, a.out_scale, g[3], h[3]);
-        sw[0] = make_float4(g[0], g[1], g[2], g[3]);
-        bw[0] = make_float4(h[0], h[1], h[2], h[3]);
+        for (int w = 0; w < FEW_WAVES; ++w) sum[0][0] += part[(w * NF + ff) * 64 + lane];
+        unscale<BITS>(sum);
+        if (a.out_dtype == 3) {                // the columns' multipliers and offsets
+            float g[4], h[4];
+            requant_column(a.act_scale, sw[0].x, bw[0].x, a.out_scale, g[0], h[0]);
+            requant_column(a.act_scale, sw[0].y, bw[0].y, a.out_scale, g[1], h[1]);
+            requant_column(a.act_scale, sw[0].z, bw[0].z, a.out_scale, g[2], h[2]);
+            requant_column(a.act_scale, sw[0].w, bw[0].w, a.out_scale, g[3], h[3]);
+            sw[0] = make_float4(g[0], g[1], g[2], g[3]);
+            bw[0] = make_float4(h[0], h[1], h[2], h[3]);
+        }
+        m = store_tile_pre<1, 1>(a, sum, sw, bw, o0 + ffo * 16, t0 + fft * 16, li, lg);
     }
-    const float m = store_tile_pre<1, 1>(a, sum, sw, bw, o0 + ffo * 16, t0 + fft * 16, li, lg);
-    if (a.out_dtype == 3) absmax_commit(m, out_scale_of(a), a.absmax);
+    if (meet) {
+        __syncthreads();                       // every partial sum is read
+        absmax_commit_group<FEW_WAVES>(m, out_scale_of(a), a.absmax, reinterpret_cast<float*>(part));
+    } else if (a.out_dtype == 3) {
+        absmax_commit(m, out_scale_of(a), a.absmax);
+    }
 }
 
 // One GEMM per launch; each XCD (workgroups are dealt to the eight in turn) takes a contiguous run of
