@@ -825,6 +825,7 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
             if (best < 0 || c * 105 < best * 100) { best = c; pick = sh.cfg; }
         }
         const long long n96 = (long long)((a.tokens + 127) / 128) * ((a.O + 95) / 96);
+        const long long n128 = (long long)((a.tokens + 127) / 128) * ((a.O + 127) / 128);
         const long long n64x96 = (long long)((a.tokens + 63) / 64) * ((a.O + 95) / 96);
         const long long n64x48 = (long long)((a.tokens + 63) / 64) * ((a.O + 47) / 48);
         // A problem of fewer than 128 tiles of 128 x 96 leaves half the chip idle while every workgroup
@@ -838,9 +839,14 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         // wide, 1024 to 24576 tokens, K 768 and 3072: 0.79 to 1.01 of the time of decoding once; 512, 640 and 1024 wide 0.94 to 1.3),
         // 128 x 128 by eight wavefronts 4 x 2 from 448 tiles on (8192 x 1024 -> 1024 15.1 -> 12.6 us, 24576 x 2048 -> 512
         // 39 -> 28.5; 376 tiles, 6000 x 1024 -> 1024: 12.2 and 12.5; K = 4096: equal).
-        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.O % 96 == 0) cfg = 115;
-        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.K <= 2048 &&
-                 (long long)((a.tokens + 127) / 128) * ((a.O + 127) / 128) >= 448) cfg = 117;
+        // Up to two rounds of 128 columns, 96 do not pay where they need one more (6000 x 384 -> 576: 235 and 282 tiles, 6.1 and 6.6 us;
+        // 16000 -> 480: 500 and 625, 8.3 and 10.2; a fourth for a third is repaid, 16000 -> 768: 15.9 and 13.2), nor where 128 divides
+        // the width too and all is one round (9000 -> 384: 5.8 and 6.6).  Of two rounds, int8 codes are best decoded once (12000 x 384 ->
+        // 576: 8.1 and 9.3 with 4 x 2 wavefronts; bf16 16000 -> 480: 10.9 and 9.1).
+        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.O % 96 == 0 &&
+                 (n128 > 512 || (n96 + 255) / 256 <= (n128 + 255) / 256) && (a.O % 128 != 0 || n128 > 256)) cfg = 115;
+        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.K <= 2048 && n128 >= 448 &&
+                 (n128 > 512 || a.out_dtype != 3)) cfg = 117;
         else if (NARROW_ONCE && count == 1 && ((DECODE_BOUND && ALWAYS_ONCE) || a.O <= 1024)) cfg = 127;
         else if (U::IDENTITY && count == 1 && n96 >= 256) cfg = modelled_tile(a);
         else if (pick == 122 && WIDE24) cfg = count == 1 ? 126 : (N == 3 ? 117 : 122);
