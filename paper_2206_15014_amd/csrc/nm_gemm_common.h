@@ -482,15 +482,8 @@ __device__ __forceinline__ uint32_t requant4(const v4i c, const float (&g)[4], c
     return lo | hi;
 }
 
-// Largest of `m` (>= 0) over the wavefront, max-combined into *dst: non-negative floats order like
-// their bit patterns, so an unsigned atomic maximum does it.  Thousands of wavefronts meet at that
-// one address and an atomic there costs some 15 ns, so a wavefront first reads the value (at agent
-// scope; it only ever grows, so one that is too old merely costs an atomic that was not needed)
-// and leaves the atomic out unless its own is larger - which after the first few is rare.
-// Every lane of the wavefront must call it.  `m` is in units of the codes: the value committed is
-// m * out_scale (multiplying by a positive number keeps the order, so the largest product is the
-// product of the largest).
-__device__ __forceinline__ float wave_max(float m)
+// Largest of `m` (>= 0) over the wavefront: lane 63 alone holds it.  Every lane of the wavefront must call it.
+__device__ __forceinline__ float wave_max_last_lane(float m)
 {
     // in-register lane moves (DPP within rows of 16, then across the rows): lane 63 ends up with the
     // maximum of all 64; six round trips through the LDS crossbar cost a microsecond of latency
@@ -505,6 +498,14 @@ __device__ __forceinline__ float wave_max(float m)
 #undef NM_MAX_STEP
     return m;
 }
+// Largest of `m` (>= 0) over the wavefront, max-combined into *dst (absmax_raise): non-negative floats order like
+// their bit patterns, so an unsigned atomic maximum does it.  Thousands of wavefronts meet at that
+// one address and an atomic there costs some 15 ns, so a wavefront first reads the value (at agent
+// scope; it only ever grows, so one that is too old merely costs an atomic that was not needed)
+// and leaves the atomic out unless its own is larger - which after the first few is rare.
+// Every lane of the wavefront must call it.  `m` is in units of the codes: the value committed is
+// m * out_scale (multiplying by a positive number keeps the order, so the largest product is the
+// product of the largest).
 __device__ __forceinline__ void absmax_raise(float m, float* dst)
 {
     unsigned int* u = reinterpret_cast<unsigned int*>(dst);
@@ -512,7 +513,7 @@ __device__ __forceinline__ void absmax_raise(float m, float* dst)
 }
 __device__ __forceinline__ void absmax_commit(float m, float out_scale, float* dst)
 {
-    m = wave_max(m) * out_scale;
+    m = wave_max_last_lane(m) * out_scale;
     if ((threadIdx.x & 63) == 63 && dst != nullptr) absmax_raise(m, dst);
 }
 
@@ -524,7 +525,7 @@ template <int NW>
 __device__ __forceinline__ void absmax_commit_group(float m, float out_scale, float* dst, float* part)
 {
     if (dst == nullptr) return;
-    m = wave_max(m);
+    m = wave_max_last_lane(m);
     if ((threadIdx.x & 63) == 63) part[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
