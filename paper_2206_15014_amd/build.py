@@ -1,6 +1,7 @@
 """Build libnm.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -25,6 +26,20 @@ HIPCC_FLAGS = [
 ]
 
 
+def source_digest() -> str:
+    """Of everything the library is made from; the library carries the one it was built with (nm_test_source_digest), so
+    one that was linked from older objects, or built before a change, is told from one of this tree."""
+    h = hashlib.sha256()
+    for folder in (os.path.join(ROOT, "include"), CSRC):
+        for name in sorted(n for n in os.listdir(folder) if n.endswith((".h", ".hip", ".c"))):
+            with open(os.path.join(folder, name), "rb") as f:
+                data = f.read()
+            h.update(b"%s %d\n" % (name.encode(), len(data)) + data)
+    with open(os.path.join(HERE, "build.py"), "rb") as f:
+        h.update(f.read())
+    return h.hexdigest()
+
+
 def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -44,7 +59,7 @@ def build(verbose: bool = False) -> str:
     import shutil
     import tempfile
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"]
+    compile_flags = [f for f in HIPCC_FLAGS if f != "-shared"] + ["-DNM_SOURCE_DIGEST=" + source_digest()]
     tmpdir = tempfile.mkdtemp(prefix="libnm_build_")
     tmp = LIB + ".tmp.%d" % os.getpid()
     try:

@@ -47,6 +47,13 @@ int nm_test_force_gemm_tile(int cfg) { return g_forced_tile.exchange(cfg, std::m
 
 int nm_test_project_patience(int turns) { return g_project_patience.exchange(turns, std::memory_order_relaxed); }
 
+#define NM_TEXT2(x) #x
+#define NM_TEXT(x) NM_TEXT2(x)
+#ifndef NM_SOURCE_DIGEST
+#define NM_SOURCE_DIGEST unknown
+#endif
+const char* nm_test_source_digest(void) { return NM_TEXT(NM_SOURCE_DIGEST); }
+
 int nm_bench_last_gemm_tile(void) { return g_last_tile.load(std::memory_order_relaxed); }
 
 int nm_test_gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)

@@ -61,6 +61,9 @@ int nm_test_gemm_any_reads(int tokens, int K, int ldx, int O, int N, int M, int 
  * itself; 0: it looks once.  Returns the previous value.  One process-wide atomic integer.
  */
 int nm_test_project_patience(int turns);
+
+/* Test hook: the digest of the sources that the build made the library from, "unknown" where another way of compiling gave none. */
+const char *nm_test_source_digest(void);
 #ifdef __cplusplus
 }
 #endif
