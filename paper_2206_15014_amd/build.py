@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnm.so")
-PYTHON_MODULE = os.path.join(HERE, "_nm_python.so")      # argument marshalling of the binding's hot calls
+# Argument marshalling of the binding's hot calls, for this interpreter alone: any other has its own suffix and does not find it.
+PYTHON_MODULE = os.path.join(HERE, "_nm_python" + sysconfig.get_config_var("EXT_SUFFIX"))
 # (source, extra flags, object name).  The LDS-direct GEMM kernels are one source compiled once per
 # set of N:M patterns, so that their many instantiations build in parallel.
 DMA_SETS = 11
@@ -52,6 +53,27 @@ def _run(cmd, verbose):
         print(out)
 
 
+def remove_python_modules(folder: str) -> None:
+    for name in os.listdir(folder):
+        if name.startswith("_nm_python.") and name.endswith(".so"):
+            os.unlink(os.path.join(folder, name))
+
+
+def build_python_module(include: str, target: str, hipcc: str, verbose: bool = False) -> bool:
+    """False where the interpreter's headers are not there: the binding then goes through ctypes alone."""
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return False
+    tmp = target + ".tmp.%d" % os.getpid()
+    try:
+        _run([hipcc, "-x", "c", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", include,
+              os.path.join(CSRC, "nm_python.c"), "-o", tmp], verbose)
+        os.replace(tmp, target)
+    finally:
+        if os.path.exists(tmp):
+            os.unlink(tmp)
+    return True
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source to an object (in parallel, one hipcc each) and link them into libnm.so.
     Objects live in a temporary directory, so the tree only ever holds sources and the library."""
@@ -69,12 +91,9 @@ def build(verbose: bool = False) -> str:
         with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
             list(pool.map(lambda c: _run(c, verbose), jobs))
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
+        remove_python_modules(HERE)            # (they call the library that goes now)
         os.replace(tmp, LIB)
-        include = sysconfig.get_paths()["include"]
-        if os.path.exists(os.path.join(include, "Python.h")):        # without it the binding goes through ctypes alone
-            _run([hipcc, "-x", "c", "-O2", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", include,
-                  os.path.join(CSRC, "nm_python.c"), "-o", tmp], verbose)
-            os.replace(tmp, PYTHON_MODULE)
+        build_python_module(sysconfig.get_paths()["include"], PYTHON_MODULE, hipcc, verbose)
     finally:
         shutil.rmtree(tmpdir, ignore_errors=True)
         if os.path.exists(tmp):

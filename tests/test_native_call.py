@@ -1,12 +1,14 @@
 """The C marshalling of nm_gemm against the ctypes one: both hand the library the same arguments (CPU, a recorder in the
 library's place), and what the C side does not take it leaves to ctypes."""
 import ctypes
+import os
+import sysconfig
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2206_15014_amd import binding
+from paper_2206_15014_amd import binding, build
 
 T, K, O = 5, 32, 12
 
@@ -72,3 +74,20 @@ def test_exceptions_pass_through(recorder):
         binding._native.gemm(*args)
     args[4], args[0] = t["scales"], t["X"].reshape(-1)
     assert binding._native.gemm(*args) is None     # not two dimensions: ctypes' path raises as it did
+
+
+def test_module_is_of_this_interpreter():
+    """Compiled against one interpreter's own structures, so named for it alone: plain `.so` every interpreter would load."""
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert suffix != ".so" and build.PYTHON_MODULE == os.path.join(build.HERE, "_nm_python" + suffix)
+    assert [n for n in os.listdir(build.HERE) if n.startswith("_nm_python.") and n.endswith(".so")] in ([], [os.path.basename(build.PYTHON_MODULE)])
+
+
+def test_no_module_outlives_its_library(tmp_path):
+    """A build that makes none leaves none: an older module would call the new library's function with the old arguments."""
+    for name in ("_nm_python.so", "_nm_python" + sysconfig.get_config_var("EXT_SUFFIX"), "_nm_python.cpython-38-x86_64-linux-gnu.so", "_nm_other.so"):
+        (tmp_path / name).write_bytes(b"")
+    build.remove_python_modules(str(tmp_path))
+    assert os.listdir(tmp_path) == ["_nm_other.so"]
+    assert build.build_python_module(str(tmp_path), str(tmp_path / "made.so"), "no compiler is asked") is False
+    assert os.listdir(tmp_path) == ["_nm_other.so"]
