@@ -27,6 +27,8 @@ namespace nm {
 namespace {
 
 constexpr int FEW_WAVES = 8;
+// registers that the loads of a packed unit fill: a two-byte piece takes one like a dword
+constexpr int load_registers(int bytes) { return bytes == 0 ? 0 : piece_bytes(bytes) == 2 ? bytes / 2 : (bytes + 3) / 4; }
 
 template <int N, int M, int BITS, int FT, int FO>
 __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, const int tile)
@@ -64,8 +66,9 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
         for (int ft = 0; ft < FT; ++ft) acc[fo][ft] = v4i{0, 0, 0, 0};
 
     // slices first, first + 8, ... of this wavefront, CNT of them: loads of all, then products of all
-    // slices a wavefront has in flight: two where their packed words would not fit the registers
-    constexpr int DEEP = FO * (U::VD + U::MD) > 24 ? 2 : 4;
+    // slices a wavefront has in flight: two where their packed words would not fit the registers (5:8 int4 is the one of 10 + 10 bytes in
+    // ten pieces: with four it spilled, 512 x 4096 -> 768 28.0 us, with two 14.0)
+    constexpr int DEEP = FO * (load_registers(U::VBYTES) + load_registers(U::MBYTES)) > 24 ? 2 : 4;
     auto walk = [&](auto cnt, int first) __attribute__((always_inline)) {
         constexpr int CNT = decltype(cnt)::value;
         v8i b[CNT][FT];
@@ -134,8 +137,12 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) part[(wave * NF + fo * FT + ft) * 64 + lane] = acc[fo][ft];
     __syncthreads();
-    // the largest output: one commit per workgroup here too (layer chain 226 x 384, 1:8 int8 31.4 -> 19.8 us, 93 x 384, 2:4 int4 23.1 -> 18.2)
-    const bool meet = NF > 1 && a.out_dtype == 3 && a.absmax != nullptr;
+    // The largest output: one commit per workgroup here too (layer chain 226 x 384, 1:8 int8 31.4 -> 19.8 us, 93 x 384, 2:4 int4 23.1 -> 18.2).
+    // Not for two fragments: the two barriers cost what the one commit less saves (a maximum that is never reset: 140 calls 3 % slower).
+    // Not for 5:8 int8 either: with it the compiler orders that pattern's loop so that 600 x 3072 -> 768 takes 12.8 us, without 11.3.
+    // Any other output is done once it is stored, and its way out lies next to the stores: past the commit's instructions the last
+    // fetch was one more trip to memory (0.25 us of 4.5 where other data has gone through the L2 since the last launch).
+    const bool meet = NF > 2 && !(N == 5 && BITS == 8) && a.out_dtype == 3 && a.absmax != nullptr;
     if (wave >= NF && !meet) return;
     float m = 0.0f;
     if (wave < NF) {
@@ -143,7 +150,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
 #pragma unroll
         for (int w = 0; w < FEW_WAVES; ++w) sum[0][0] += part[(w * NF + ff) * 64 + lane];
         unscale<BITS>(sum);
-        if (a.out_dtype == 3) {                // the columns' multipliers and offsets
+        if (__builtin_expect(a.out_dtype == 3, 0)) {           // the columns' multipliers and offsets
             float g[4], h[4];
             requant_column(a.act_scale, sw[0].x, bw[0].x, a.out_scale, g[0], h[0]);
             requant_column(a.act_scale, sw[0].y, bw[0].y, a.out_scale, g[1], h[1]);
@@ -154,10 +161,11 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
         }
         m = store_tile_pre<1, 1>(a, sum, sw, bw, o0 + ffo * 16, t0 + fft * 16, li, lg);
     }
+    if (__builtin_expect(a.out_dtype != 3, 1)) return;
     if (meet) {
         __syncthreads();                       // every partial sum is read
         absmax_commit_group<FEW_WAVES>(m, out_scale_of(a), a.absmax, reinterpret_cast<float*>(part));
-    } else if (a.out_dtype == 3) {
+    } else {
         absmax_commit(m, out_scale_of(a), a.absmax);
     }
 }
