@@ -31,6 +31,7 @@ void canonical_dense(int& N, int& M)
 
 std::atomic<int> g_forced_tile{0};
 std::atomic<int> g_last_tile{0};
+thread_local nm::GemmPlan* t_plan = nullptr;
 std::atomic<int> g_project_patience{4096};     // a few milliseconds
 
 }  // namespace
@@ -38,7 +39,12 @@ std::atomic<int> g_project_patience{4096};     // a few milliseconds
 namespace nm {
 int project_patience() { return g_project_patience.load(std::memory_order_relaxed); }
 int forced_gemm_tile() { return g_forced_tile.load(std::memory_order_relaxed); }
-void note_gemm_tile(int cfg) { g_last_tile.store(cfg, std::memory_order_relaxed); }
+void note_gemm_tile(int cfg)
+{
+    if (t_plan) t_plan->tile = cfg;
+    else g_last_tile.store(cfg, std::memory_order_relaxed);
+}
+GemmPlan* planned_gemm() { return t_plan; }
 }
 
 extern "C" {
@@ -66,6 +72,22 @@ int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits)
     nm::GemmArgs a = {};
     a.tokens = tokens; a.K = K; a.O = O; a.N = N; a.M = M; a.bits = bits;
     return nm::few_tile(&a, 1);
+}
+
+int nm_test_gemm_plan(int tokens, int K, int O, int N, int M, int bits, int out_dtype, int* k_starts)
+{
+    if (check_pattern(O, K, N, M, bits, NM_LAYOUT_TILED) || tokens <= 0) return NM_ERR_DIM;
+    canonical_dense(N, M);
+    nm::GemmArgs a = {};
+    a.tokens = tokens; a.K = a.ldx = K; a.O = a.ldo = O; a.N = N; a.M = M; a.bits = bits; a.out_dtype = out_dtype;
+    a.pv = nm::packed_values(K, N, M, bits, NM_LAYOUT_TILED);
+    a.pm = nm::packed_meta(K, N, M, NM_LAYOUT_TILED);
+    nm::GemmPlan plan = {0, 0};
+    t_plan = &plan;
+    const bool takes = nm::launch_gemm_dma(&a, 1, nullptr, 0);
+    t_plan = nullptr;
+    *k_starts = plan.k_starts;
+    return takes ? plan.tile : 0;
 }
 
 int nm_bench_smfmac_probe(int blocks, int iters, unsigned long long* counters_dev, void* hip_stream)
@@ -220,7 +242,7 @@ int gemm_args(nm::GemmArgs& a, const int8_t* X_dev, int tokens, int K, int ldx, 
     a.pm = nm::packed_meta(K, N, M, layout);
     a.bias = bias_dev; a.ldo = ldo;
     a.store_through = 0;
-    a.k_rotate = 0;
+    a.k_starts = 0;
     a.out_scale = 1.0f;
     a.out_scale_dev = nullptr;
     a.absmax = nullptr;

@@ -349,7 +349,7 @@ __device__ __forceinline__ void unscale(v4i (&acc)[FO][FT])
 __device__ __forceinline__ void fetch_now(GemmArgs& a)
 {
     asm volatile("" : "+s"(a.X), "+s"(a.vals), "+s"(a.meta), "+s"(a.scales), "+s"(a.bias), "+s"(a.tokens), "+s"(a.K),
-                      "+s"(a.ldx), "+s"(a.O), "+s"(a.k_rotate), "+s"(a.out), "+s"(a.acc), "+s"(a.out_dtype), "+s"(a.ldo),
+                      "+s"(a.ldx), "+s"(a.O), "+s"(a.k_starts), "+s"(a.out), "+s"(a.acc), "+s"(a.out_dtype), "+s"(a.ldo),
                       "+s"(a.store_through), "+s"(a.out_scale));
 }
 

@@ -108,13 +108,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
     const uint8_t* sbase[PER_WAVE];
     uint32_t stepb[PER_WAVE];                  // bytes per stage along the source row
     // Workgroups walk K in rotated order: stage j of this workgroup is K block (kstart + j) mod ns (integer sums do
-    // not care).  The tiles of one token row (consecutive workgroups of an XCD) start a.k_rotate blocks apart, the
-    // first one in the lead, so that what the leader has fetched is in the XCD's L2 when the others come to it:
-    // started together they all miss on the same lines at once, started far apart the L2 has lost the lines by then
-    // (eight token tiles of 256 x 4096 are twice its size).  With a CU to itself a tile also starts one block on from the
-    // token row before it, which spreads the reads of the packed weights; two-stage tiles do without (the int8 chain at
-    // 12288 tokens 111 us with it, 109 without).
-    const int kstart = (int)(((STAGES > 2 ? (unsigned)(tile / tiles_o) : 0u) + (unsigned)(ns - 1) * (unsigned)a.k_rotate * (unsigned)(tile % tiles_o)) % (unsigned)ns);
+    // not care).  What lies between the starts of neighbouring tiles is the launcher's choice (k_starts).
+    const int kstart = a.k_starts == 0 ? 0 :
+        (int)(((unsigned)(tile / tiles_o) * ((unsigned)a.k_starts >> 16) + (unsigned)(tile % tiles_o) * ((unsigned)a.k_starts & 0xFFFFu)) % (unsigned)ns);
     const int rb_last = (a.O + 15) / 16 - 1;   // last row block of the packed arrays
     const uint32_t lds_mine = (uint32_t)(uintptr_t)smem + (uint32_t)wave_u * 1024u;
 #pragma unroll
@@ -643,9 +639,42 @@ gemm_dma_batch_kernel(const GemmBatch p)
     gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU>(a, p.tiles_o[item], tile - p.first_tile[item]);
 }
 
+// K blocks between the starts of neighbouring tiles, token rows in the upper 16 bits, column tiles in the lower 16.  The column
+// tiles of one token row, consecutive workgroups of an XCD, start some blocks before one another, so that what the first has fetched
+// is in the XCD's L2 when the others come to it: started together they all miss on the same lines at once, started far
+// apart the L2 has lost the lines by then.
+// Measured on 700 shapes (six patterns, 1100 to 49152 tokens, K 384 to 4096), operands in the last-level cache and in HBM,
+// against starts 7 tiles apart with more than 256 tiles and none with fewer, mean / worst of time over time:
+//   one round of tiles: any rotation costs where the operands are in the last-level cache, because all column tiles then ask for lines of their own
+//   at once (one block 1.002 to 1.016 / 1.06, two 1.003 to 1.02 / 1.09), and all but three tiles gain next to nothing from HBM.  The three: 128 x 96 by four
+//   wavefronts, one block: HBM 0.975 / 1.01, cache 1.001 / 1.02; with two slices a stage, two blocks: 0.885 / 0.91 and 1.004 / 1.03.
+//   Several rounds on CUs of their own: one block, token rows one block too: 0.72 (49152 x 4096 -> 1024, 187 -> 131 us) to 1.00 / 1.04.  Reductions of 2048
+//   and more on 128 x 96 and on 128 columns of more than 128 tokens lose up to 13 % by that from HBM (49152 x 2560 -> 640 82.6 and 93.6 us), three
+//   blocks do not: 0.98 / 1.06.
+//   Two-stage tiles of 128 x 192: one block, rows one block: HBM 0.991 / 1.03, cache 0.995 / 1.04; dense 4-bit codes without the rows 0.994 / 1.04 (with
+//   them 1.013 / 1.07); two blocks 1.01 / 1.12.  Of 128 x 256: three blocks, rows one: HBM 0.969 / 1.02, cache 0.980 / 1.03 (two without rows 0.986 / 1.09).
+template <bool DUAL, int BT, int BO, int NW, int STAGES, int KU>
+int k_starts(bool one_round, int K)
+{
+    const int ns = K / (128 * KU);
+    int row = 0, column = 0;
+    if (STAGES > 2 && one_round) {
+        column = KU == 2 ? 2 : BT == 128 && BO == 96 && NW == 4 ? 1 : 0;
+    } else if (STAGES > 2) {
+        row = 1;
+        column = K >= 2048 && ((BT == 128 && BO == 96) || (BT > 128 && BO == 128)) ? 3 : 1;
+    } else if (!one_round) {
+        row = DUAL ? 0 : 1;
+        column = BO == 256 ? 3 : 1;
+    }
+    column = (ns - column % ns) % ns;          // (a start before is one ns - column after)
+    return column <= 0xFFFF ? (row % ns) << 16 | column : 0;
+}
+
 template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU, bool BATCHABLE = false>
 bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
 {
+    using U = Unit<N, M, BITS>;
     using G = DmaGeom<N, M, BITS, BT, BO, KU>;
     constexpr int NW = WAVES_T * WAVES_O;
     constexpr int PER_WAVE = (G::BLOCKS + NW - 1) / NW;
@@ -679,18 +708,13 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
     // (measured at 4096 tokens: equal at 12.6 MB, 17 % faster at 18.9 MB, slower below), int8
     // codes from 8 MB (9.4 MB: 11.4 -> 10.4 us, 12.6 MB: 12.5 -> 11.8 us, 50 MB: 56.9 -> 52.9 us);
     // fp32 always is, in the kernel.
-    // K blocks between the starts of neighbouring column tiles (see the kernel).  Against starts 7 tiles apart with
-    // more than 256 tiles and none with fewer, us, operands in the last-level cache / in HBM, [tile]:
-    //   one block, several rounds of tiles on CUs of their own: 49152 x 4096 -> 1024 200 -> 123 / 189 -> 130 [256 x 256]
-    //   (two blocks the same), 49152 x 1024 -> 4096 188 -> 177 / 186 -> 180 (two: 189 / 188);
-    //   two blocks, two-stage rings: 49152 x 1024 -> 1024 60 -> 49 / 58 -> 49 [128 x 256] (one: 59 / 58), 24576 x 4096 ->
-    //   1024 98 -> 85 / 99 -> 83 (one: 88 / 86), 4096 x 768 -> 2304 10.4 -> 10.2 / 11.6 -> 10.6 [128 x 192] (one: the same);
-    //   two blocks, one round: 4096 x 3072 -> 768 11.8 -> 11.9 / 15.4 -> 13.6 [128 x 96] (one: 11.7 / 14.5), 3001 x 3072 -> 768
-    //   11.0 -> 11.3 / 15.0 -> 12.4, 4096 x 768 -> 768 6.3 -> 6.4 / 7.5 -> 7.0; the worst, 8192 x 3072 -> 768, 16.8 -> 18.3 / 23.6 -> 21.8
-    //   [256 x 96] (one: 17.8 / 22.5).  Operands that the L2s themselves hold: no difference.
     for (int i = 0; i < count; ++i) {
         b.item[i].store_through = out_bytes >= ((items[0].out_dtype == 3 ? 8ll : 14ll) << 20);
-        b.item[i].k_rotate = n_tiles > 256 && STAGES > 2 ? 1 : 2;
+        b.item[i].k_starts = k_starts<U::DUAL, BT, BO, NW, STAGES, KU>(n_tiles <= 256, items[i].K);
+    }
+    if (GemmPlan* plan = planned_gemm()) {
+        plan->k_starts = b.item[0].k_starts;
+        return true;
     }
     if constexpr (BATCHABLE) {
         if (count > 1) {

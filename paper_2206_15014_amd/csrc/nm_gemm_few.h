@@ -219,6 +219,7 @@ bool launch_few_tile(const GemmArgs* items, int count, hipStream_t st)
         b.tiles_o[i] = 0;
         b.first_tile[i + 1] = b.first_tile[count];
     }
+    if (planned_gemm()) return true;
     const int n_tiles = b.first_tile[count];
     const dim3 grid(8 * ((n_tiles + 7) / 8)), wg(64 * FEW_WAVES);
     if (count > 1) hipLaunchKernelGGL((gemm_few_batch_kernel<N, M, BITS, FT, FO>), grid, wg, 0, st, b);

@@ -88,7 +88,7 @@ struct GemmArgs {
     int out_dtype;         // nm_out_dtype; 3 = int8 codes (nm_gemm_q8)
     int ldo;
     int store_through;     // set by a launcher: output stores bypass the L2's write-back (large outputs)
-    int k_rotate;          // set by a launcher: K blocks between the starts of neighbouring column tiles
+    int k_starts;          // set by a launcher: K blocks between the starts of neighbouring token rows (upper 16 bits) and column tiles (lower 16)
     float out_scale;       // out_dtype 3: scale of the output codes
     const float* out_scale_dev;   // replaces out_scale when given
     float* absmax;         // out_dtype 3: max |y| is max-combined into it, or null
@@ -183,6 +183,9 @@ int forced_gemm_tile();
 // of the LDS-direct kernels, 1 .. 3 for the register-staged shapes, -1 for the kernel of the odd
 // shapes): read back by bench.py to group a step's launches by kernel.
 void note_gemm_tile(int cfg);
+// What a call would launch: while a test asks (nm_test_gemm_plan), the tiled-layout launchers of this thread fill it and launch nothing.
+struct GemmPlan { int tile, k_starts; };
+GemmPlan* planned_gemm();
 
 }  // namespace nm
 

@@ -62,6 +62,14 @@ int nm_test_gemm_any_reads(int tokens, int K, int ldx, int O, int N, int M, int 
  */
 int nm_test_project_patience(int turns);
 
+/*
+ * Test hook: the tile id that nm_gemm (out_dtype 3: nm_gemm_q8) would choose for one aligned call in the tiled layout, 0 where
+ * another kernel family takes it, and where its tiles would start on their walk along K: the distance between neighbouring token
+ * rows (upper 16 bits) and column tiles (lower 16) in K blocks of 128 columns (256 on tile 113), modulo their number.
+ * Host arithmetic only, nothing is launched.
+ */
+int nm_test_gemm_plan(int tokens, int K, int O, int N, int M, int bits, int out_dtype, int *k_starts);
+
 /* Test hook: the digest of the sources that the build made the library from, "unknown" where another way of compiling gave none. */
 const char *nm_test_source_digest(void);
 #ifdef __cplusplus
