@@ -639,6 +639,15 @@ gemm_dma_batch_kernel(const GemmBatch p)
     gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU>(a, p.tiles_o[item], tile - p.first_tile[item]);
 }
 
+// bf16 outputs of 14 MB and more (all items of the launch together) are written through
+// (measured at 4096 tokens: equal at 12.6 MB, 17 % faster at 18.9 MB, slower below), int8
+// codes from 8 MB (9.4 MB: 11.4 -> 10.4 us, 12.6 MB: 12.5 -> 11.8 us, 50 MB: 56.9 -> 52.9 us);
+// fp32 always is, in the kernel.
+inline bool written_through(int out_dtype, long long outputs)
+{
+    return outputs * (out_dtype == 3 ? 1 : 2) >= ((out_dtype == 3 ? 8ll : 14ll) << 20);
+}
+
 // K blocks between the starts of neighbouring tiles, token rows in the upper 16 bits, column tiles in the lower 16.  The column
 // tiles of one token row, consecutive workgroups of an XCD, start some blocks before one another, so that what the first has fetched
 // is in the XCD's L2 when the others come to it: started together they all miss on the same lines at once, started far
@@ -684,7 +693,7 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
     GemmBatch b;
     b.count = count;
     b.first_tile[0] = 0;
-    long long out_bytes = 0;
+    long long outputs = 0;
     for (int i = 0; i < count; ++i) {
         const GemmArgs& a = items[i];
         if ((a.K / 128) % KU != 0) return false;
@@ -695,7 +704,7 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
         if ((long long)b.first_tile[i] + (long long)tiles_t * b.tiles_o[i] > 0x7FFFFFF0ll) return false;
         b.first_tile[i + 1] = b.first_tile[i] + tiles_t * b.tiles_o[i];
         b.item[i] = a;
-        out_bytes += (long long)a.tokens * a.O * (a.out_dtype == 3 ? 1 : 2);
+        outputs += (long long)a.tokens * a.O;
     }
     for (int i = count; i < GEMM_BATCH_MAX; ++i) {      // unused slots: defined values
         b.item[i] = items[0];
@@ -704,12 +713,8 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
     }
     const int n_tiles = b.first_tile[count];
     const int grid = 8 * ((n_tiles + 7) / 8);
-    // bf16 outputs of 14 MB and more (all items of the launch together) are written through
-    // (measured at 4096 tokens: equal at 12.6 MB, 17 % faster at 18.9 MB, slower below), int8
-    // codes from 8 MB (9.4 MB: 11.4 -> 10.4 us, 12.6 MB: 12.5 -> 11.8 us, 50 MB: 56.9 -> 52.9 us);
-    // fp32 always is, in the kernel.
     for (int i = 0; i < count; ++i) {
-        b.item[i].store_through = out_bytes >= ((items[0].out_dtype == 3 ? 8ll : 14ll) << 20);
+        b.item[i].store_through = written_through(items[0].out_dtype, outputs);
         b.item[i].k_starts = k_starts<U::DUAL, BT, BO, NW, STAGES, KU>(n_tiles <= 256, items[i].K);
     }
     if (GemmPlan* plan = planned_gemm()) {
@@ -816,6 +821,7 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
     // 4096 tokens: 2:4 int4 14.6 -> 13.0 us, 2:8 int8 15.0 -> 13.0, dense int4 18.7 -> 15.7); 1:4 int8
     // and dense int8 measure equal either way and keep 128 x 96.
     constexpr bool NARROW_ONCE = !U::IDENTITY && !(N == 1 && M == 4 && BITS == 8) && !(N == M && BITS == 8);
+    constexpr bool NARROW_4 = BITS == 4 && M == 4 && N != 3;
     constexpr bool WIDE24 = (BITS == 4 && ((N == 3 && M == 4) || (N == 4 && M == 8)));
     if (cfg == 0) {
         // Cost of a tile shape = rounds over the 256 CUs x tile area x the shape's cost per
@@ -850,6 +856,7 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         }
         const long long n96 = (long long)((a.tokens + 127) / 128) * ((a.O + 95) / 96);
         const long long n128 = (long long)((a.tokens + 127) / 128) * ((a.O + 127) / 128);
+        const bool through = a.out_dtype >= 2 && written_through(a.out_dtype, (long long)a.tokens * a.O);
         const long long n64x96 = (long long)((a.tokens + 63) / 64) * ((a.O + 95) / 96);
         const long long n64x48 = (long long)((a.tokens + 63) / 64) * ((a.O + 47) / 48);
         // A problem of fewer than 128 tiles of 128 x 96 leaves half the chip idle while every workgroup
@@ -858,19 +865,20 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
         // do not come here: see few_tile.
         if (!U::DUAL && n96 < 128 && n64x48 <= 256) cfg = 130;
         else if (!U::DUAL && n96 < 128 && n64x96 <= 256 && count == 1) cfg = 132;
-        // 4-bit codes in groups of four (2:4, 1:4, dense) decode so cheaply since they are multiplied as 16 times their value
-        // that decoding once is worth less than tiles that fit: four wavefronts on 128 x 96 where 96 divides the width (768
-        // wide, 1024 to 24576 tokens, K 768 and 3072: 0.79 to 1.01 of the time of decoding once; 512, 640 and 1024 wide 0.94 to 1.3),
-        // 128 x 128 by eight wavefronts 4 x 2 from 448 tiles on (8192 x 1024 -> 1024 15.1 -> 12.6 us, 24576 x 2048 -> 512
-        // 39 -> 28.5; 376 tiles, 6000 x 1024 -> 1024: 12.2 and 12.5; K = 4096: equal).
-        // Up to two rounds of 128 columns, 96 do not pay where they need one more (6000 x 384 -> 576: 235 and 282 tiles, 6.1 and 6.6 us;
-        // 16000 -> 480: 500 and 625, 8.3 and 10.2; a fourth for a third is repaid, 16000 -> 768: 15.9 and 13.2), nor where 128 divides
-        // the width too and all is one round (9000 -> 384: 5.8 and 6.6).  Of two rounds, int8 codes are best decoded once (12000 x 384 ->
-        // 576: 8.1 and 9.3 with 4 x 2 wavefronts; bf16 16000 -> 480: 10.9 and 9.1).
-        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.O % 96 == 0 &&
-                 (n128 > 512 || (n96 + 255) / 256 <= (n128 + 255) / 256) && (a.O % 128 != 0 || n128 > 256)) cfg = 115;
-        else if (BITS == 4 && M == 4 && N != 3 && count == 1 && a.O <= 1024 && a.K <= 2048 && n128 >= 448 &&
-                 (n128 > 512 || a.out_dtype != 3)) cfg = 117;
+        // 4-bit codes in groups of four (2:4, 1:4, dense) on outputs up to 1024 wide decode so cheaply since they are multiplied as 16 times
+        // their value that decoding once [127] is worth less than a tile that fits.  Measured: 2:4, 1:4 and dense, 192 to 1024 wide, 1100 to
+        // 24576 tokens, K 384 to 4096, operands in the last-level cache and in HBM, time over that of 127:
+        //  - 128 x 96 by four wavefronts [115] where 96 divides the width and takes no more rounds than 128 columns do, or there are more than two rounds:
+        //    0.81 to 0.97 (6000 -> 768 in two rounds: 0.92; with one round more than 128 columns 1.2 to 1.26: 9000 -> 768, 6000 -> 576).  In one
+        //    round the two are equal: cache 1.00 to 1.09, HBM 0.93 to 0.97, so 128 columns keep the widths that they divide too.
+        //  - 127 stores sixteen columns per wavefront, which goes badly where bf16 or codes are written through: there 128 x 128 by eight wavefronts 4 x 2
+        //    [117] up to K = 2048, 0.66 at K = 384 (8192 x 384 -> 1024 to codes 17.6 -> 8.4 us), 0.8 at 768 and 1024, 0.95 at 2048.  Against 128 x 96 there:
+        //    0.89 at K = 384, 1.00 from 768 on, 0.8 to 0.97 up to K = 2048 where 128 divides the width and 96 takes a round more.
+        //    At smaller outputs it is behind 127 (1.07 to 1.15), and so it is at fp32 (1.05 to 1.12 at any size).
+        else if (NARROW_4 && count == 1 && a.O <= 1024 && a.O % 96 == 0 &&
+                 ((n96 + 255) / 256 <= (n128 + 255) / 256 || (n128 > 512 && !(through && a.O % 128 == 0 && a.K <= 2048))) &&
+                 (a.O % 128 != 0 || (n128 > 256 && !(through && a.K < 768)))) cfg = 115;
+        else if (NARROW_4 && count == 1 && a.O <= 1024 && through && a.K <= 2048) cfg = 117;
         else if (NARROW_ONCE && count == 1 && ((DECODE_BOUND && ALWAYS_ONCE) || a.O <= 1024)) cfg = 127;
         else if (U::IDENTITY && count == 1 && n96 >= 256) cfg = modelled_tile(a);
         else if (pick == 122 && WIDE24) cfg = count == 1 ? 126 : (N == 3 ? 117 : 122);

@@ -1,4 +1,5 @@
-"""What nm_gemm would launch in the tiled layout, read back without a GPU: where the tiles of a launch start on their walk along K."""
+"""What nm_gemm would launch in the tiled layout, read back without a GPU: the tile of narrow 4-bit layers, and where the tiles of a
+launch start on their walk along K."""
 import ctypes
 
 import pytest
@@ -37,3 +38,21 @@ def test_starts_are_the_launchs_own():
     for K in (128, 256, 384):
         tile, row, column = plan(49152, K, 1024, "2:4/8")
         assert 0 <= row < K // 128 and 0 <= column < K // 128
+
+
+@pytest.mark.parametrize("tokens, K, O, out, tile", [
+    # one round: 128 columns by eight wavefronts side by side where they divide the width, 128 x 96 where 96 alone does
+    (4096, 768, 768, BF16, 127), (4096, 3072, 768, CODES, 127), (8192, 768, 384, BF16, 127), (4096, 768, 576, BF16, 115), (5000, 768, 480, F32, 115),
+    # 96 columns take no more rounds than 128 / one more
+    (6000, 384, 768, BF16, 115), (8192, 3072, 768, F32, 115), (5000, 768, 768, BF16, 127), (6000, 384, 576, BF16, 127), (9000, 768, 768, CODES, 127),
+    (12288, 768, 576, BF16, 127), (24576, 768, 768, F32, 115),
+    # written through (16-bit outputs from 14 MB, codes from 8): 128 x 128 by 4 x 2 wavefronts up to K = 2048, but where 96 is as good
+    (8192, 384, 1024, CODES, 117), (8192, 2048, 896, BF16, 117), (12288, 1024, 640, BF16, 117), (12288, 1024, 640, CODES, 127), (8191, 384, 1024, CODES, 127),
+    (8192, 2176, 1024, BF16, 127), (16000, 768, 768, BF16, 117), (12288, 640, 768, BF16, 117), (12288, 768, 768, BF16, 115), (16000, 3072, 768, BF16, 115),
+    (24576, 768, 480, CODES, 115),
+    # fp32 is always written through, sixteen columns at a time as well as any: never 117
+    (24576, 384, 1024, F32, 127), (12288, 768, 640, F32, 127),
+])
+@pytest.mark.parametrize("scheme", ["2:4/4", "1:4/4", "4:4/4"])
+def test_tile_of_narrow_4_bit_layers(tokens, K, O, out, tile, scheme):
+    assert plan(tokens, K, O, scheme, out)[0] == tile
