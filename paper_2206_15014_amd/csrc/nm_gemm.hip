@@ -324,11 +324,14 @@ int few_tile(const GemmArgs* items, int count)
 
 bool launch_gemm_dma(const GemmArgs* items, int count, hipStream_t st, int cfg)
 {
-    for (int i = 0; i < count; ++i)            // (a reduction of 131072 kept 4-bit weights and more: gemm_any_kernel)
-        if (items[i].bits == 4 && (long long)items[i].K / items[i].M * items[i].N > SCALED_MOST_KEPT) return false;
     static GemmSet* const rings[] = {NM_SETS(launch_gemm_dma_set)};
     static GemmSet* const fews[] = {NM_SETS(launch_gemm_few_set)};
-    const int few = cfg == 0 ? few_tile(items, count) : cfg >= 141 && cfg <= 144 ? cfg : 0;
+    int few = cfg == 0 ? few_tile(items, count) : cfg >= 141 && cfg <= 144 ? cfg : 0;
+    for (int i = 0; i < count; ++i) {
+        if (items[i].bits != 4 || kept_entries(items[i]) <= SCALED_MOST_KEPT) continue;
+        if (kept_in_slices(items[i], (items[i].K / 128 + 7) / 8) > SCALED_MOST_KEPT) few = 0;     // (a wavefront's share)
+        if (!few && count > 1) return false;   // one by one
+    }
     for (GemmSet* const set : few ? fews : rings)
         if (set(items, count, st, few ? few : cfg)) return true;
     return false;

@@ -242,7 +242,8 @@ struct Unit {
     // other against the same activations.  Of the (up to four) entries a subgroup keeps, operand
     // 1 takes the first two and operand 2 the rest, zero where there is none.  The sparse
     // instruction at twice its issue count does the work of the dense one at the same rate, and
-    // the whole staging path stays as it is.  4-bit codes come out times 16 (see decode).
+    // the whole staging path stays as it is.  SCALED as in decode.
+    template <bool SCALED>
     static __device__ __forceinline__ void decode2(const Raw& r, v4i& c1, int& p1, v4i& c2, int& p2)
     {
         static_assert(DUAL, "patterns with more than two kept entries per group");
@@ -251,7 +252,7 @@ struct Unit {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
                 uint32_t lo, hi;
-                nibbles<true>(r.v[d], lo, hi);
+                nibbles<SCALED>(r.v[d], lo, hi);
                 c1[d] = (int)lo;
                 c2[d] = (int)hi;
             }
@@ -268,7 +269,7 @@ struct Unit {
 #pragma unroll
             for (int d = 0; d < (EPU + 7) / 8; ++d) {
                 uint32_t lo, hi;
-                nibbles<true>(r.v[d], lo, hi);
+                nibbles<SCALED>(r.v[d], lo, hi);
                 w[2 * d] = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
                 w[2 * d + 1] = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
             }
@@ -329,9 +330,12 @@ struct Unit {
 
 // 4-bit codes are multiplied as 16 times their value, which spares the sign extension (six of the nine to thirteen vector
 // operations per packed dword); the sums are 16 times the accumulator's value, exactly while kept entries x 16 x 8 x 128 stay below 2^31.
+// The few-token kernels undo it per wavefront, of which eight share a reduction; longer ones go to a tile that extends the signs.
 // A dense 4-bit unit is 12 operations instead of 52, and its tiles were bound by them: 4096 x 768 -> 3072 19.1 -> 14.7 us, -> 2304 17.6 -> 13.9;
 // 2:4 int4 12.0 -> 11.3 and, 3072 -> 768, 16.0 -> 15.3; 1:4 int4 3 %, 2:8 int4 1 to 3 %.
 constexpr long long SCALED_MOST_KEPT = (1ll << 31) / (16 * 8 * 128) - 1;
+inline long long kept_in_slices(const GemmArgs& a, int slices) { return 128ll * slices / a.M * a.N; }
+inline long long kept_entries(const GemmArgs& a) { return (long long)a.K / a.M * a.N; }
 template <int BITS, int FO, int FT>
 __device__ __forceinline__ void unscale(v4i (&acc)[FO][FT])
 {

@@ -48,7 +48,8 @@ namespace {
 // KU = 128-column slices per stage (1 or 2): two slices per stage halve the barriers per column
 // at the price of a coarser ring.  In the tiled layout consecutive slices of a row block are
 // adjacent in memory, so either way every direct load fetches whole 128-byte lines.
-template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU>
+// SCALED: 4-bit codes are multiplied as 16 times their value (see unscale).
+template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU, bool SCALED>
 __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles_o, const int tile)
 {
     using U = Unit<N, M, BITS>;
@@ -241,7 +242,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
         constexpr int fo = decltype(foc)::value;
         if constexpr (U::DUAL) {
             v4i c1, c2; int p1, p2;
-            U::decode2(w, c1, p1, c2, p2);
+            U::template decode2<SCALED>(w, c1, p1, c2, p2);
 #pragma unroll
             for (int ft = decltype(ft0)::value; ft < decltype(ft1)::value; ++ft) {
                 acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(c1, bsrc[ft], acc[fo][ft], p1, 0, 0);
@@ -249,7 +250,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
             }
         } else {
             v4i codes; int pos;
-            U::template decode<true>(w, codes, pos);
+            U::template decode<SCALED>(w, codes, pos);
 #pragma unroll
             for (int ft = decltype(ft0)::value; ft < decltype(ft1)::value; ++ft)
                 acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(codes, bsrc[ft], acc[fo][ft], pos, 0, 0);
@@ -428,7 +429,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
         });
     }
 
-    unscale<BITS>(acc);
+    if constexpr (SCALED) unscale<BITS>(acc);
     // ---- epilogue: Eq. 4 with offset 0 on the product of two quantised operands --------------
     // The MFMA leaves each lane with 4 consecutive outputs of one token, so a plain store would
     // write 8-byte (bf16) pieces, 32 contiguous bytes per token and instruction.  Exact
@@ -609,7 +610,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
 
 // One GEMM per launch.  Workgroup -> tile: each XCD (workgroups are dealt to the eight XCDs in
 // turn) takes a contiguous run of tiles, so that the CUs behind one L2 share token rows.
-template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU>
+template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU, bool SCALED>
 __global__ NM_RING_ALIGNED void __launch_bounds__(64 * WAVES_T * WAVES_O, STAGES == 2 ? 2 : 1)
 gemm_dma_kernel(const GemmArgs a_in, const int tiles_o, const int n_tiles)
 {
@@ -618,7 +619,7 @@ gemm_dma_kernel(const GemmArgs a_in, const int tiles_o, const int n_tiles)
     const int per_xcd = (n_tiles + 7) >> 3;
     const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (tile >= n_tiles) return;               // whole workgroup leaves before any barrier
-    gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU>(a, tiles_o, tile);
+    gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU, SCALED>(a, tiles_o, tile);
 }
 
 // Several GEMMs per launch (nm_gemm_batch): each workgroup first finds the item its tile belongs
@@ -636,7 +637,7 @@ gemm_dma_batch_kernel(const GemmBatch p)
     while (item + 1 < p.count && tile >= p.first_tile[item + 1]) ++item;
     GemmArgs a = p.item[item];
     fetch_now(a);
-    gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU>(a, p.tiles_o[item], tile - p.first_tile[item]);
+    gemm_dma_tile<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU, true>(a, p.tiles_o[item], tile - p.first_tile[item]);
 }
 
 // bf16 outputs of 14 MB and more (all items of the launch together) are written through
@@ -680,7 +681,7 @@ int k_starts(bool one_round, int K)
     return column <= 0xFFFF ? (row % ns) << 16 | column : 0;
 }
 
-template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU, bool BATCHABLE = false>
+template <int N, int M, int BITS, int BT, int BO, int WAVES_T, int WAVES_O, int STAGES, int KU, bool BATCHABLE = false, bool SCALED = true>
 bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
 {
     using U = Unit<N, M, BITS>;
@@ -732,7 +733,7 @@ bool launch_dma_tile(const GemmArgs* items, int count, hipStream_t st)
             return true;
         }
     }
-    auto kern = gemm_dma_kernel<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU>;
+    auto kern = gemm_dma_kernel<N, M, BITS, BT, BO, WAVES_T, WAVES_O, STAGES, KU, SCALED>;
     if (lds > 64 * 1024) {
         static std::atomic<uint64_t> raised{0};   // per instantiation
         raise_lds_limit(reinterpret_cast<const void*>(kern), lds, raised);
@@ -821,6 +822,14 @@ bool launch_dma_pattern(const GemmArgs* items, int count, hipStream_t st, int cf
     // 4096 tokens: 2:4 int4 14.6 -> 13.0 us, 2:8 int8 15.0 -> 13.0, dense int4 18.7 -> 15.7); 1:4 int8
     // and dense int8 measure equal either way and keep 128 x 96.
     constexpr bool NARROW_ONCE = !U::IDENTITY && !(N == 1 && M == 4 && BITS == 8) && !(N == M && BITS == 8);
+    // Sums that 16 times the codes could carry past 32 bits: one tile that extends the signs, whatever variant a test forces.
+    // 4096 x 262144 -> 1024, 2:4: 2.5 ms on the kernel of the odd shapes, 0.95 here.
+    if constexpr (BITS == 4) {
+        if (kept_entries(items[0]) > SCALED_MOST_KEPT) {
+            note_gemm_tile(127);
+            return launch_dma_tile<N, M, BITS, 128, 128, 1, 8, 3, 1, false, false>(items, count, st);
+        }
+    }
     constexpr bool NARROW_4 = BITS == 4 && M == 4 && N != 3;
     constexpr bool WIDE24 = (BITS == 4 && ((N == 3 && M == 4) || (N == 4 && M == 8)));
     if (cfg == 0) {

@@ -93,7 +93,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
             for (int fo = 0; fo < FO; ++fo) {
                 if constexpr (U::DUAL) {
                     v4i c1, c2; int p1, p2;
-                    U::decode2(w[i][fo], c1, p1, c2, p2);
+                    U::template decode2<true>(w[i][fo], c1, p1, c2, p2);
 #pragma unroll
                     for (int ft = 0; ft < FT; ++ft) {
                         acc[fo][ft] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(c1, b[i][ft], acc[fo][ft], p1, 0, 0);
@@ -132,6 +132,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
         for (int k0 = 0; k0 < nk; k0 += DEEP * FEW_WAVES) walk(std::integral_constant<int, DEEP>{}, k0 + wave);
     }
 
+    unscale<BITS>(acc);
 #pragma unroll
     for (int fo = 0; fo < FO; ++fo)
 #pragma unroll
@@ -149,7 +150,6 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
         v4i sum[1][1] = {{v4i{0, 0, 0, 0}}};
 #pragma unroll
         for (int w = 0; w < FEW_WAVES; ++w) sum[0][0] += part[(w * NF + ff) * 64 + lane];
-        unscale<BITS>(sum);
         if (__builtin_expect(a.out_dtype == 3, 0)) {           // the columns' multipliers and offsets
             float g[4], h[4];
             requant_column(a.act_scale, sw[0].x, bw[0].x, a.out_scale, g[0], h[0]);

@@ -56,3 +56,13 @@ def test_starts_are_the_launchs_own():
 @pytest.mark.parametrize("scheme", ["2:4/4", "1:4/4", "4:4/4"])
 def test_tile_of_narrow_4_bit_layers(tokens, K, O, out, tile, scheme):
     assert plan(tokens, K, O, scheme, out)[0] == tile
+
+
+@pytest.mark.parametrize("K, few", [
+    (2 * 131072 - 128, True), (2 * 131072, True),           # a wavefront of the few-token kernels walks an eighth of the reduction
+    (8 * 2047 * 128, True), (8 * 2047 * 128 + 128, False),  # ... and 131072 kept entries from here on
+])
+def test_longest_4_bit_reductions_stay_on_matrix_tiles(K, few):
+    assert plan(300, K, 768, "2:4/4")[0] == (142 if few else 127)
+    assert plan(2, K, 16, "2:4/4")[0] == (141 if few else 127)
+    assert plan(2048, K, 1024, "2:4/4")[0] == 127 and plan(2048, K, 1024, "4:4/4")[0] == 127      # (2048 rows of X: its offsets are 32 bits wide)

@@ -41,3 +41,26 @@ def test_longest_reductions(K):
                acc=acc, layout=nm.NM_LAYOUT_TILED)
     want = np.array([[K // 2 * 8 * 128] * O, [K // 2 * -8 * 127] * O], np.int64)
     assert np.array_equal(acc.cpu().numpy().astype(np.int64), want)
+
+
+# (One column of codes -8 a row against activations of -128 and 127.)  Past the few-token kernels' eight shares, and many tokens past
+# the limit of one share: a tile that extends the signs
+@pytest.mark.parametrize("N, M, T, K, O", [(2, 4, 2, 8 * 2047 * 128, 16), (2, 4, 2, 8 * 2047 * 128 + 128, 16), (2, 4, 2100, 2 * 131072, 256),
+                                           (4, 4, 1030, 131072 + 128, 520), (1, 8, 140, 8 * 131072, 1040), (5, 8, 1030, 8 * 26240, 520)])
+def test_longest_reductions_on_matrix_tiles(N, M, T, K, O):
+    pieces = nm.nm_packed_sizes(O, K, N, M, 4, nm.NM_LAYOUT_TILED)
+    vals = torch.full((pieces[0],), 0x88, dtype=torch.uint8, device="cuda")
+    if M == 8 and N == 5:                                              # offsets 0 1 2 3 4 | 0 1 2 3 4: whole groups from the oracle's own packing
+        W = np.tile(np.array([-7, -7, -7, -7, -7, 0, 0, 0], np.float32), (16, 128 // 8))
+        _, m, _ = oracle.compress(W, N, M, 4)
+        _, tiled = oracle.to_tiled(np.zeros((16, 128 // 8 * 5 // 2), np.uint8), m, 128, N, M, 4)
+        meta = torch.from_numpy(np.tile(tiled.reshape(-1), pieces[1] // tiled.size)).cuda()
+    else:
+        meta = torch.full((max(pieces[1], 1),), {(2, 4): 0x44, (4, 4): 0, (1, 8): 0}[N, M], dtype=torch.uint8, device="cuda")
+    X = torch.full((T, K), -128, dtype=torch.int8, device="cuda")
+    X[1::2] = 127
+    acc = torch.empty((T, O), dtype=torch.int32, device="cuda")
+    nm.nm_gemm(X, 1.0, vals, meta, torch.ones(O, device="cuda"), O, N, M, 4, acc=acc, layout=nm.NM_LAYOUT_TILED)
+    assert nm.binding.raw().nm_bench_last_gemm_tile() > 0
+    kept = K // M * N
+    assert torch.equal(acc[0::2], torch.full_like(acc[0::2], kept * 8 * 128)) and torch.equal(acc[1::2], torch.full_like(acc[1::2], -kept * 8 * 127))
