@@ -8,8 +8,10 @@
  * Ownership and execution model (all entry points):
  *   - every *_dev pointer is DEVICE memory owned by the caller; the library
  *     allocates nothing and never frees anything; the only device memory of its
- *     own is the fixed scratch array of nm_scale_search_static (see there), and no
- *     result depends on anything an earlier call left behind;
+ *     own, static and per GPU, is the scratch array of nm_scale_search_static
+ *     (NM_SCALE_SEARCH_STATIC_MAX_BYTES) and the array through which the workgroups
+ *     of an nm_project call exchange maxima (NM_PROJECT_EXCHANGE_BYTES; see both),
+ *     and no result depends on anything an earlier call left behind;
  *   - work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL =
  *     the default stream) and the call returns without synchronising;
  *   - buffers of one call must not overlap;
@@ -330,7 +332,15 @@ int nm_gemm_batch(const nm_gemm_item *items, int count,
  *                    one group hold the same value); it also serves as the call's scratch space.
  *   rows_per_scale   >= 1; the last group may be shorter.
  * Errors as for nm_compress (bits may also be 0 here).
+ *
+ * A scale group of several rows is the work of several workgroups of one launch, which tell one another their
+ * largest values through an array built into the library (static device memory, NM_PROJECT_EXCHANGE_BYTES per
+ * GPU).  A value carries its call's number there, so calls on any streams and threads may overlap, nothing has to
+ * be cleared, and a workgroup that waits too long for the others computes their values itself.  A call on a stream
+ * that is being captured (the call asks, hipStreamIsCapturing) or with U_out_dev = U_dev does without the array, in
+ * two or three launches.
  */
+#define NM_PROJECT_EXCHANGE_BYTES (2u << 20)
 int nm_project(const float *W_dev, const float *U_dev, int rows, int cols, int ldw,
                int N, int M, int bits, int rows_per_scale,
                float *Z_dev, float *U_out_dev, int ldz, float *scales_dev, void *hip_stream);

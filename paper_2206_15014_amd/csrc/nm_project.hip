@@ -26,6 +26,7 @@
 
 #include <type_traits>
 
+#include "nm.h"
 #include "nm_internal.h"
 
 #include <atomic>
@@ -34,6 +35,7 @@
 // call uses one region of the 64 in turn, a word per workgroup; should two calls in flight ever share one, words of the other call are
 // seen for what they are by their number.
 constexpr int MEET_REGIONS = 64, MEET_WORDS = 4096;
+static_assert(MEET_REGIONS * MEET_WORDS * sizeof(unsigned long long) == NM_PROJECT_EXCHANGE_BYTES, "as the header says");
 static __device__ unsigned long long meet_words[MEET_REGIONS * MEET_WORDS];
 
 namespace nm {

@@ -1,4 +1,6 @@
-"""What the library's kernel descriptors say about registers: no GEMM kernel keeps part of its state in scratch memory."""
+"""What the library's code objects say: no few-token kernel keeps part of its state in scratch memory, and the static device memory is what the
+header names."""
+import os
 import re
 import struct
 
@@ -31,3 +33,20 @@ def test_few_token_kernels_do_not_spill():
     kernels = {k: v for k, v in _scratch_bytes().items() if "gemm_few_" in k}
     assert len(kernels) == 22 * 8             # patterns and widths; four tiles, for one GEMM and for several
     assert not {k: v for k, v in kernels.items() if v}
+
+
+def test_device_memory_of_its_own_is_what_the_header_names():
+    """The library's static device arrays, from its code objects' zero-initialised sections, against the sizes in include/nm.h."""
+    header = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "nm.h")).read()
+    named = sorted(int(n) << int(shift) for n, shift in re.findall(r"#define NM_[A-Z_]+_BYTES \((\d+)u << (\d+)\)", header))
+    data, held = open(binding.library_path(), "rb").read(), []
+    for m in re.finditer(b"\x7fELF", data):
+        o = data[m.start():]
+        machine, table, size, count = struct.unpack_from("<H20xQ10xHH", o, 18)
+        if machine != 224:
+            continue
+        for i in range(count):
+            _, kind, flags, _, _, length = struct.unpack_from("<IIQQQQ", o, table + size * i)
+            if kind == 8 and flags & 2 and length > 4096:     # SHT_NOBITS, allocated
+                held.append(length >> 12 << 12)
+    assert sorted(held) == named
