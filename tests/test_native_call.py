@@ -16,6 +16,8 @@ T, K, O = 5, 32, 12
 @pytest.fixture()
 def recorder():
     lib = binding._load()
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        pytest.skip("no Python.h, so no marshalling module: the binding goes through ctypes alone")
     assert binding._native is not None, "the marshalling module is not built"
     seen = []
     proto = ctypes.CFUNCTYPE(ctypes.c_int, *lib.nm_gemm.argtypes)
@@ -91,3 +93,39 @@ def test_no_module_outlives_its_library(tmp_path):
     assert os.listdir(tmp_path) == ["_nm_other.so"]
     assert build.build_python_module(str(tmp_path), str(tmp_path / "made.so"), "no compiler is asked") is False
     assert os.listdir(tmp_path) == ["_nm_other.so"]
+
+
+@pytest.mark.parametrize("native", [False, True])
+@pytest.mark.parametrize("status", [0, -2])
+def test_entry_point_on_either_side(monkeypatch, status, native):
+    """nm_gemm itself, without the module (as where it is not built) and with one that leaves the call to ctypes."""
+    seen = []
+
+    class Lib:
+        @staticmethod
+        def nm_gemm(*args):
+            seen.append(args)
+            return status
+
+        @staticmethod
+        def nm_status_string(code):
+            return b"refused"
+
+    class LeavesIt:
+        @staticmethod
+        def gemm(*args):
+            return None
+
+    monkeypatch.setattr(binding, "_lib", Lib)
+    monkeypatch.setattr(binding, "_native", LeavesIt if native else None)
+    t = _tensors()
+    call = lambda: binding.nm_gemm(t["Xwide"], 0.25, t["vals"], t["meta"], t["scales"], O, 2, 4, 8, bias=t["bias"], out=t["out"], out_dtype=2, stream=16, layout=1)
+    if status:
+        with pytest.raises(binding.NMError) as e:
+            call()
+        assert e.value.code == status
+    else:
+        acc, out = call()
+        assert acc is None and out is t["out"]
+    assert seen[0] == (t["Xwide"].data_ptr(), T, K, 2 * K, 0.25, None, t["vals"].data_ptr(), t["meta"].data_ptr(), t["scales"].data_ptr(), O, 2, 4, 8, 1,
+                       t["bias"].data_ptr(), None, t["out"].data_ptr(), 2, O + 4, 16)
