@@ -1,5 +1,5 @@
 """4-bit weights are multiplied as 16 times their value in the tiled-layout kernels: exact sums at the largest magnitudes the codes
-have, on both sides of the reduction length up to which 16 times the sum fits 32 bits, and at the sizes where the tile choice changes."""
+have, on both sides of the reduction length up to which 16 times the sum fits 32 bits, and on either side of the lines between tiles."""
 import numpy as np
 import pytest
 import torch
@@ -64,3 +64,35 @@ def test_longest_reductions_on_matrix_tiles(N, M, T, K, O):
     assert nm.binding.raw().nm_bench_last_gemm_tile() > 0
     kept = K // M * N
     assert torch.equal(acc[0::2], torch.full_like(acc[0::2], kept * 8 * 128)) and torch.equal(acc[1::2], torch.full_like(acc[1::2], -kept * 8 * 127))
+
+
+# (kind of output, tile): one round and two, 128 and 96 columns, outputs written through and not, whole and ragged tiles, and the two-stage
+# tiles of short reductions
+@pytest.mark.parametrize("N, M", [(2, 4), (1, 4), (4, 4)])
+@pytest.mark.parametrize("T, K, O, kind, tile", [
+    (2750, 128, 576, "bf16", 115), (2750, 256, 640, "bf16", 127), (6010, 384, 768, "bf16", 115), (6010, 384, 576, "f32", 127), (16010, 128, 480, "bf16", 117),
+    (9010, 256, 1024, "q8", 117), (7990, 384, 1024, "q8", 127), (9010, 256, 1024, "f32", 127), (12300, 256, 768, "bf16", 117), (24600, 128, 480, "q8", 115),
+    (4100, 256, 2304, "bf16", 133), (700, 256, 768, "bf16", None)])
+def test_exact_on_every_tile_of_the_rule(N, M, T, K, O, kind, tile):
+    rng = np.random.default_rng(T + N + O)
+    W = rng.choice(np.array([-1.0, 1.0], np.float32), (O, K))
+    W[0], W[-1] = 1.0, -1.0
+    vals, meta, scales = nm.nm_compress(torch.from_numpy(W).cuda(), N, M, 4, layout=nm.NM_LAYOUT_TILED)
+    Wq = nm.nm_decompress_i8(vals, meta, O, K, N, M, 4, layout=nm.NM_LAYOUT_TILED)
+    X = torch.from_numpy(rng.choice(np.array([-128, 127, 3], np.int8), (T, K))).cuda()
+    want = (X.float() @ Wq.float().t().contiguous()).int()            # |sums| <= 384 * 7 * 128 < 2^24: exact in fp32
+    out = torch.empty((T, O), dtype={"bf16": torch.bfloat16, "f32": torch.float32, "q8": torch.int8}[kind], device="cuda")
+    acc = torch.empty((T, O), dtype=torch.int32, device="cuda")
+    ones = torch.ones(O, device="cuda")
+    for with_acc in (True, False):                                     # either way out of the tile
+        a = acc if with_acc and kind != "q8" else None
+        if kind == "q8":
+            nm.nm_gemm_q8(X, 1.0, vals, meta, ones, O, N, M, 4, 4096.0, out, layout=nm.NM_LAYOUT_TILED)
+            assert torch.equal(out, (want.float() / 4096.0).round().to(torch.int8))       # powers of two: one rounding here too
+        else:
+            nm.nm_gemm(X, 1.0, vals, meta, ones, O, N, M, 4, acc=a, out=out, out_dtype=2 if kind == "bf16" else 1, layout=nm.NM_LAYOUT_TILED)
+            assert torch.equal(out, want.to(out.dtype))                # one rounding, to nearest even, of an exact sum
+        if tile is not None:
+            assert nm.binding.raw().nm_bench_last_gemm_tile() == tile
+        if a is not None:
+            assert torch.equal(a, want)
