@@ -62,9 +62,10 @@ const char* nm_test_source_digest(void) { return NM_TEXT(NM_SOURCE_DIGEST); }
 
 int nm_bench_last_gemm_tile(void) { return g_last_tile.load(std::memory_order_relaxed); }
 
-int nm_test_gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)
+int nm_test_gemm_any_launches(int tokens, int K, int O, int N, int M, long long* tiles, unsigned* most_workgroups)
 {
-    return nm::gemm_any_launches(tokens, O, tiles, most_workgroups);
+    canonical_dense(N, M);
+    return nm::gemm_any_launches(tokens, K, O, N, M, tiles, most_workgroups);
 }
 
 int nm_test_few_tile(int tokens, int K, int O, int N, int M, int bits)

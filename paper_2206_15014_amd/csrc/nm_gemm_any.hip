@@ -38,8 +38,9 @@ static_assert((unsigned long long)any_workgroups(ANY_LAUNCH_TILES) * 256 < (1ull
 constexpr int KC = 256;                        // columns per chunk
 
 struct AnyPlan { int side; long long tiles_o, tiles; };        // of side x side outputs
-AnyPlan any_plan(int tokens, int O, bool chunks)
+AnyPlan any_plan(int tokens, int K, int O, int N, int M)
 {
+    const bool chunks = K > KC && (N < M || K >= 2 * KC);      // (dense: two whole ones; 1999 x 312 -> 872, 448 tiles: 6.6 us on the small tiles, 6.8)
     const long long big = ((tokens + 63ll) / 64) * ((O + 63ll) / 64);
     // Fewer than two 64 x 64 tiles per CU leave it short of wavefronts to cover the latency of a chunk.  With several chunks
     // the large tiles, which stage each operand half as often, are ahead from 400 on (2:4 int8, 1999 x 312 -> 936, 480 tiles: 7.0 -> 6.2 us,
@@ -49,8 +50,7 @@ AnyPlan any_plan(int tokens, int O, bool chunks)
     const long long tiles_o = (O - 1ll + side) / side;
     return AnyPlan{side, tiles_o, ((tokens - 1ll + side) / side) * tiles_o};
 }
-// (dense: two whole chunks; 1999 x 312 -> 872, 448 tiles: 6.6 us on the small tiles, 6.8)
-AnyPlan any_plan(const GemmArgs& a) { return any_plan(a.tokens, a.O, a.K > KC && (a.N < a.M || a.K >= 2 * KC)); }
+AnyPlan any_plan(const GemmArgs& a) { return any_plan(a.tokens, a.K, a.O, a.N, a.M); }
 
 constexpr int ROW = KC + 16;                   // LDS bytes per row: 16-byte reads of 8 consecutive rows cover all banks once
 constexpr int CROW = KC / 2 + 16;              // the same for rows of sparse-MFMA codes (16 bytes per 32 columns) ...
@@ -510,9 +510,9 @@ bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_e
     return true;
 }
 
-int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups)
+int gemm_any_launches(int tokens, int K, int O, int N, int M, long long* tiles, unsigned* most_workgroups)
 {
-    const AnyPlan plan = any_plan(tokens, O, false);
+    const AnyPlan plan = any_plan(tokens, K, O, N, M);
     *tiles = plan.tiles;
     *most_workgroups = any_workgroups(plan.tiles < ANY_LAUNCH_TILES ? plan.tiles : ANY_LAUNCH_TILES);
     return (int)((plan.tiles + ANY_LAUNCH_TILES - 1) / ANY_LAUNCH_TILES);

@@ -161,7 +161,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t st);
 // Every call the sparse-MFMA kernels do not take (nm_gemm_any.hip); part of launch_gemm's bracket.
 void launch_gemm_any(const GemmArgs& a, hipStream_t st);
 // How it divides a call (for the tests): launches, output tiles, workgroups of the largest launch.
-int gemm_any_launches(int tokens, int O, long long* tiles, unsigned* most_workgroups);
+int gemm_any_launches(int tokens, int K, int O, int N, int M, long long* tiles, unsigned* most_workgroups);
 // Ends of the bytes its tiles read of X, vals and meta; false: no tiles, a thread per output.
 bool gemm_any_reads(const GemmArgs& a, size_t* x_end, size_t* v_end, size_t* m_end);
 // `count` (1 .. GEMM_BATCH_MAX) GEMMs of one pattern, layout and output type: one launch where the

@@ -36,11 +36,11 @@ int nm_bench_smfmac_probe(int blocks, int iters, unsigned long long *counters_de
 int nm_bench_last_gemm_tile(void);
 
 /*
- * Test hook: how many launches nm_gemm would make of the kernel of the odd shapes for an output of
- * tokens x O, the number of its output tiles, and the workgroups (of 256 threads) of the largest
+ * Test hook: how many launches nm_gemm would make of the kernel of the odd shapes for a call on its tiles,
+ * the number of its output tiles, and the workgroups (of 256 threads) of the largest
  * launch.  Host arithmetic only.
  */
-int nm_test_gemm_any_launches(int tokens, int O, long long *tiles, unsigned *most_workgroups);
+int nm_test_gemm_any_launches(int tokens, int K, int O, int N, int M, long long *tiles, unsigned *most_workgroups);
 
 /*
  * Test hook: the tile id of the few-token kernels that nm_gemm would choose for one call in the

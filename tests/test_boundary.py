@@ -205,15 +205,23 @@ def test_gemm_batch_validates_before_launch():
     assert call([item()], layout=1) == -3                        # tiled layout needs K % 128 == 0
 
 
-@pytest.mark.parametrize("tokens,O", [(1, 1), (31, 3), (1 << 28, 193), (1 << 28, 64), ((1 << 31) - 1, 1), (1, (1 << 31) - 1), (1 << 24, 5000)])
-def test_odd_shape_gemm_never_launches_too_many_threads(tokens, O):
+def _any_launches(tokens, K, O, N, M):
+    tiles, most = ctypes.c_longlong(0), ctypes.c_uint(0)
+    n = binding.raw().nm_test_gemm_any_launches(tokens, K, O, N, M, ctypes.byref(tiles), ctypes.byref(most))
+    return n, tiles.value, most.value
+
+
+# (one chunk of 256 columns, and several, of which the large tiles take 400 and more instead of 512)
+@pytest.mark.parametrize("K,N,M,least", [(8, 2, 4, 512), (256, 2, 4, 512), (264, 2, 4, 400), (264, 4, 4, 512), (504, 8, 8, 512), (512, 4, 4, 400), (1000, 3, 8, 400)])
+@pytest.mark.parametrize("tokens,O", [(1, 1), (31, 3), (1 << 28, 193), (1 << 28, 64), ((1 << 31) - 1, 1), (1, (1 << 31) - 1), (1 << 24, 5000),
+                                      (64 * 399, 64), (64 * 399 + 1, 64), (64 * 511, 64), (64 * 511 + 1, 64), (64 * 40, 640), (64 * 40, 624)])
+def test_odd_shape_gemm_never_launches_too_many_threads(tokens, O, K, N, M, least):
     """nm_gemm on the kernel of the odd shapes: every launch has fewer than 2^32 threads, so a call cannot fail with
     part of it enqueued, and the launches cover the tiles."""
-    tiles, most = ctypes.c_longlong(0), ctypes.c_uint(0)
-    n = binding.raw().nm_test_gemm_any_launches(tokens, O, ctypes.byref(tiles), ctypes.byref(most))
-    side = 32 if -(-tokens // 64) * -(-O // 64) < 512 else 64
-    assert tiles.value == -(-tokens // side) * -(-O // side)
-    assert 0 < most.value * 256 < 1 << 32 and n * most.value >= tiles.value > (n - 1) * (1 << 23)
+    n, tiles, most = _any_launches(tokens, K, O, N, M)
+    side = 32 if -(-tokens // 64) * -(-O // 64) < least else 64
+    assert tiles == -(-tokens // side) * -(-O // side)
+    assert 0 < most * 256 < 1 << 32 and n * most >= tiles > (n - 1) * (1 << 23)
 
 
 @pytest.mark.parametrize("tokens,K,O,N,M,bits,tile", [
