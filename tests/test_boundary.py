@@ -26,7 +26,7 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, n), n
 
 
-def test_ring_kernels_come_first_in_their_code_objects_at_whole_kilobytes():
+def test_ring_kernels_come_first_in_their_code_objects_at_multiples_of_4_kilobytes():
     """Where a ring kernel lies in its code object shows in its time, so kernels added beside it must not move it."""
     data, objects = open(binding.library_path(), "rb").read(), 0
     for m in re.finditer(b"\x7fELF", data):
@@ -47,7 +47,7 @@ def test_ring_kernels_come_first_in_their_code_objects_at_whole_kilobytes():
                     (ring if b"gemm_dma_" in text else other).append(value)
         if ring:
             objects += 1
-            assert all(v % 1024 == 0 for v in ring)
+            assert all(v % 4096 == 0 for v in ring)
             assert not other or max(ring) < min(other)
     assert objects == 11                      # one per set of patterns
 
