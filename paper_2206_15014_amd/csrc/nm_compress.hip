@@ -772,7 +772,9 @@ decompress_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ 
 
 // The same from the tiled layout, a thread per unit (32 columns of one row): whole pieces in, lane-contiguous, 32 bytes out, so
 // that a wavefront's 16 rows x 128 columns are read as one run and written as whole lines.  Needs 16-byte aligned arrays.
-// 3072 x 768, 2:4 int8 6.1 -> 3.0 us.
+// 3072 x 768, 2:4 int8 6.1 -> 3.0 us.  A last block of one or two rows leaves a wavefront to eight lanes with 32 columns each one after the
+// other, and unless there are a dozen blocks beside it the byte kernel is done earlier (1 x 2048, 4:8 int4, 2.7 and 3.1 us; 17 x 8192 2.8 and 3.2; 129 x
+// 1024 equal; three rows 1.10 the other way).
 template <int N, int M, int BITS>
 __global__ void __launch_bounds__(256)
 decompress_units_kernel(const uint8_t* __restrict__ vals, const uint8_t* __restrict__ meta, int rows, int cols, uint32_t blocks, int8_t* __restrict__ Wq)
@@ -1098,7 +1100,8 @@ int launch_decompress(const void* vals, const void* meta, int rows, int cols, in
     const PackedArray pv = packed_values(cols, N, M, bits, layout), pm = packed_meta(cols, N, M, layout);
     const dim3 grid((unsigned)((total + 255) / 256));
     const long long blocks = (long long)((rows + 15) / 16) * (cols / 128);
-    if (layout && ((uintptr_t)vals | (uintptr_t)meta | (uintptr_t)Wq) % 16 == 0 && blocks < (1 << 25)) {      // (a launch holds fewer than 2^32 threads)
+    const bool rest = rows % 16 == 1 || rows % 16 == 2;
+    if (layout && !(rest && rows < 192) && ((uintptr_t)vals | (uintptr_t)meta | (uintptr_t)Wq) % 16 == 0 && blocks < (1 << 25)) {      // (a launch holds fewer than 2^32 threads)
         const dim3 wgs((unsigned)((blocks + 3) / 4));
 #define NM_CASE(n, m) \
         if (N == n && M == m) { \
