@@ -603,9 +603,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs& a, const int tiles
 // of 64 KB holds or more, so its place decides what its fetches meet: the same instructions at other offsets of the
 // code object, or in an object that the loader put elsewhere, were up to 8 % faster or slower where kernels follow one
 // another (one library loaded eight times, the same buffers: int8 chain at 12288 tokens 112 to 122 us).  So ring kernels
-// start at multiples of 4 KB, in front of everything else in their object.  BERT-large block at 49152 tokens, int8 chain at
-// 12288, BERT-base layers at 3001 tokens, us a pass on one GPU, each library alone in a process: 1 KB 513, 109 to 111, 100;
-// 2 KB 514, 111, 100; 4 KB 512, 107, 99; 8 KB 514, 108, 99; 16 KB 513, 108, 100; 64 KB 514, 106, 99.
+// start at one alignment, in front of everything else in their object, so that kernels added beside them do not move them.  Which
+// alignment matters little.  BERT-large block at 49152 tokens, int8 chain at 12288, BERT-base layers at 3001 tokens, us a pass on one GPU,
+// each library built whole and alone in a process, three processes each: 1 KB 515 to 516, 101.6 to 101.8, 102 to 103; 4 KB 515 to
+// 517, 102.6 to 102.8, 102; 64 KB 517 to 518, 103.5 to 103.7, 102 to 103.
 #define NM_RING_ALIGNED __attribute__((aligned(4096)))
 
 // One GEMM per launch.  Workgroup -> tile: each XCD (workgroups are dealt to the eight XCDs in
