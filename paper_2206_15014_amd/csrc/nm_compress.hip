@@ -539,9 +539,11 @@ compress_batch_kernel(const BatchArgs<BATCH_MAX> b)
 }
 
 // A call of more than 16 matrices, a whole encoder's: up to 48 per launch and two shares of rows per workgroup.  Bound by HBM.
-// Against launches of 16 matrices with one share: the 96 matrices of BERT-large (1.2 GB) 290 -> 284 us (4.9 TB/s read and
-// written; a large copy reaches 5.2), the 48 of BERT-base 90 -> 84, 24 of them 48 -> 45, 64 of 512 x 512 to 2048 63 -> 56, 64 of 256 x 256
-// to 1024 28 -> 24.  One share 270 and 90 for the first two, four 281 and 84.
+// Against launches of 16 matrices with one share, 2:4 int8, tiled: the 96 matrices of BERT-large (1.2 GB) 290 -> 286 us (4.9 TB/s read and
+// written; a large copy reaches 5.2), the 96 of two BERT-base 173 -> 164, 48 of 640 x 640 to 2560 67 -> 57, 40 of 300 x 1024 20 -> 15.
+// One share in the same launches is no better on the whole (11 sets of 20 to 96 matrices, four schemes and layouts each): ahead where a row is four
+// passes of a wavefront and the output tiled (BERT-large 274, 20 to 96 matrices of it 2 to 5 %), behind elsewhere (two BERT-base 176, 640 wide 73, BERT-large in
+// the row layout 256 and 263, large and base mixed 2:4 int4 107 and 110), and its runs spread more (BERT-large 272 to 304, two shares 285 to 287).
 template <int N, int M, int BITS, int RES>
 __global__ void __launch_bounds__(256)
 compress_stream_kernel(const BatchArgs<3 * BATCH_MAX> b)
