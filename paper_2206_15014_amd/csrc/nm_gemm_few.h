@@ -138,7 +138,7 @@ __device__ __forceinline__ void gemm_few_tile(GemmArgs& a, const int tiles_t, co
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft) part[(wave * NF + fo * FT + ft) * 64 + lane] = acc[fo][ft];
     __syncthreads();
-    // The largest output: one commit per workgroup here too (layer chain 226 x 384, 1:8 int8 31.4 -> 19.8 us, 93 x 384, 2:4 int4 23.1 -> 18.2).
+    // The largest output: one commit per workgroup here too (layer chain 93 x 384, 2:4 int4, replayed 22.8 -> 17.3 us, 226 x 384, 1:8 int8 18.2 -> 16.9).
     // Not for two fragments: the two barriers cost what the one commit less saves (a maximum that is never reset: 140 calls 3 % slower).
     // Not for 5:8 int8 either: with it the compiler orders that pattern's loop so that 600 x 3072 -> 768 takes 12.8 us, without 11.3.
     // Any other output is done once it is stored, and its way out lies next to the stores: past the commit's instructions the last
